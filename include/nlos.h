@@ -477,11 +477,15 @@ int nlos_poisson_noise(const float* tau, int64_t n, const double* sigma_n, uint6
  * at layer round((4 slope)^2 (x^2 + y^2) M), slope = w / (M c dt), layers past
  * the window dropped; back to time bins by the mean over each bin's v-span
  * [j^2, (j+1)^2) divided by (J dz)^3; Gaussian jitter.  Output float
- * [N][N][M].  The first call for a size creates and keeps an FFT plan (the
- * FFT library allocates its tables then); later calls allocate nothing.  A
+ * [N][N][M].  The convolution is the sum over the volume's samples (at most
+ * one per pixel) and the cone's layers, in 64-bit fixed point; its workspace
+ * is about 18 N^2 + 8 M bytes, 256-byte aligned.  Thin, wide volumes
+ * (N^2 > 1500 M) and rows of more than 16384 bins go through fp64 FFTs
+ * instead: the first such call for a size creates and keeps an FFT plan (the
+ * FFT library allocates its tables then), later calls allocate nothing, a
  * failure inside the FFT library gives NLOS_EHIP with nlos_last_hip_error()
- * = -1.  The workspace (two complex fp64 volumes + FFT work) is about
- * 32 * (2N)^2 * 2M bytes, 256-byte aligned.
+ * = -1, and the workspace (two complex fp64 volumes + FFT work) is about
+ * 32 * (2N)^2 * 2M bytes.
  */
 int nlos_lct_workspace_bytes(const nlos_params* p, size_t* bytes);
 

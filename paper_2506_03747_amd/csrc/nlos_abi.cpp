@@ -1582,6 +1582,10 @@ int nlos_lct_workspace_bytes(const nlos_params* p, size_t* bytes)
     const int dev = device_check();
     if (dev != NLOS_OK) return dev;
     size_t work = 0;
+    if (nlos::lct_by_samples(a)) {
+        *bytes = nlos::lct_samples_layout(a).bytes;
+        return NLOS_OK;
+    }
     if (nlos::lct_fft_work_bytes(a.N, a.M, &work) != 0) {
         g_last_hip = -1;
         return NLOS_EHIP;
@@ -1606,6 +1610,10 @@ int nlos_lct_forward(const nlos_params* p, const float* depth, const float* albe
     a.depth = depth;
     a.albedo = albedo;
     a.mask = mask;
+    if (nlos::lct_by_samples(a)) {
+        const hipError_t e = nlos::launch_lct_samples(a, ws, out, (hipStream_t)stream);
+        return e == hipSuccess ? NLOS_OK : hip_fail(e);
+    }
     unsigned char* w = static_cast<unsigned char*>(ws);
     double2* vol = reinterpret_cast<double2*>(w);
     double2* psf = reinterpret_cast<double2*>(w + (size_t)n3 * 16);

@@ -388,6 +388,33 @@ hipError_t launch_poisson(const float* tau, int64_t n, const double* sigma_n, ui
                           hipStream_t st);
 constexpr int kNoiseMomentBlocks = 1024;
 
+// By samples: pixels in any order, their count and largest weight.
+struct LctPixel {
+    double w;        // albedo / (J M)
+    uint32_t c;      // coarse v-sample
+    uint32_t xy;     // x << 16 | y
+};
+struct LctList {
+    unsigned long long max_bits;   // bits of the largest weight
+    int32_t n;
+    int32_t ties;                  // 1: an offset has two nearest layers
+};
+constexpr int kLctPer = 16;             // time bins per thread, through registers
+constexpr int kLctV = 5;                // consecutive outputs per lane in the jitter
+constexpr int kLctMaxRow = 1 << 14;     // M whose row fits in LDS
+constexpr size_t kLctLds = 163840;
+constexpr int64_t kLctThin = 1500;      // N^2 / M up to which the sum by samples is the faster one
+bool lct_by_samples(const LctArgs& a);
+// u64 words per row: M bins, R zeros on either side, odd so that rows of a
+// power of two start on different banks.
+__host__ __device__ inline int lct_pitch(const LctArgs& a) { return (a.M + 2 * a.R) | 1; }
+// Workspace: the cone's table, then the pixels, the time bins' gains and the
+// list's head at these byte offsets.
+struct LctLayout {
+    size_t pix, gain, list, bytes;
+};
+LctLayout lct_samples_layout(const LctArgs& a);
+hipError_t launch_lct_samples(const LctArgs& a, void* ws, float* out, hipStream_t st);
 int lct_fft_work_bytes(int N, int M, size_t* bytes);
 hipError_t launch_lct(const LctArgs& a, double2* vol, double2* psf, void* fft_work, float* out, hipStream_t st,
                       int* fft_status);

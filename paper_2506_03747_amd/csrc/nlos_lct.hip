@@ -1,10 +1,23 @@
 // The paper's FFT ("light-cone") forward route, gfx950: Section 2 rewrites
 // Eq. (1) with u = z^2, v = (t c / 2)^2 as a 3-D convolution of the
-// resampled volume with a cone (Eq. (3)-(5)), evaluated with 3-D FFTs
-// (Algorithm 1 steps 1.1-2.3).  A cross-check of the direct operator, for a
+// resampled volume with a cone (Eq. (3)-(5)), which Algorithm 1 steps 1.1-2.3
+// evaluate with 3-D FFTs.  A cross-check of the direct operator, for a
 // confocal N x N scan co-registered with the depth map, no stand-off, no
 // cosine terms (Eq. (1) as printed), M = T a power of two.
 //
+// The volume holds at most one sample per pixel and the cone one layer (two
+// at a tie) per lateral offset, so the convolution is a sum of N^4 shifted
+// samples, 1 / 500 of the multiplications that a dense product needs; the
+// transforms spend their time streaming zeros.  Two evaluations:
+//
+//   by samples (lct_by_samples; every size but thin, wide volumes)
+//   k_lct_cone    the cone's layer of each lateral offset |dx|, |dy|.
+//   k_lct_pixels  present pixels: coarse v-sample and weight, compacted.
+//   k_lct_sum     a workgroup per row piece of scan points: every pixel's
+//                 weight into the points' LDS rows, then the time resampling,
+//                 the jitter and the write-out.
+//
+//   by transforms (N^2 > kLctThin M, or rows past the LDS)
 //   k_lct_clear / k_lct_volume   R_z V on the (2N, 2N, 2M) zero-padded grid:
 //       pixel (x, y) at depth layer j = floor(D / dz) (dz = c dt / 2) adds
 //       albedo / (J M), J = j + 1, at coarse v-sample (J^2 - 1) / M (the
@@ -37,21 +50,51 @@ __global__ void k_lct_clear(double2* a, int64_t n)
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) a[i] = make_double2(0.0, 0.0);
 }
 
+// The sample of pixel p: coarse v-sample c and weight albedo / (J M); false
+// where the pixel is absent or past the window.
+__device__ __forceinline__ bool lct_sample(const LctArgs& a, int64_t p, int* c, double* w)
+{
+    const int M = a.M;
+    const double D = (double)a.depth[p];
+    const double A = a.albedo ? (double)a.albedo[p] : 0.5;
+    const bool present = (!a.mask || a.mask[p] != 0) && A > 0.0 && isfinite(D) && D > 0.0;
+    if (!present) return false;
+    const double jd = floor(D / a.dz);
+    if (!(jd >= 0.0 && jd < (double)M)) return false;
+    const int64_t J = (int64_t)jd + 1;
+    *c = (int)((J * J - 1) / M);
+    *w = (1.0 / (double)J) / (double)M * A;
+    return true;
+}
+
+// Lateral offset (nx, ny) cells: its distance from the cone's axis in layers
+// over M, the layer floor and the smallest distance to a layer of 0 .. 2M - 1
+// (the candidates next to zs M: the true nearest layers are among them).
+__device__ __forceinline__ double lct_cone_best(const LctArgs& a, int nx, int ny, double* zs, double* kf)
+{
+    const int N = a.N, M = a.M;
+    const double x = (double)nx / (double)N, y = (double)ny / (double)N;
+    *zs = a.cone * (x * x + y * y);
+    *kf = floor(*zs * (double)M);
+    double best = fabs(*zs - (double)(2 * M - 1) / (double)M);
+    for (int d = -1; d <= 2; ++d) {
+        const double kk = *kf + d;
+        if (kk < 0.0 || kk > (double)(2 * M - 1)) continue;
+        best = fmin(best, fabs(*zs - kk / (double)M));
+    }
+    return best;
+}
+
 __global__ void k_lct_volume(const LctArgs a, double2* vol)
 {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int N = a.N, M = a.M;
     if (p >= (int64_t)N * N) return;
-    const double D = (double)a.depth[p];
-    const double A = a.albedo ? (double)a.albedo[p] : 0.5;
-    const bool present = (!a.mask || a.mask[p] != 0) && A > 0.0 && isfinite(D) && D > 0.0;
-    if (!present) return;
-    const double jd = floor(D / a.dz);
-    if (!(jd >= 0.0 && jd < (double)M)) return;
-    const int64_t J = (int64_t)jd + 1;
-    const int64_t c = (J * J - 1) / M;
+    int c;
+    double w;
+    if (!lct_sample(a, p, &c, &w)) return;
     const int x = (int)(p / N), y = (int)(p % N);
-    vol[((int64_t)x * 2 * N + y) * 2 * M + c] = make_double2((1.0 / (double)J) / (double)M * A, 0.0);
+    vol[((int64_t)x * 2 * N + y) * 2 * M + c] = make_double2(w, 0.0);
 }
 
 // One thread per element of the (2N, 2N, 2M) grid (coalesced stores); each
@@ -70,15 +113,8 @@ __global__ void k_lct_psf(const LctArgs a, double2* psf, int64_t n3)
         double v = 0.0;
         if (k < M) {
             const int nx = ix < N ? ix : ix - 2 * N, ny = iy < N ? iy : iy - 2 * N;
-            const double x = (double)nx / (double)N, y = (double)ny / (double)N;
-            const double zs = a.cone * (x * x + y * y);
-            const double kf = floor(zs * (double)M);
-            double best = fabs(zs - (double)(2 * M - 1) / (double)M);
-            for (int d = -1; d <= 2; ++d) {
-                const double kk = kf + d;
-                if (kk < 0.0 || kk > (double)(2 * M - 1)) continue;
-                best = fmin(best, fabs(zs - kk / (double)M));
-            }
+            double zs, kf;
+            const double best = lct_cone_best(a, nx, ny, &zs, &kf);
             if (fabs(zs - (double)k / (double)M) == best) v = 1.0;
         }
         psf[p] = make_double2(v, 0.0);
@@ -126,6 +162,274 @@ __global__ void k_lct_jitter(const LctArgs a, const double* pre, float* out)
         if (src >= 0 && src < M) acc += a.taps[i + a.R] * row[src];
     }
     out[p] = (float)acc;
+}
+
+// ---------------------------------------------------------------------------
+// By samples.
+//
+// Table entry of lateral offset (|dx|, |dy|), 0 .. N - 1 each (the cone
+// depends on the offset's squares only): the layer nearest its distance, M
+// when that is past the window, and kLctTie when the next layer is as near.
+constexpr uint32_t kLctTie = 0x8000u;
+constexpr double kLctInt = 4503599627370496.0;   // 2^52
+
+__global__ void __launch_bounds__(256) k_lct_cone(const LctArgs a, uint16_t* tab, double* gain, LctList* list)
+{
+    const int N = a.N, M = a.M;
+    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    for (int64_t j = p; j < M; j += (int64_t)gridDim.x * 256) {
+        // time bin j: over the 2 j + 1 fine samples of its span and (J dz)^3
+        const double t = (double)(j + 1) * a.dz;
+        gain[j] = 1.0 / ((double)(2 * j + 1) * (t * t * t));
+    }
+    if (p == 0) {
+        list->n = 0;
+        list->max_bits = 0ull;
+        list->ties = 0;
+    }
+    if (p >= (int64_t)N * N) return;
+    double zs, kf;
+    const double best = lct_cone_best(a, (int)(p / N), (int)(p % N), &zs, &kf);
+    // (a nearest layer of 0 .. M - 1 is kf or kf + 1; past the grid kf >= M)
+    const bool lo = kf < (double)M && fabs(zs - kf / (double)M) == best;
+    const bool hi = kf + 1.0 < (double)M && fabs(zs - (kf + 1.0) / (double)M) == best;
+    uint32_t v = (uint32_t)M;
+    if (hi) v = (uint32_t)kf + 1u;
+    if (lo) v = (uint32_t)kf | (hi ? kLctTie : 0u);
+    tab[p] = (uint16_t)v;
+}
+
+// Present pixels, appended in any order (every later sum is of integers): one
+// counter add and one maximum per wavefront.  Also whether the table has ties.
+__global__ void __launch_bounds__(256)
+    k_lct_pixels(const LctArgs a, const uint16_t* tab, LctPixel* pix, LctList* list)
+{
+    const int N = a.N;
+    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (p < (int64_t)N * N && (tab[p] & kLctTie)) list->ties = 1;
+    int c = 0;
+    double w = 0.0;
+    const bool on = p < (int64_t)N * N && lct_sample(a, p, &c, &w);
+    const unsigned long long m = __ballot(on);
+    if (m == 0ull) return;
+    const int lane = (int)threadIdx.x & 63;
+    double mx = w;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) mx = fmax(mx, __shfl_xor(mx, d));
+    int base = 0;
+    if (lane == 0) {
+        base = atomicAdd(&list->n, (int)__popcll(m));
+        // (weights are positive: their bits order as they do)
+        atomicMax(&list->max_bits, (unsigned long long)__double_as_longlong(mx));
+    }
+    base = __builtin_amdgcn_readfirstlane(base);
+    if (on) {
+        const int64_t i = base + __popcll(m & ((1ull << lane) - 1ull));
+        pix[i] = LctPixel{w, (uint32_t)c, (uint32_t)(p / N) << 16 | (uint32_t)(p % N)};
+    }
+}
+
+// A workgroup owns NP scan points (x', y'0 .. y'0 + NP - 1): one row of M
+// 64-bit sums each in LDS.  A lane takes a pixel and adds its weight at bin
+// c + layer(|x' - x|, |y' - y|) of each row: per pair a table address, a
+// 16-bit table read (2 N^2 bytes, mostly from the L1; a copy in LDS measured
+// no faster and took the second workgroup's room), add, compare, ds_add_u64.
+// Weights are fixed point, w s rounded to an integer of at most 2^51 with s at
+// most 2^62 / (N^2 max w), so that a row's sums cannot wrap and do not depend
+// on the order: a sample is within 2^-52 of the largest weight (2^-63 N^2
+// where N > 45), below the noise of fp64 transforms.
+// Bound: the LDS adds (bank conflicts included) and VALU, about 15 cycles per
+// wavefront and pair; then the write-out's fp64 resampling and jitter.  128^2
+// points and pixels, 1024 bins: 13.2 ms by transforms; 367 us with 1024
+// threads, a table read and add at a time; 220 us with the reads of all rows
+// before the adds and the jitter from a sliding window; 170 us (back to back) with four
+// workgroups of 512 threads per CU, so that one's write-out runs under
+// another's adds.
+template <int NP, bool TIES>
+__device__ __forceinline__ void lct_add(const LctPixel* __restrict__ pix, int n, const uint16_t* __restrict__ tab,
+                                        int N, int M, int x1, int y1, double s,
+                                        unsigned long long* rows, int pitch, int tid, int nthr)
+{
+    if (tid >= n) return;
+    LctPixel q = pix[tid];
+    for (int i = tid; i < n; i += nthr) {
+        const int x = (int)(q.xy >> 16), y = (int)(q.xy & 0xffffu);
+        const uint32_t c = q.c;
+        // round(w s) < 2^51 as the low bits of w s + 2^52
+        const unsigned long long inc =
+            (unsigned long long)__double_as_longlong(fma(q.w, s, kLctInt)) & 0x000fffffffffffffull;
+        q = pix[min(i + nthr, n - 1)];   // the next one lands while this one is added
+        const int row = abs(x1 - x) * N;
+        // every row's table entry before any add, so that one wait serves all
+        // (a row past the grid repeats the last one; it is not written out)
+        uint32_t v[NP];
+#pragma unroll
+        for (int r = 0; r < NP; ++r) {
+            v[r] = tab[row + abs(min(y1 + r, N - 1) - y)];
+        }
+#pragma unroll
+        for (int r = 0; r < NP; ++r) {
+            const uint32_t k = (TIES ? v[r] & ~kLctTie : v[r]) + c;
+            unsigned long long* dst = rows + (size_t)r * pitch + k;
+            if (k < (uint32_t)M) __hip_atomic_fetch_add(dst, inc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (TIES && (v[r] & kLctTie) && k + 1u < (uint32_t)M)
+                __hip_atomic_fetch_add(dst + 1, inc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    }
+}
+
+template <int NP>
+__global__ void __launch_bounds__(1024) k_lct_sum(const LctArgs a, const uint16_t* __restrict__ tab,
+                                                  const LctPixel* __restrict__ pix, const double* __restrict__ gain,
+                                                  const LctList* __restrict__ list, float* __restrict__ out)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int N = a.N, M = a.M, R = a.R, nthr = (int)blockDim.x, tid = (int)threadIdx.x;
+    const int pitch = lct_pitch(a);   // R zeros around each row, for the jitter
+    unsigned long long* rows = reinterpret_cast<unsigned long long*>(smem);
+    const int nt = (N + NP - 1) / NP;
+    const int x1 = (int)blockIdx.x / nt, y1 = (int)(blockIdx.x % nt) * NP;
+    const int n = list->n;
+    const double wmax = __longlong_as_double((long long)list->max_bits);
+    const double per = fmin(4611686018427387904.0 / ((double)N * (double)N), 2251799813685248.0);
+    const double s = wmax > 0.0 ? per / wmax : 0.0;
+    for (int i = tid; i < NP * pitch; i += nthr) rows[i] = 0ull;
+    const bool ties = list->ties != 0;
+    __syncthreads();
+    if (ties)
+        lct_add<NP, true>(pix, n, tab, N, M, x1, y1, s, rows + R, pitch, tid, nthr);
+    else
+        lct_add<NP, false>(pix, n, tab, N, M, x1, y1, s, rows + R, pitch, tid, nthr);
+    __syncthreads();
+    // time bin j: the mean over its fine v-span [j^2, (j + 1)^2) (at most three
+    // coarse samples), over (J dz)^3; in place, through registers
+    // (an infinite weight leaves no number anywhere, as the transforms do)
+    const double inv = !(wmax > 0.0) ? 0.0 : isfinite(wmax) ? wmax / per : __longlong_as_double(0x7ff8000000000000ll);
+    const int lm = 31 - __clz(M);
+    double pre[kLctPer];
+#pragma unroll
+    for (int e = 0; e < kLctPer; ++e) {
+        const int i = tid + e * nthr;
+        pre[e] = 0.0;
+        if (i >= NP * M) continue;
+        const int r = i >> lm, j = i & (M - 1);
+        const unsigned long long* col = rows + (size_t)r * pitch + R;
+        const int lo = j * j, hi = lo + 2 * j + 1;   // (at most 2^28)
+        const int c0 = lo >> lm, c1 = (hi - 1) >> lm;
+        double sum = 0.0;
+        for (int c = c0; c <= c1; ++c) sum += (double)(min(hi, (c + 1) << lm) - max(lo, c << lm)) * (double)col[c];
+        pre[e] = sum * inv * gain[j];
+    }
+    __syncthreads();
+    double* rowd = reinterpret_cast<double*>(rows);
+#pragma unroll
+    for (int e = 0; e < kLctPer; ++e) {
+        const int i = tid + e * nthr;
+        if (i < NP * M) rowd[(size_t)(i >> lm) * pitch + R + (i & (M - 1))] = pre[e];
+    }
+    __syncthreads();
+    // jitter: a lane makes kLctV consecutive outputs from a sliding window, one
+    // LDS read per tap for all of them (lanes kLctV doubles apart: every bank
+    // in turn, as kLctV is odd)
+    const int nseg = (M + kLctV - 1) / kLctV;
+    for (int i = tid; i < NP * nseg; i += nthr) {
+        const int r = i / nseg, t0 = (i - r * nseg) * kLctV;
+        if (y1 + r >= N) break;
+        const int last = pitch - 1;
+        const double* h = rowd + (size_t)r * pitch;
+        // output t0 + m, tap k: row word t0 + m + 2 R - k
+        double w[kLctV], acc[kLctV];
+#pragma unroll
+        for (int m = 0; m < kLctV; ++m) {
+            w[m] = h[min(t0 + m + 2 * R, last)];
+            acc[m] = a.taps[0] * w[m];
+        }
+        for (int k = 1; k <= 2 * R; ++k) {
+#pragma unroll
+            for (int m = kLctV - 1; m > 0; --m) w[m] = w[m - 1];
+            w[0] = h[t0 + 2 * R - k];
+#pragma unroll
+            for (int m = 0; m < kLctV; ++m) acc[m] += a.taps[k] * w[m];
+        }
+        float* o = out + ((size_t)x1 * N + (y1 + r)) * M + t0;
+#pragma unroll
+        for (int m = 0; m < kLctV; ++m)
+            if (t0 + m < M) o[m] = (float)acc[m];
+    }
+}
+
+// Scan points per workgroup, threads and LDS of k_lct_sum.  4096 bins in all
+// leave room for four workgroups per CU (8192 and two: 1.13 times the time at
+// 128^2, 1024 bins); fewer points while that leaves CUs idle.  A thread
+// resamples at most kLctPer bins, so the longest rows take 1024 threads.
+struct LctShape {
+    int np, threads;
+    size_t lds;
+};
+
+static LctShape lct_shape(const LctArgs& a)
+{
+    LctShape s{8, 512, 0};
+    while (s.np > 1 && ((int64_t)s.np * a.M > 4096 || (int64_t)a.N * ((a.N + s.np - 1) / s.np) < 512)) s.np /= 2;
+    if (s.np * a.M > s.threads * kLctPer) s.threads = 1024;
+    s.lds = (size_t)s.np * lct_pitch(a) * 8;
+    return s;
+}
+
+// The sum by samples costs N^4 adds (0.41 to 0.75 ps each), the transforms about
+// 100 ps for each of their 8 N^2 M grid points; thin, wide volumes are the only
+// ones where the transforms cost less.
+bool lct_by_samples(const LctArgs& a)
+{
+    return a.M <= kLctMaxRow && (int64_t)a.N * a.N <= kLctThin * a.M;
+}
+
+LctLayout lct_samples_layout(const LctArgs& a)
+{
+    const size_t n2 = (size_t)a.N * a.N;
+    LctLayout l;
+    l.pix = (n2 * 2 + 255) & ~(size_t)255;
+    l.gain = l.pix + ((n2 * sizeof(LctPixel) + 255) & ~(size_t)255);
+    l.list = l.gain + (((size_t)a.M * 8 + 255) & ~(size_t)255);
+    l.bytes = l.list + 256;
+    return l;
+}
+
+template <int NP>
+static hipError_t launch_lct_sum(const LctArgs& a, const LctShape& sh, const uint16_t* tab, const LctPixel* pix,
+                                 const double* gain, const LctList* list, float* out, hipStream_t st)
+{
+    const hipError_t e = hipFuncSetAttribute((const void*)k_lct_sum<NP>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh.lds);
+    if (e != hipSuccess) return e;
+    const unsigned blocks = (unsigned)(a.N * ((a.N + NP - 1) / NP));
+    hipLaunchKernelGGL(k_lct_sum<NP>, dim3(blocks), dim3((unsigned)sh.threads), sh.lds, st, a, tab, pix, gain, list, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_lct_samples(const LctArgs& a, void* ws, float* out, hipStream_t st)
+{
+    const LctLayout l = lct_samples_layout(a);
+    unsigned char* w = static_cast<unsigned char*>(ws);
+    uint16_t* tab = reinterpret_cast<uint16_t*>(w);
+    LctPixel* pix = reinterpret_cast<LctPixel*>(w + l.pix);
+    double* gain = reinterpret_cast<double*>(w + l.gain);
+    LctList* list = reinterpret_cast<LctList*>(w + l.list);
+    const LctShape sh = lct_shape(a);
+    if (a.M > kLctMaxRow || a.N > 65535 || sh.lds > kLctLds || sh.np * a.M > sh.threads * kLctPer)
+        return hipErrorInvalidValue;
+    const unsigned nb = (unsigned)(((int64_t)a.N * a.N + 255) / 256);
+    hipLaunchKernelGGL(k_lct_cone, dim3(nb), dim3(256), 0, st, a, tab, gain, list);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_lct_pixels, dim3(nb), dim3(256), 0, st, a, tab, pix, list);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    switch (sh.np) {
+    case 8: return launch_lct_sum<8>(a, sh, tab, pix, gain, list, out, st);
+    case 4: return launch_lct_sum<4>(a, sh, tab, pix, gain, list, out, st);
+    case 2: return launch_lct_sum<2>(a, sh, tab, pix, gain, list, out, st);
+    default: return launch_lct_sum<1>(a, sh, tab, pix, gain, list, out, st);
+    }
 }
 
 // ---------------------------------------------------------------------------
