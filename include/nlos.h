@@ -380,12 +380,12 @@ int nlos_tick_graph_destroy(nlos_tick_graph* graph);
  * Rs = ceil(6 sigma), 0 <= k < T, with w and u exactly as in nlos_forward.
  * Arrivals outside the window still reach in-window bins within Rs.
  * Requires fwhm_ps > 0 and sigma * 6 <= 1024 bins; one T-bin histogram of
- * 64-bit bins must fit in LDS (T <= ~20000).  For Rs of 12, 16 or 20 bins
- * (when the rows fit in LDS) the Gaussian samples are taken as a series in
- * the sub-bin offset t = u - floor(u) - 1/2: each pair adds w (-t)^m,
- * m <= 7 (Rs = 12) or m <= 5 (Rs = 16, 20), and the rows are convolved with
- * N^(m) / m!; the series is within 7e-8 resp. 1.2e-6 (relative L2 over the
- * support) of the samples.
+ * 64-bit bins must fit in LDS (T <= ~20000).  For sigma >= 1.2 bins (when the
+ * rows fit in LDS) the Gaussian samples are taken as polynomials in the
+ * sub-bin offset t = u - floor(u) - 1/2 of 8 terms (sigma < 1.6), 7 (< 2.5),
+ * 6 (< 4.9) or 5: each pair adds w (-t)^m, and the rows are convolved with the
+ * polynomials' coefficients; they are within 2.5e-8 (relative L2 over the
+ * support, root mean square over t) of the samples.
  */
 int nlos_forward_smooth_workspace_bytes(const nlos_params* p, int32_t n_patches, size_t* bytes);
 
@@ -394,10 +394,10 @@ int nlos_forward_smooth(const nlos_params* p, const float* patches, int32_t n_pa
                         const int32_t* n_active, float* out, void* ws, size_t ws_bytes, void* stream);
 
 /* Workspace of nlos_adjoint: per-record partial gradients (fp64) of each
- * range of scan points; for support radii ceil(6 sigma) of 12, 16 or 20 bins
- * it starts with the correlations of the upstream gradient rows with the
- * Gaussian's derivatives (fp32 [nx*ny][n][T + 2 radius], n = 9 at radius 12,
- * 7 at 16 and 20).  256-byte aligned. */
+ * range of scan points; for sigma >= 1.2 bins it starts with the correlations
+ * of the upstream gradient rows with the polynomials' coefficients (fp32
+ * [nx*ny][T + 2 radius][n | 1], both sizes rounded up to 4, n one more than the
+ * forward's terms).  256-byte aligned. */
 int nlos_adjoint_workspace_bytes(const nlos_params* p, int32_t n_patches, size_t* bytes);
 
 /*
@@ -409,11 +409,10 @@ int nlos_adjoint_workspace_bytes(const nlos_params* p, int32_t n_patches, size_t
  * (records past *n_active get zeros).  Per pair dL/dw = sum_k G N(x_k) and
  * dL/du = w sum_k G (x_k / sigma^2) N(x_k), x_k = k + 1/2 - u, chained
  * through w(z, n, a) and u(z).  The step of the support with floor(u) is
- * not differentiated (below the tail at 6 sigma).  For support radii of 12,
- * 16 or 20 bins both sums are evaluated as series in the sub-bin offset
- * (t = u - floor(u) - 1/2, terms up to t^7 at radius 12, t^5 at 16 and 20)
- * of precomputed correlations of G with the Gaussian's derivatives.  Deterministic: partial sums per scan
- * range are added in a fixed order.
+ * not differentiated (below the tail at 6 sigma).  For sigma >= 1.2 bins both
+ * sums are evaluated as a polynomial in the sub-bin offset and its derivative,
+ * from precomputed correlations of G with the coefficients.  Deterministic:
+ * partial sums per scan range are added in a fixed order.
  */
 int nlos_adjoint(const nlos_params* p, const float* patches, int32_t n_patches, const int32_t* n_active,
                  const float* grad_out, float* grad_patches, void* ws, size_t ws_bytes, void* stream);

@@ -10,6 +10,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <utility>
 #include <vector>
 
 #include "nlos.h"
@@ -521,6 +522,33 @@ int plan_geom_batch(const nlos_depth_request* reqs, int32_t n, GeomBatch* b)
 // Smooth forward and adjoint (confocal).
 constexpr int kSmoothMaxRadius = 1024;
 
+double smooth_sigma(const nlos_params* p) { return p->fwhm_ps / (2.0 * std::sqrt(2.0 * std::log(2.0))) / p->bin_ps; }
+
+// The polynomials of n terms for width sigma (MomentFit): coef[m][j] is the
+// coefficient of s^m in the Lagrange polynomial of node j.
+nlos::MomentFit moment_fit(double sigma, int rs, int n)
+{
+    const double pi = 3.14159265358979323846;
+    nlos::MomentFit f;
+    std::memset(&f, 0, sizeof(f));
+    f.sigma = sigma;
+    f.norm = 1.0 / (sigma * std::sqrt(2.0 * pi));
+    f.n = n;
+    f.Rs = rs;
+    for (int j = 0; j < n; ++j) f.node[j] = 2 * j + 1 == n ? 0.0 : 0.5 * std::cos(pi * (2 * j + 1) / (2.0 * n));
+    for (int j = 0; j < n; ++j) {
+        double c[nlos::kMaxMoments] = {1.0};
+        int deg = 0;
+        for (int i = 0; i < n; ++i) {
+            if (i == j) continue;
+            const double q = 1.0 / (f.node[j] - f.node[i]);
+            for (int m = ++deg; m >= 0; --m) c[m] = ((m > 0 ? c[m - 1] : 0.0) - (m < deg ? c[m] * f.node[i] : 0.0)) * q;
+        }
+        for (int m = 0; m < n; ++m) f.coef[m * nlos::kMaxMoments + j] = c[m];
+    }
+    return f;
+}
+
 int smooth_setup(const nlos_params* p, const float* patches, int32_t n_patches, const int32_t* n_active,
                  nlos::SmoothArgs* a)
 {
@@ -531,7 +559,7 @@ int smooth_setup(const nlos_params* p, const float* patches, int32_t n_patches, 
     if (n_patches > 0 && !patches) return NLOS_EINVAL;
     if ((patches && !aligned(patches, 16)) || (n_active && !aligned(n_active, 4))) return NLOS_EINVAL;
     std::memset(a, 0, sizeof(*a));
-    const double sigma = p->fwhm_ps / (2.0 * std::sqrt(2.0 * std::log(2.0))) / p->bin_ps;
+    const double sigma = smooth_sigma(p);
     const double rs = std::ceil(6.0 * sigma);
     if (!(rs <= (double)kSmoothMaxRadius) || !(sigma > 1e-3)) return NLOS_EINVAL;
     a->patches = reinterpret_cast<const float4*>(patches);
@@ -543,7 +571,6 @@ int smooth_setup(const nlos_params* p, const float* patches, int32_t n_patches, 
     a->cy = p->relay.cy;
     a->s = p->standoff_m;
     a->inv = 1.0 / (kC * (p->bin_ps * 1e-12));
-    a->sigma = (float)sigma;
     a->norm = (float)(1.0 / (sigma * std::sqrt(2.0 * 3.14159265358979323846)));
     a->inv_s2 = (float)(1.0 / (sigma * sigma));
     a->c1 = (float)std::exp(-1.0 / (sigma * sigma));
@@ -557,8 +584,10 @@ struct SmoothPlan {
     int tx, ty;
     int64_t tiles, n_blocks;
     size_t lds;
-    int moments;   // 1: k_smooth_mom (moment rows), 0: k_smooth (taps)
-    int stride;    // u64 bins per LDS row
+    int moments;   // moment rows per scan point (k_smooth_mom), 0: by taps (k_smooth)
+    int stride;    // by taps: u64 bins per LDS row
+    int wg;        // moments: workgroups per CU
+    size_t taps_bytes;
 };
 
 size_t smooth_lds(int nh, int stride) { return (size_t)nh * stride * 8 + (size_t)nh * 12 + 64 * 4 + 64; }
@@ -567,36 +596,39 @@ int smooth_plan(const nlos_params* p, int32_t n_patches, int rs, SmoothPlan* sp,
 {
     static const int shapes[5][2] = {{4, 4}, {4, 2}, {2, 2}, {2, 1}, {1, 1}};
     const int T = p->n_bins;
-    // moments of the sub-bin offset when the support radius has a compiled
-    // variant and the moment rows (with a halo of rs bins on both sides) fit
-    sp->moments = 0;
+    // moments of the sub-bin offset when the width takes them and the rows of
+    // one scan point (with a halo of rs bins on both sides) fit.  Two
+    // workgroups per CU before more points in one, as one's write-out then runs
+    // under the other's adds: 128^2 points and patches at radius 12, 1024 bins,
+    // 0.96 ms with two of one point, 1.13 with one of two; 64^2 points, 512
+    // bins at radius 16, 64 us with two of three, 72 with two of two, 93 with
+    // one of three.
     sp->stride = T;
-    if (nlos::smooth_moments_radius(rs)) {
-        int stride = (T + 2 * rs + 1) & ~1;
-        const nlos::SmoothMomShape sh = nlos::smooth_mom_shape(rs);
-        const int64_t rows = (int64_t)sh.points * sh.moments;
-        // rows that take more than half the LDS leave one workgroup per CU:
-        // then the compile-time pitch, which costs no occupancy
-        if ((size_t)rows * stride * 8 + 2048 > kLdsMax / 2 && stride <= nlos::smooth_mom_pitch(rs))
-            stride = nlos::smooth_mom_pitch(rs);
-        const size_t lds = (size_t)rows * stride * 8 + 2048;
-        if (lds <= kLdsMax && rows * (T + 2 * rs) <= 24 * (int64_t)nlos::kBlock) {
-            sp->moments = 1;
-            sp->stride = stride;
-            sp->tx = sh.points;
-            sp->ty = 1;
-            sp->tiles = (int64_t)((p->relay.nx + sp->tx - 1) / sp->tx) * p->relay.ny;
-            int64_t sv = 1;
-            if (sp->tiles < kTargetBlocks) {
-                sv = (kTargetBlocks + sp->tiles - 1) / sp->tiles;
-                sv = std::min<int64_t>(sv, std::max<int64_t>(1, n_patches / nlos::kBlock));
-            }
-            *split = (int)sv;
-            sp->n_blocks = sp->tiles * sv;
-            sp->lds = lds;
-            return NLOS_OK;
-        }
+    sp->taps_bytes = 0;
+    sp->moments = n_patches > 0 ? nlos::smooth_moments(smooth_sigma(p)) : 0;
+    int points = 0;
+    for (const auto& s : {std::pair<int, int>{2, 3}, {2, 2}, {2, 1}, {1, 1}}) {
+        if (sp->moments == 0 || T + 2 * rs > nlos::smooth_mom_pitch(s.second, sp->moments, s.first)) continue;
+        sp->wg = s.first;
+        points = s.second;
+        break;
     }
+    if (points > 0) {
+        sp->taps_bytes = ((size_t)sp->moments * nlos::taps_fwd(rs) * 4 + 255) & ~(size_t)255;
+        sp->tx = points;
+        sp->ty = 1;
+        sp->tiles = (int64_t)((p->relay.nx + sp->tx - 1) / sp->tx) * p->relay.ny;
+        int64_t sv = 1;
+        if (sp->tiles < kTargetBlocks) {
+            sv = (kTargetBlocks + sp->tiles - 1) / sp->tiles;
+            sv = std::min<int64_t>(sv, std::max<int64_t>(1, n_patches / nlos::kBlock));
+        }
+        *split = (int)sv;
+        sp->n_blocks = sp->tiles * sv;
+        sp->lds = 0;
+        return NLOS_OK;
+    }
+    sp->moments = 0;
     int chosen = -1, largest = -1;
     for (int i = 0; i < 5; ++i) {
         if (smooth_lds(shapes[i][0] * shapes[i][1], T) > kLdsMax) continue;
@@ -644,13 +676,14 @@ int adjoint_rows(int T)
 size_t adjoint_lds(int rows, int T) { return (((size_t)rows * T * 4 + 15) & ~(size_t)15) + (size_t)rows * 24; }
 
 // Plan of the adjoint: by moments (correlation rows computed once per scan
-// point, in the workspace ahead of the partials) when the support radius has
-// a compiled variant and its rows fit in LDS, else the tap gather.
+// point, in the workspace ahead of the partials) when the width takes them and
+// one scan point's rows fit in LDS, else the tap gather.
 struct AdjPlan {
-    int moments, rows, split, mlen;
+    int moments;       // correlation rows per scan point, 0: by taps
+    int rows, split, mlen;
     int dbuf;          // moment gather: two row buffers, one filled while the other is read
     int64_t pbk;       // patch blocks of the gather
-    size_t c_bytes;    // kernel taps (256 bytes per 64 floats), then correlation rows [S][adj_moments][mlen] fp32
+    size_t c_bytes;    // kernel taps, then correlation rows [S][mlen][adj_row_words] fp32
     size_t taps_bytes; // the taps' share of c_bytes
     size_t lds;
 };
@@ -664,35 +697,27 @@ int adjoint_plan(const nlos_params* p, int32_t n_patches, int rs, AdjPlan* ap)
     ap->mlen = 0;
     ap->c_bytes = 0;
     ap->taps_bytes = 0;
-    if (nlos::smooth_moments_radius(rs)) {
-        const int L = T + 2 * rs;
-        const int nm = nlos::adj_moments(rs);
-        const int64_t per_row = (int64_t)nm * L * 4;
-        const int64_t rows = std::min<int64_t>(5, ((int64_t)kLdsMax - 1024) / per_row);
-        // correlation pass: gradient row (rounded to 16 bytes), then the taps
-        const size_t lds_pre = (size_t)((T + 4 * rs + 8 + 3) & ~3) * 4 + (size_t)nm * (2 * rs + 1) * 4;
-        if (rows >= 1 && lds_pre <= kLdsMax) {
-            ap->moments = 1;
-            ap->rows = (int)rows;
-            // double-buffered staging when two buffers of at least one scan
-            // point fit and the rows are whole 16-byte pieces
-            ap->dbuf = 0;
-            if ((L & 3) == 0) {
-                int r2 = 5;
-                while (r2 >= 1 && nlos::adj_mom_lds(2, r2, nm, L) > kLdsMax) --r2;
-                if (r2 >= 1) {
-                    ap->dbuf = 1;
-                    ap->rows = r2;
-                }
-            }
+    const int nf = nlos::smooth_moments(smooth_sigma(p));
+    if (nf > 0) {
+        const int L = nlos::adj_row_bins(T, rs), nm = nlos::adj_moments(nf);
+        // double-buffered staging when two buffers of at least one scan point fit
+        for (int buffers = 2; buffers >= 1 && !ap->moments; --buffers) {
+            int rows = 5;
+            while (rows >= 1 && nlos::adj_mom_lds(buffers, rows, nm, L) > kLdsMax) --rows;
+            if (rows < 1) continue;
+            ap->moments = nm;
+            ap->rows = rows;
+            ap->dbuf = buffers == 2;
+        }
+        if (ap->moments) {
             ap->mlen = L;
             const int64_t per_block = (int64_t)nlos::kAdjPatches * nlos::kBlock;
             ap->pbk = ((int64_t)n_patches + per_block - 1) / per_block;
             const int64_t pb = std::max<int64_t>(1, ap->pbk);
             int64_t sv = (2 * kTargetBlocks + pb - 1) / pb;
             ap->split = (int)std::max<int64_t>(1, std::min<int64_t>(sv, std::min<int64_t>(S, 65535)));
-            ap->taps_bytes = ((size_t)nm * (2 * rs + 1) * 4 + 255) & ~(size_t)255;
-            ap->c_bytes = ap->taps_bytes + (((size_t)S * nm * L * 4 + 255) & ~(size_t)255);
+            ap->taps_bytes = ((size_t)nm * nlos::taps_adj(rs) * 4 + 255) & ~(size_t)255;
+            ap->c_bytes = ap->taps_bytes + (((size_t)S * nlos::adj_row_words(nm) * L * 4 + 255) & ~(size_t)255);
             ap->lds = nlos::adj_mom_lds(ap->dbuf ? 2 : 1, ap->rows, nm, L);
             return NLOS_OK;
         }
@@ -1400,7 +1425,7 @@ int nlos_forward_smooth_workspace_bytes(const nlos_params* p, int32_t n_patches,
     int split = 1;
     rc = smooth_plan(p, n_patches, a.Rs, &sp, &split);
     if (rc != NLOS_OK) return rc;
-    *bytes = stats_bytes(n_patches);
+    *bytes = stats_bytes(n_patches) + sp.taps_bytes;
     return NLOS_OK;
 }
 
@@ -1415,7 +1440,7 @@ int nlos_forward_smooth(const nlos_params* p, const float* patches, int32_t n_pa
     int split = 1;
     rc = smooth_plan(p, n_patches, a.Rs, &sp, &split);
     if (rc != NLOS_OK) return rc;
-    const size_t need = stats_bytes(n_patches);
+    const size_t need = stats_bytes(n_patches) + sp.taps_bytes;
     if (ws_bytes < need) return NLOS_ENOSPC;
     if (need > 0 && (!ws || !aligned(ws, 16))) return NLOS_EINVAL;
     const int dev = device_check();
@@ -1429,20 +1454,26 @@ int nlos_forward_smooth(const nlos_params* p, const float* patches, int32_t n_pa
     a.stats = reinterpret_cast<nlos::ChunkStat*>(ws);
     a.n_stats = (int32_t)stats_count(n_patches);
     hipStream_t st = (hipStream_t)stream;
-    // record summaries through the hard forward's kernel (same records)
-    nlos::FwdArgs fa;
-    std::memset(&fa, 0, sizeof(fa));
-    fa.patches = a.patches;
-    fa.n_active = a.n_active;
-    fa.n_cap = a.n_cap;
-    fa.n_stats = a.n_stats;
-    hipError_t e = nlos::launch_stats(fa, a.stats, st);
+    hipError_t e = hipSuccess;
+    if (sp.moments) {
+        a.mtaps = reinterpret_cast<float*>(static_cast<char*>(ws) + stats_bytes(n_patches));
+        e = nlos::launch_smooth_prep(a, moment_fit(smooth_sigma(p), a.Rs, sp.moments), false, st);
+    } else {
+        // record summaries through the hard forward's kernel (same records)
+        nlos::FwdArgs fa;
+        std::memset(&fa, 0, sizeof(fa));
+        fa.patches = a.patches;
+        fa.n_active = a.n_active;
+        fa.n_cap = a.n_cap;
+        fa.n_stats = a.n_stats;
+        e = nlos::launch_stats(fa, a.stats, st);
+    }
     if (e != hipSuccess) return hip_fail(e);
     if (a.atomic_out) {
         e = nlos::launch_fill(out, (size_t)n_hist(p) * (size_t)p->n_bins, st);
         if (e != hipSuccess) return hip_fail(e);
     }
-    e = sp.moments ? nlos::launch_smooth_moments(a, sp.n_blocks, sp.lds, st)
+    e = sp.moments ? nlos::launch_smooth_moments(a, sp.moments, sp.tx, sp.wg, sp.n_blocks, st)
                    : nlos::launch_smooth(a, sp.tx, sp.ty, sp.n_blocks, sp.lds, st);
     return e == hipSuccess ? NLOS_OK : hip_fail(e);
 }
@@ -1486,7 +1517,8 @@ int nlos_adjoint(const nlos_params* p, const float* patches, int32_t n_patches, 
     a.n_split = ap.split;
     a.rows = ap.rows;
     hipStream_t st = (hipStream_t)stream;
-    hipError_t e = ap.moments ? nlos::launch_adjoint_moments(a, ap.pbk, ap.lds, ap.dbuf, st)
+    hipError_t e = ap.moments ? nlos::launch_adjoint_moments(a, moment_fit(smooth_sigma(p), a.Rs, ap.moments), ap.pbk,
+                                                             ap.lds, ap.dbuf != 0, st)
                               : nlos::launch_adjoint(a, ap.pbk, ap.lds, st);
     if (e != hipSuccess) return hip_fail(e);
     e = nlos::launch_adjoint_reduce(a, grad_patches, st);

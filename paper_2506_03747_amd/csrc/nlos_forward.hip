@@ -152,23 +152,6 @@ __device__ __forceinline__ void block_max(float* v, float* red)
     }
 }
 
-// Device buffers named by the arguments are global memory; saying so keeps
-// the accesses global (not flat) when the pointer itself was loaded from a
-// table, so they do not share the LDS wait counter.
-template <typename T>
-__device__ __forceinline__ __attribute__((address_space(1))) T* gmem(T* p)
-{
-    return (__attribute__((address_space(1))) T*)p;
-}
-
-typedef float v4f __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ float4 load4(const float4* p, size_t i)
-{
-    const v4f v = gmem(reinterpret_cast<const v4f*>(p))[i];
-    return make_float4(v.x, v.y, v.z, v.w);
-}
-
 // The first three words of record half i (the pair loop does not read the
 // fourth; a 12-byte load leaves no dead register that an in-flight load
 // would still be writing).
@@ -298,49 +281,9 @@ __device__ __forceinline__ void guard_drain(const Lds& L, const FwdArgs& a, int 
 // Load patch p of [pb, pe) or, past the range, a stand-in patch whose arrival
 // lies at least 64 bins past the window (never binned, never queued, culled).
 
-// ---------------------------------------------------------------------------
-// Record summaries: one workgroup per kStatBlock consecutive records.
-__device__ __forceinline__ void chunk_stats_body(const FwdArgs& a, ChunkStat* st, int blk)
-{
-    __shared__ float red[6][kStatBlock / 64];
-    const int n_act = active_count(a);
-    const int p = blk * kStatBlock + (int)threadIdx.x;
-    float v[6] = {3.0e38f, 3.0e38f, 3.0e38f, 3.0e38f, 3.0e38f, 0.f};   // x0, -x1, y0, -y1, z0, amax
-    if (p < n_act) {
-        const float4 A = load4(a.patches, 2 * (size_t)p);
-        v[0] = A.x;
-        v[1] = -A.x;
-        v[2] = A.y;
-        v[3] = -A.y;
-        v[4] = A.z;
-        v[5] = A.w;
-    }
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-        const float x = k == 5 ? wave_extreme_f<true>(v[k]) : wave_extreme_f<false>(v[k]);
-        if ((threadIdx.x & 63) == 0) red[k][threadIdx.x >> 6] = x;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float r[6] = {3.0e38f, 3.0e38f, 3.0e38f, 3.0e38f, 3.0e38f, 0.f};
-        for (int w = 0; w < kStatBlock / 64; ++w)
-            for (int k = 0; k < 6; ++k) r[k] = (k == 5) ? fmaxf(r[k], red[k][w]) : fminf(r[k], red[k][w]);
-        ChunkStat c;
-        c.x0 = ord_f(r[0]);
-        c.x1 = ord_f(-r[1]);
-        c.y0 = ord_f(r[2]);
-        c.y1 = ord_f(-r[3]);
-        c.z0 = ord_f(r[4]);
-        c.amax = ord_f(r[5]);
-        c.count = max(0, min(kStatBlock, n_act - blk * kStatBlock));
-        c.pad = 0;
-        st[blk] = c;
-    }
-}
-
 __global__ void __launch_bounds__(kStatBlock) k_chunk_stats(const FwdArgs a, ChunkStat* st)
 {
-    chunk_stats_body(a, st, (int)blockIdx.x);
+    chunk_stats_body(a.patches, active_count(a), st, (int)blockIdx.x);
 }
 
 // Wall rectangles of the aligned block of histograms that holds unit u --
@@ -1159,7 +1102,7 @@ __global__ void __launch_bounds__(kStatBlock) k_chunk_stats_batch(const BatchLis
 {
     const int i = batch_slot(b.first, b.n, (int64_t)blockIdx.x);
     const FwdArgs& a = b.tab[b.req[i]];
-    chunk_stats_body(a, a.stats, (int)((int64_t)blockIdx.x - b.first[i]));
+    chunk_stats_body(a.patches, active_count(a), a.stats, (int)((int64_t)blockIdx.x - b.first[i]));
 }
 
 // Zero the outputs of the listed requests (those accumulated with atomics):

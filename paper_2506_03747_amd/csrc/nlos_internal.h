@@ -262,7 +262,6 @@ struct SmoothArgs {
     Axis rx, ry;
     double cx, cy, s;          // device position
     double inv;                // bins per metre
-    float sigma;               // bins
     float norm;                // 1 / (sigma sqrt(2 pi))
     float inv_s2;              // 1 / sigma^2
     float c1;                  // exp(-1 / sigma^2)
@@ -270,15 +269,15 @@ struct SmoothArgs {
     int32_t Rs;                // support radius, bins
     int32_t tiles_x, tiles_y;  // forward: scan tiles
     int32_t n_split;           // forward: patch ranges per tile; adjoint: scan ranges
-    int32_t stride;            // forward: u64 bins per LDS row
+    int32_t stride;            // forward by taps: u64 bins per LDS row
     int32_t rows;              // adjoint: rows staged in LDS at a time
     int32_t atomic_out;
     int32_t cosines;
     ChunkStat* stats;
     int32_t n_stats;
-    float* moments;            // adjoint by moments: [S][adj_moments(Rs)][mlen] correlations
-    float* mtaps;              // adjoint by moments: kernels K_m(d), [adj_moments(Rs)][2 Rs + 1]
-    int32_t mlen;              // T + 2 Rs
+    float* moments;            // adjoint by moments: [S][mlen][adj_row_words(n)] correlations
+    float* mtaps;              // by moments: kernels K_m(d), [n][taps_fwd(Rs)] or [n][taps_adj(Rs)]
+    int32_t mlen;              // adj_row_bins(T, Rs)
 };
 
 // Record gradients -> map gradients (depth-stencil adjoint).
@@ -344,39 +343,61 @@ hipError_t launch_fill(float* out, size_t n, hipStream_t st);
 hipError_t launch_debug(const DebugArgs& a, hipStream_t st);
 
 hipError_t launch_smooth(const SmoothArgs& a, int tx, int ty, int64_t n_blocks, size_t lds, hipStream_t st);
-// Smooth forward by moments of the sub-bin offset (support radii 12, 16, 20):
-// scan points per workgroup and moment rows per point (the series is cut
-// after m = moments - 1: 7 at radius 12, 5 at 16 and 20, where sigma > 2.5
-// bins makes the terms fall faster).
-struct SmoothMomShape {
-    int points, moments;
+// By moments of the sub-bin offset: N(d + s) ~ sum_m s^m K_m(d), |s| <= 1/2, the
+// polynomial of degree n - 1 through the n Chebyshev nodes of [-1/2, 1/2]:
+// K_m(d) = sum_j coef[m][j] N(d + node[j]).
+constexpr int kMaxMoments = 9;
+struct MomentFit {
+    double sigma, norm;        // bins; 1 / (sigma sqrt(2 pi))
+    int32_t n, Rs;
+    double node[kMaxMoments];
+    double coef[kMaxMoments * kMaxMoments];
 };
-constexpr SmoothMomShape smooth_mom_shape(int rs) { return rs == 12 ? SmoothMomShape{2, 8} : SmoothMomShape{3, 6}; }
-// The rows' pitch (u64 bins) used whenever the rows take more than half the
-// LDS (one workgroup per CU either way): the largest even pitch whose rows
-// and 2 KiB of constants fit in 160 KiB, known at compile time so that the
-// rows' offsets go into the LDS instructions' immediate field.
-constexpr int smooth_mom_pitch(int rs)
+// Moments of the forward at width sigma; 0: by taps.  The error of the
+// polynomials (relative L2 over the support, root mean square over the bin)
+// stays below 2.5e-8, a quarter of what fp32 weights leave: 8 terms down to
+// 1.2 bins (1.2e-8), 7 from 1.6 (2.0e-8), 6 from 2.5 (2.4e-8), 5 from 4.9
+// (2.3e-8).  Below 1.2 bins the support has at most 15 taps and the direct
+// sum costs as much.  The adjoint takes one more (adj_moments), as it uses the
+// polynomial's derivative too.
+inline int smooth_moments(double sigma)
 {
-    return ((163840 - 2048) / (smooth_mom_shape(rs).points * smooth_mom_shape(rs).moments * 8)) & ~1;
+    return sigma < 1.2 ? 0 : sigma < 1.6 ? 8 : sigma < 2.5 ? 7 : sigma < 4.9 ? 6 : 5;
 }
-bool smooth_moments_radius(int rs);
-hipError_t launch_smooth_moments(const SmoothArgs& a, int64_t n_blocks, size_t lds, hipStream_t st);
-// Adjoint by moments (the same radii): adj_moments correlation rows per scan
-// point, kAdjPatches patches per thread in the gather.
-// Correlation rows per scan point: C_0 .. C_{n-1} give G0 to the power
-// n - 2 of the sub-bin offset and G1 to the same power; 9 at radius 12, 7 at
-// 16 and 20 (sigma > 2.5 bins).
-constexpr int adj_moments(int rs) { return rs == 12 ? 9 : 7; }
+constexpr int adj_moments(int n) { return n + 1; }
+// Words per kernel in the table (k_smooth_prep).
+__host__ __device__ constexpr int taps_fwd(int rs) { return (2 * rs + 1 + 3) & ~3; }
+__host__ __device__ constexpr int taps_adj(int rs) { return 4 + ((rs + 3) & ~3); }
+// The forward's LDS, for `wg` workgroups per CU: points x moments rows at the
+// largest even pitch (u64 bins) that fits, known at compile time so that the
+// rows' offsets go into the LDS instructions' immediate field; then the
+// points' constants and the reduction.
+constexpr int smooth_mom_pitch(int points, int moments, int wg)
+{
+    return (int)((size_t)(163840 / wg - 512) / ((size_t)points * moments * 8)) & ~1;
+}
+constexpr size_t smooth_mom_lds(int points, int moments, int wg)
+{
+    return (size_t)points * moments * smooth_mom_pitch(points, moments, wg) * 8 + 512;
+}
+hipError_t launch_smooth_prep(const SmoothArgs& a, const MomentFit& f, bool adjoint, hipStream_t st);
+hipError_t launch_smooth_moments(const SmoothArgs& a, int moments, int points, int wg, int64_t n_blocks, hipStream_t st);
+// Adjoint by moments: a bin's correlations side by side, an odd number of
+// words apart; rows of adj_row_bins bins, whole 16-byte pieces.  kAdjPatches
+// patches per thread in the gather.
 constexpr int kAdjPatches = 4;
+__host__ __device__ constexpr int adj_row_words(int n) { return n | 1; }
+__host__ __device__ constexpr int adj_halo(int rs) { return (rs + 3) & ~3; }
+__host__ __device__ constexpr int adj_row_bins(int t, int rs) { return ((t + 3) & ~3) + 2 * adj_halo(rs); }
 // LDS of the moment gather: `buffers` copies (2: the next scan points' rows
 // land while the current ones are used) of `rows` scan points' correlation
-// rows, rounded to 16 bytes, and 24 bytes of constants per point.
-inline size_t adj_mom_lds(int buffers, int rows, int nm, int L)
+// rows and 24 bytes of constants per point.
+inline size_t adj_mom_lds(int buffers, int rows, int n, int bins)
 {
-    return (size_t)buffers * ((((size_t)rows * nm * L * 4 + 15) & ~(size_t)15) + (size_t)rows * 24);
+    return (size_t)buffers * rows * ((size_t)adj_row_words(n) * bins * 4 + 24);
 }
-hipError_t launch_adjoint_moments(const SmoothArgs& a, int64_t patch_blocks, size_t lds, int dbuf, hipStream_t st);
+hipError_t launch_adjoint_moments(const SmoothArgs& a, const MomentFit& f, int64_t patch_blocks, size_t lds, bool dbuf,
+                                  hipStream_t st);
 hipError_t launch_adjoint(const SmoothArgs& a, int64_t patch_blocks, size_t lds, hipStream_t st);
 hipError_t launch_adjoint_reduce(const SmoothArgs& a, float* grad_rec, hipStream_t st);
 hipError_t launch_grad_maps(const GradMapArgs& g, hipStream_t st);

@@ -10,19 +10,19 @@
 // extensions).  Arrivals are computed in fp64: an fp32 distance puts u off by
 // ~1e-4 bins at u ~ 1000, which would move the Gaussian samples by ~1e-5.
 //
-// k_smooth_mom   forward for support radii 12, 16, 20: eight (radius 12) or
-//                six moments of the sub-bin offset per pair into LDS rows,
-//                then a convolution of each moment row with the matching
-//                Gaussian-derivative kernel, four bins per thread from
-//                registers.
-// k_smooth       forward otherwise: a workgroup owns a tile of scan points
+// k_smooth_prep  record summaries and the polynomials' kernels.
+// k_smooth_mom   forward for sigma >= 1.2 bins: 5 to 8 moments of the sub-bin
+//                offset per pair into LDS rows, then a convolution of each
+//                moment row with its kernel, four bins per thread.
+// k_smooth       forward otherwise, or where the moment rows of one scan point
+//                do not fit in LDS: a workgroup owns a tile of scan points
 //                (LDS rows of 64-bit fixed-point bins), a lane one patch;
 //                2 Rs + 1 LDS adds per pair, Gaussian samples by a
 //                three-exponential recurrence.
-// k_adj_moments, k_adjoint_mom   adjoint for support radii 12, 16, 20: the
-//                upstream gradient's correlations with the Gaussian's
-//                derivatives once per scan point, then per pair two series in
-//                the sub-bin offset.
+// k_adj_moments, k_adjoint_mom   adjoint for the same widths: the upstream
+//                gradient's correlations with the polynomials' kernels once
+//                per scan point, then per pair a polynomial in the sub-bin
+//                offset and its derivative.
 // k_adjoint      gather otherwise: a lane owns one patch and loops over a range of scan
 //                points whose upstream-gradient rows are staged in LDS; per
 //                pair G0 = sum g N(x), G1 = sum g (x / sigma^2) N(x) give
@@ -269,65 +269,135 @@ __global__ void __launch_bounds__(kBlock) k_smooth(const SmoothArgs a)
 }
 
 // ---------------------------------------------------------------------------
-// Smooth forward by moments.  With t = f - 1/2 the pair's sub-bin offset
-// about the centre of its bin k0 = floor(u), its contribution w N(d + 1/2 - f)
-// to bin k0 + d is the Taylor series sum_m (-t)^m / m! w N^(m)(d).  A pair
-// therefore adds w (-t)^m to moment row m at bin k0 (one LDS add per moment
-// instead of 2 Rs + 1), and the flush convolves each moment row with
-// K_m(d) = N^(m)(d) / m! over |d| <= Rs, the same support as the direct sum.
-// N^(m)(d) = N(d) (-1/sigma)^m He_m(d / sigma) (He: probabilists' Hermite
-// polynomials).  With |t| <= 1/2, the series cut after m = 7 (radius 12,
-// sigma > 11/6 bins) is within 7e-8 of the direct sum (relative L2 over the
-// support, every t), and cut after m = 5 (radii 16 and 20, sigma > 2.5 bins)
-// within 1.2e-6.  Moments are signed 64-bit fixed point (two's complement
-// sums), increments |w (-t)^m| s <= 2^30.
+// Moments of the sub-bin offset.  With t = f - 1/2 the pair's offset from the
+// centre of its bin k0 = floor(u), its contribution w N(d + 1/2 - f) =
+// w N(d - t) to bin k0 + d is, for every d, a polynomial in -t up to an error
+// that MomentFit bounds:
+//     N(d - t) = sum_{m < n} (-t)^m K_m(d),
+// the polynomial through the n Chebyshev nodes of [-1/2, 1/2].  A pair
+// therefore adds w (-t)^m to moment row m at bin k0 (n LDS adds instead of
+// 2 Rs + 1), and the flush convolves moment row m with K_m.  Interpolation
+// spreads the error evenly over the bin where a Taylor series about its
+// centre piles it up at the edges: at sigma = 2.65 bins and n = 6, 2.5e-8
+// (relative L2 over the support, worst t) against 8e-7.
+// K_m(-d) = (-1)^m K_m(d), as the nodes are symmetric.
 
-// Taps K_m(d) = N^(m)(d) / m! = N(d) (-1/sigma)^m He_m(d / sigma) / m!,
-// m < n_moments, |d| <= RS, into kt[m pitch + d + RS] (fp64, then fp32).
-template <int RS>
-__device__ __forceinline__ void moment_taps(const SmoothArgs& a, float* kt, int n_moments, int pitch)
+// K_m(d), |d| <= Rs, fp32 of the fp64 value.
+__device__ __forceinline__ float moment_tap(const MomentFit& f, int m, int d)
 {
-    constexpr int ND = 2 * RS + 1;
-    for (int i = threadIdx.x; i < n_moments * ND; i += blockDim.x) {
-        const int m = i / ND, d = i % ND - RS;
-        const double sig = (double)a.sigma, x = d / sig;
-        double h0 = 1.0, h1 = x;   // He_0, He_1
-        for (int n = 1; n < m; ++n) {
-            const double h2 = x * h1 - n * h0;
-            h0 = h1;
-            h1 = h2;
-        }
-        const double he = m == 0 ? 1.0 : h1;
-        double f = 1.0;
-        for (int n = 2; n <= m; ++n) f *= n;
-        kt[m * pitch + d + RS] = (float)((double)a.norm * exp(-0.5 * x * x) * he * pow(-1.0 / sig, m) / f);
+    const int ad = d < 0 ? -d : d;
+    if (ad > f.Rs || ((m & 1) && d == 0)) return 0.f;
+    double k = 0.0;
+    for (int j = 0; j < f.n; ++j) {
+        const double x = ((double)ad + f.node[j]) / f.sigma;
+        k += f.coef[m * kMaxMoments + j] * exp(-0.5 * x * x);
+    }
+    k *= f.norm;
+    return (float)((d < 0 && (m & 1)) ? -k : k);
+}
+
+// The first n_stats workgroups make the record summaries of the forward (none
+// for the adjoint); the others the kernels' table, the same for every
+// workgroup of the launches behind (scalar reads there):
+//   forward  [m][taps_fwd(Rs)]   word e = K_m(Rs - e), zeros past 2 Rs
+//   adjoint  [m][taps_adj(Rs)]   word 0 = K_m(0), word 3 + d = K_m(d), zeros
+//                                elsewhere
+__global__ void __launch_bounds__(kStatBlock)
+    k_smooth_prep(const SmoothArgs a, const MomentFit f, int adjoint)
+{
+    if ((int)blockIdx.x < a.n_stats) {
+        chunk_stats_body(a.patches, smooth_active(a), a.stats, (int)blockIdx.x);
+        return;
+    }
+    const int pitch = adjoint ? taps_adj(f.Rs) : taps_fwd(f.Rs);
+    const int nb = (int)gridDim.x - a.n_stats;
+    for (int i = ((int)blockIdx.x - a.n_stats) * kStatBlock + (int)threadIdx.x; i < f.n * pitch; i += nb * kStatBlock) {
+        const int m = i / pitch, e = i % pitch;
+        a.mtaps[i] = adjoint ? (e == 0 || e > 3 ? moment_tap(f, m, e == 0 ? 0 : e - 3) : 0.f)
+                             : moment_tap(f, m, f.Rs - e);   // (0 past the support)
     }
 }
 
-template <bool COS, int RS, bool PITCH>
-__global__ void __launch_bounds__(kBlock) k_smooth_mom(const SmoothArgs a)
+typedef const __attribute__((address_space(4))) float* kconst;
+
+// Distance terms of one pair from its squared distance in fp64 (r2d) and fp32
+// (r2f): the bin k0 = floor(u), mt = 1/2 - (u - k0) and the reciprocals the
+// weight takes.  u = 2 r inv + o inv with 2 r = 2 rf + (r^2 - rf^2) / rf, rf an
+// fp32 root: one Newton step, its residual exact in fp64 (relative error
+// ~1e-14; an fp32 arrival would put u off by ~1e-4 bins at u ~ 1000).  The
+// step, below 1e-4 bins, goes to mt alone: where it would carry u over a bin
+// edge, mt leaves [-1/2, 1/2] by that much, which the polynomials take as is.
+struct Arrival {
+    int k0;
+    float mt;
+    float ri2;    // 1 / r^2
+    float rinv;   // 1 / r
+};
+
+__device__ __forceinline__ Arrival arrival(double r2d, float r2f, double inv2, double oi, float invf)
 {
-    constexpr int NP = smooth_mom_shape(RS).points, NM = smooth_mom_shape(RS).moments, NR = NP * NM, ND = 2 * RS + 1;
-    constexpr int NDP = (ND + 3) & ~3;             // tap row pitch: rows start 16-byte aligned
+    Arrival q;
+    const float rf = __builtin_amdgcn_sqrtf(r2f);
+    q.ri2 = __builtin_amdgcn_rcpf(r2f);   // (weights: 1 ulp is ample)
+    q.rinv = rf * q.ri2;
+    const double rfd = (double)rf;
+    const double base = fma(rfd, inv2, oi);
+    const float step = (float)fma(-rfd, rfd, r2d) * (q.rinv * invf);
+    q.k0 = (int)base;   // base >= 0; a saturated conversion fails the range test
+    q.mt = (0.5f - (float)__builtin_amdgcn_fract(base)) - step;
+    return q;
+}
+
+// Nearest integer of a float within the int32 range (one instruction).
+__device__ __forceinline__ int round_i(float v)
+{
+    int r;
+    asm("v_cvt_rpi_i32_f32 %0, %1" : "=v"(r) : "v"(v));
+    return r;
+}
+
+// Squared distance past which every arrival of a scan point with offset o lies
+// at least two bins past bin T - 1 + Rs, the last one that reaches the window
+// (enlarged by 1e-5: the fp32 squares round).
+__device__ __forceinline__ float cull_r2(const SmoothArgs& a, double o)
+{
+    const double r = 0.5 * ((double)(a.T + a.Rs + 2) / a.inv - o);
+    return r > 0.0 ? (float)(r * r * 1.00001) : 0.f;
+}
+
+// Smooth forward by moments.  A workgroup owns NP scan points of one wall row
+// (x0 .. x0 + NP - 1, y), NM moment rows each, and streams all records (or its
+// share of them), a patch per lane.  Terms of y are per patch, shared by the
+// NP points.  A wavefront whose patches all arrive past the window (a record
+// wavefront is a small square of the surface) goes on at once; the record
+// order deals a 16 x 16-pixel block's four wavefronts to the four SIMDs, so
+// what is skipped thins all of them alike.
+// Bound: the LDS adds -- a 64-lane ds_add_u64 takes 7.5 cycles on consecutive
+// bins, 10.9 on random ones and 8.6 more per lane that shares a bin; here 13
+// on average, NM of them per pair -- with VALU (about 50 instructions per pair
+// that reaches the window) close behind.  128^2 points and patches, 1024 bins:
+// radius 16 (NM = 6) 0.80 -> 0.66 ms, radius 12 (8 -> 7 terms) 1.32 -> 0.97;
+// 48 x 40 points, 3840 patches, 1501 bins, radius 31: 185 us by taps, 87 by
+// moments.
+template <bool COS, int NM, int NP, int WG>
+__global__ void __launch_bounds__(kBlock, 4 * WG) k_smooth_mom(const SmoothArgs a)
+{
+    constexpr int NR = NP * NM, PITCH = smooth_mom_pitch(NP, NM, WG);
     extern __shared__ __align__(16) unsigned char smem[];
-    u64s* hist = reinterpret_cast<u64s*>(smem);   // row (point c, moment m) = c NM + m; bin k0 at k0 + RS
-    // (PITCH: the rows at the compile-time pitch, which the host passes as the stride)
-    const int stride = PITCH ? smooth_mom_pitch(RS) : a.stride;
-    double* so = reinterpret_cast<double*>(smem + (size_t)NR * stride * 8);
+    u64s* hist = reinterpret_cast<u64s*>(smem);   // row (point c, moment m) = c NM + m; bin k0 at k0 + Rs
+    double* so = reinterpret_cast<double*>(smem + (size_t)NR * PITCH * 8);
     float* sg = reinterpret_cast<float*>(so + NP);
     float* red = sg + NP;
-    constexpr int KT_OFF = (NP * 12 + 64 * 4 + 15) & ~15;   // past so, sg and red
-    static_assert(KT_OFF + NM * NDP * 4 <= 2048, "the taps must fit the 2 KiB past the moment rows");
-    float* kt = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(so) + KT_OFF);   // [NM][NDP], 16-byte aligned
     const int n_act = smooth_active(a);
     const int split = (int)(blockIdx.x % a.n_split);
     const int tile = (int)(blockIdx.x / a.n_split);
     const int tx0 = (tile / a.tiles_y) * NP, ty0 = tile % a.tiles_y;
     const int chunk = (n_act + a.n_split - 1) / a.n_split;
     const int pb = min(n_act, split * chunk), pe = min(n_act, pb + chunk);
-    const int T = a.T;
+    const int T = a.T, Rs = a.Rs;
 
-    for (int i = threadIdx.x; i < NR * stride; i += kBlock) hist[i] = 0ull;
+    static_assert(PITCH % 2 == 0, "rows are cleared 16 bytes at a time");
+    for (int i = threadIdx.x; i < NR * PITCH / 2; i += kBlock) reinterpret_cast<uint4*>(hist)[i] = uint4{0, 0, 0, 0};
     if (threadIdx.x < NP) {
         const int c = threadIdx.x;
         double off, g;
@@ -335,23 +405,20 @@ __global__ void __launch_bounds__(kBlock) k_smooth_mom(const SmoothArgs a)
         so[c] = off + off;
         sg[c] = (float)(g * g);
     }
-    moment_taps<RS>(a, kt, NM, NDP);
     float wx[NP];
 #pragma unroll
-    for (int c = 0; c < NP; ++c) wx[c] = canon(a.rx, min(tx0 + c, a.rx.n - 1));
-    const float wy = canon(a.ry, ty0);
+    for (int c = 0; c < NP; ++c) wx[c] = uniform_f(canon(a.rx, min(tx0 + c, a.rx.n - 1)));
+    const float wy = uniform_f(canon(a.ry, ty0));
+    const float x0 = fminf(wx[0], wx[NP - 1]), x1 = fmaxf(wx[0], wx[NP - 1]);
     // weight bound over the record summaries: a_max / r_min^4 -> scale
     float wb = 0.f;
-    {
-        const float x0 = fminf(wx[0], wx[NP - 1]), x1 = fmaxf(wx[0], wx[NP - 1]);
-        for (int i = threadIdx.x; i < a.n_stats; i += kBlock) {
-            const StatF c = load_stat(a.stats, i);
-            if (c.count <= 0) continue;
-            const float ddx = fmaxf(fmaxf(x0 - c.x1, c.x0 - x1), 0.f);
-            const float ddy = fmaxf(fmaxf(wy - c.y1, c.y0 - wy), 0.f);
-            const float r2 = fmaf(ddx, ddx, fmaf(ddy, ddy, c.z0 * c.z0));
-            wb = fmaxf(wb, c.amax / (r2 * r2));
-        }
+    for (int i = threadIdx.x; i < a.n_stats; i += kBlock) {
+        const StatF c = load_stat(a.stats, i);
+        if (c.count <= 0) continue;
+        const float ddx = fmaxf(fmaxf(x0 - c.x1, c.x0 - x1), 0.f);
+        const float ddy = fmaxf(fmaxf(wy - c.y1, c.y0 - wy), 0.f);
+        const float r2 = fmaf(ddx, ddx, fmaf(ddy, ddy, c.z0 * c.z0));
+        wb = fmaxf(wb, c.amax / (r2 * r2));
     }
     wb = wave_max_f(wb);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = wb;
@@ -359,76 +426,89 @@ __global__ void __launch_bounds__(kBlock) k_smooth_mom(const SmoothArgs a)
     float W = 0.f;
     for (int w = 0; w < kBlock / 64; ++w) W = fmaxf(W, red[w]);
     const float s = W > 0.f ? 1073741824.0f / W : 1.0f;   // |increments| <= 2^30
-    double soc[NP];
-    float sgc[NP];
+    double oi[NP];
+    float gs[NP];
+    float cut = 0.f;
 #pragma unroll
     for (int c = 0; c < NP; ++c) {
-        soc[c] = so[c];
-        sgc[c] = sg[c];
+        const double o = uniform_d(so[c]);
+        oi[c] = uniform_d(o * a.inv);
+        gs[c] = uniform_f(sg[c] * s);
+        cut = fmaxf(cut, cull_r2(a, o));
     }
+    cut = uniform_f(cut);
+    const double inv2 = 2.0 * a.inv, wyd = (double)wy;
+    const float invf = (float)a.inv;
 
     for (int base = pb; base < pe; base += kBlock) {
         const int p = base + (int)threadIdx.x;
         if (p >= pe) continue;
         const float4 A = a.patches[2 * (size_t)p];
         const float4 B = a.patches[2 * (size_t)p + 1];
+        const float dy = A.y - wy;
+        const float dxm = fmaxf(fmaxf(x0 - A.x, A.x - x1), 0.f);
+        if (__all(fmaf(dxm, dxm, fmaf(dy, dy, A.z * A.z)) >= cut)) continue;
+        const double px = (double)A.x, ey = (double)A.y - wyd, ez = (double)A.z;
+        const double yz2 = fma(ey, ey, ez * ez);
+        // w = a g pz^2 c^2 / r^8, c = -n.(p - w) clamped at 0 (a g / r^4 without cosines)
+        const float cyz = fmaf(-B.y, dy, -B.z * A.z);
+        const float aw = COS ? A.w * (A.z * A.z) : A.w;
 #pragma unroll
         for (int c = 0; c < NP; ++c) {
-            if (tx0 + c >= a.rx.n) continue;
-            const PairS q = pair_smooth(A, B, wx[c], wy, soc[c], sgc[c], a.inv, COS, false);
-            const double k0d = floor(q.u);
-            const int k0 = (int)k0d;   // u >= 0; a saturated conversion fails the test below
-            // the support [k0 - RS, k0 + RS] meets the bins [0, T)
-            if (q.w <= 0.f || (uint32_t)k0 + (uint32_t)RS > (uint32_t)(T - 1 + 2 * RS)) continue;
-            const float mt = 0.5f - (float)(q.u - k0d);   // -t
-            float v = q.w * s;
-            u64s* r0 = hist + (size_t)(c * NM) * stride + (k0 + RS);
+            const double ex = px - (double)wx[c];
+            const double r2d = fma(ex, ex, yz2);
+            const Arrival q = arrival(r2d, (float)r2d, inv2, oi[c], invf);
+            const float ri4 = q.ri2 * q.ri2;
+            const float cn = COS ? fmaxf(fmaf(-B.x, A.x - wx[c], cyz), 0.f) : 1.f;
+            const float h = COS ? cn * ri4 : 1.f;
+            float v = (aw * gs[c]) * (COS ? h * h : ri4);
+            // the support [k0 - Rs, k0 + Rs] meets the bins [0, T)
+            if (v <= 0.f || (uint32_t)q.k0 + (uint32_t)Rs > (uint32_t)(T - 1 + 2 * Rs)) continue;
+            u64s* r0 = hist + (c * NM) * PITCH + (q.k0 + Rs);
 #pragma unroll
             for (int m = 0; m < NM; ++m) {
                 // even moments are non-negative (w > 0, (-t)^m >= 0): no sign extension
-                const int iv = __float2int_rn(v);
+                const int iv = round_i(v);
                 const u64s inc = (m & 1) ? (u64s)(long long)iv : (u64s)(uint32_t)iv;
-                __hip_atomic_fetch_add(r0 + (size_t)m * stride, inc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                v *= mt;
+                __hip_atomic_fetch_add(r0 + m * PITCH, inc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                v *= q.mt;
             }
         }
     }
     __syncthreads();
-    // moment rows -> float, in place (row r keeps its byte offset; values
-    // pass through registers so that no thread overwrites what another reads)
-    const int L = T + 2 * RS;
-    constexpr int kMaxPer = 24;
-    float vals[kMaxPer];
-    const int n_vals = NR * L;
+    // moment rows -> float, in place (row r starts at the same byte; values
+    // pass through registers so that no thread overwrites what another
+    // reads), and zeros behind each row: the last windows reach past it
+    constexpr int kPer = (NR * PITCH + kBlock - 1) / kBlock;
+    float vals[kPer];
 #pragma unroll
-    for (int k = 0; k < kMaxPer; ++k) {
-        const int i = (int)threadIdx.x + k * kBlock;
-        vals[k] = 0.f;
-        if (i < n_vals) {
-            const int r = i / L, b = i - r * L;
-            const u64s x = hist[(size_t)r * stride + b];
-            vals[k] = fmaf((float)(int32_t)(uint32_t)(x >> 32), 4294967296.0f, (float)(uint32_t)x);
-        }
+    for (int k = 0; k < kPer; ++k) {
+        const int i = min((int)threadIdx.x + k * kBlock, NR * PITCH - 1);
+        // (the low word as a signed one: of a small negative sum it is near
+        // 2^32 and would round there)
+        const int2 x = reinterpret_cast<const int2*>(hist)[i];
+        vals[k] = fmaf((float)(x.y - (x.x >> 31)), 4294967296.0f, (float)x.x);
     }
     __syncthreads();
-    float* F = reinterpret_cast<float*>(smem);     // row r at float offset 2 r stride
+    float* F = reinterpret_cast<float*>(smem);     // row r at float offset 2 r PITCH
 #pragma unroll
-    for (int k = 0; k < kMaxPer; ++k) {
+    for (int k = 0; k < kPer; ++k) {
         const int i = (int)threadIdx.x + k * kBlock;
-        if (i < n_vals) {
-            const int r = i / L, b = i - r * L;
-            F[(size_t)r * 2 * stride + b] = vals[k];
-        }
+        if (i < NR * PITCH) F[i + (i / PITCH) * PITCH] = vals[k];
     }
+    static_assert(PITCH >= 8, "room for the zeros");
+    for (int i = threadIdx.x; i < NR * 8; i += kBlock) F[(i / 8) * 2 * PITCH + PITCH + i % 8] = 0.f;
     __syncthreads();
-    // Each thread takes V consecutive bins of one scan point and holds, per
-    // moment, their window of V + 2 RS samples and the moment's taps in
-    // registers (16-byte LDS reads; row starts and k0 are multiples of four
-    // floats).  A bin's sum runs over m, then d.  Window samples past the
-    // row's T + 2 RS values reach only bins >= T, which are not written.
+    // Each thread takes V = 4 consecutive bins of one scan point.  Bin k0 + v
+    // is sum_m sum_e F_m[k0 + v + e] K_m(Rs - e): per moment a sliding window
+    // of two 16-byte LDS reads (one new per four taps; rows start and k0 are
+    // multiples of four floats), taps as scalars.  The sums run over m downwards,
+    // then e; the largest row's, last, four taps at a time, so that few additions
+    // round at the size of the result.
     const float inv_sc = 1.0f / s;
-    constexpr int V = 4, NW = (V + 2 * RS + 3) / 4;
-    const int nseg = (T + V - 1) / V;
+    constexpr int V = 4;
+    const int nseg = (T + V - 1) / V, npp = taps_fwd(Rs);
+    kconst kt = (kconst)a.mtaps;
     const bool vec_out = !a.atomic_out && (T & 3) == 0 && ((uintptr_t)a.out & 15) == 0;
     for (int o = threadIdx.x; o < NP * nseg; o += kBlock) {
         const int c = o / nseg, k0 = (o - c * nseg) * V;
@@ -437,31 +517,31 @@ __global__ void __launch_bounds__(kBlock) k_smooth_mom(const SmoothArgs a)
 #pragma unroll
         for (int v = 0; v < V; ++v) acc[v] = 0.f;
 #pragma unroll
-        for (int m = 0; m < NM; ++m) {
-            // bin k0 + v, offset d = dd - RS, reads F at k0 + v + 2 RS - dd
-            const float4* f4 = reinterpret_cast<const float4*>(F + (size_t)(c * NM + m) * 2 * stride + k0);
-            const float4* t4 = reinterpret_cast<const float4*>(kt + m * NDP);
-            float w[4 * NW], t[NDP];
+        for (int m = NM - 1; m >= 0; --m) {
+            const float4* f4 = reinterpret_cast<const float4*>(F + (size_t)(c * NM + m) * 2 * PITCH + k0);
+            kconst tm = kt + m * npp;
+            float4 lo = f4[0];
+#pragma unroll 4
+            for (int e = 0; e < npp; e += 4) {
+                const float4 hi = f4[e / 4 + 1];
+                const float w[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+                float part[V];
 #pragma unroll
-            for (int q = 0; q < NW; ++q) {
-                const float4 x = f4[q];
-                w[4 * q] = x.x;
-                w[4 * q + 1] = x.y;
-                w[4 * q + 2] = x.z;
-                w[4 * q + 3] = x.w;
-            }
+                for (int i = 0; i < 4; ++i) {
+                    const float t = tm[e + i];
 #pragma unroll
-            for (int q = 0; q < NDP / 4; ++q) {
-                const float4 x = t4[q];
-                t[4 * q] = x.x;
-                t[4 * q + 1] = x.y;
-                t[4 * q + 2] = x.z;
-                t[4 * q + 3] = x.w;
-            }
+                    for (int v = 0; v < V; ++v) {
+                        if (m > 0)
+                            acc[v] = fmaf(w[v + i], t, acc[v]);
+                        else
+                            part[v] = i == 0 ? w[v] * t : fmaf(w[v + i], t, part[v]);
+                    }
+                }
+                if (m == 0) {
 #pragma unroll
-            for (int dd = 0; dd < ND; ++dd) {
-#pragma unroll
-                for (int v = 0; v < V; ++v) acc[v] = fmaf(w[v + 2 * RS - dd], t[dd], acc[v]);
+                    for (int v = 0; v < V; ++v) acc[v] += part[v];
+                }
+                lo = hi;
             }
         }
         float* dst = a.out + ((size_t)(tx0 + c) * a.ry.n + ty0) * (size_t)T + k0;
@@ -619,133 +699,156 @@ __global__ void __launch_bounds__(kBlock) k_adjoint(const SmoothArgs a)
 }
 
 // ---------------------------------------------------------------------------
-// Adjoint by moments.  For a pair with bin k0 and t = f - 1/2 (as in
-// k_smooth_mom), G0 = sum_k g[k] N(x) and G1 = sum_k g[k] (x / sigma^2) N(x)
-// = -sum_k g[k] N'(x) over the support are the series
-//     G0 = sum_m (-t)^m C_m[k0],   G1 = -sum_m (-t)^m (m + 1) C_{m+1}[k0]
-// (m = 0 .. n - 2, n = adj_moments(Rs)) of the correlations
-// C_m[k0] = sum_{|d|<=Rs} g[k0 + d] K_m(d), K_m = N^(m) / m!.  k_adj_moments
-// computes C_0 .. C_{n-1} once per scan point (bins k0 = -Rs .. T + Rs - 1,
-// stored at k0 + Rs); k_adjoint_mom then needs n LDS reads and two Horner
-// sums per pair instead of 2 Rs + 1 taps.
-template <int RS>
-__global__ void __launch_bounds__(256) k_adj_taps(const SmoothArgs a)
-{
-    moment_taps<RS>(a, a.mtaps, adj_moments(RS), 2 * RS + 1);
-}
+// Adjoint by moments.  For a pair with bin k0 and offset t (as in
+// k_smooth_mom), G0 = sum_k g[k] N(x) over the support is the polynomial
+//     P(-t) = sum_{m < n} (-t)^m C_m[k0],
+// and G1 = sum_k g[k] (x / sigma^2) N(x) = -sum_k g[k] N'(x) is -P'(-t), of
+// the correlations C_m[k0] = sum_{|d|<=Rs} g[k0 + d] K_m(d).  k_adj_moments
+// computes C_0 .. C_{n-1} once per scan point (bins k0 = -H .. T4 + H - 1, H
+// and T4 the radius and T rounded up to 4; a bin's n values side by side, NS
+// apart with NS odd so that neighbouring bins start on different banks);
+// k_adjoint_mom then needs n LDS reads and one Horner pass for P and P'.
 
-// Correlation rows.  A thread produces V = 4 consecutive bins j0 .. j0 + 3
-// (bins k0 = j - RS of a row of L = T + 2 RS) of every row of one scan point,
-// from a register window of that point's upstream gradient g[j0 - 2 RS ..
-// j0 + 3] (zero outside 0 .. T - 1).  Threads map flat onto (scan
-// point, group of 4 bins), so every lane of every wavefront has work and no
-// row is staged anywhere first.  The kernels have the parity of their order,
-// K_m(-d) = (-1)^m K_m(d) exactly (He_m has the parity of m, and every
-// operation of moment_taps is symmetric in the sign of d), so
-//     C_m[k0] = K_m(0) g[k0] + sum_{d=1..RS} K_m(d) (g[k0 + d] + (-1)^m g[k0 - d]):
+// A thread produces V = 4 consecutive bins k0 .. k0 + 3 of one scan point from
+// sliding windows of its upstream gradient on either side (zero outside
+// 0 .. T - 1; one new 16-byte read per side and four taps).  The kernels have
+// the parity of their order, so
+//     C_m[k0] = K_m(0) g[k0] + sum_{d=1..Rs} K_m(d) (g[k0 + d] + (-1)^m g[k0 - d]):
 // a bin's mirrored sums serve every even row and its mirrored differences
-// every odd row, 2 RS adds and about RS + 1 fmas per row where the full
-// support takes 2 RS + 1 fmas.  The kernels are scalar reads (the same for
-// every lane, written by an earlier launch), fma operands in scalar
-// registers, one row at a time.  ALIGNED (T a multiple of 4, so L is too,
-// and both arrays 16-byte aligned): the window arrives as 16-byte reads, each
-// wholly inside the row or wholly in the zero padding, and each row's four
-// bins go out as one 16-byte store.
-template <int RS, bool ALIGNED>
+// every odd row.  The kernels are scalar reads (written by an earlier launch).
+// The 4 NS values of a thread go through LDS (its own wavefront's piece), so
+// that the stores are contiguous over the wavefront.  ALIGNED: T a multiple of
+// 4 and the gradient 16-byte aligned; else single reads.
+// Bound: HBM, NS words written per bin and point (128^2 points, 1056 bins of 7
+// words: 484 MB in 107 us).
+template <int NM, bool ALIGNED>
 __global__ void __launch_bounds__(256) k_adj_moments(const SmoothArgs a)
 {
-    constexpr int V = 4, NM = adj_moments(RS), ND = 2 * RS + 1, W = V + 2 * RS;
-    static_assert(W % 4 == 0, "the window is whole 16-byte pieces");
-    const int T = a.T, L = a.mlen, Q = (L + V - 1) / V;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)(a.rx.n * a.ry.n) * Q) return;
-    const int s = (int)(t / Q), j0 = (int)(t % Q) * V;
-    const float* g = a.grad_out + (size_t)s * T;
-    const int kw = j0 - 2 * RS;   // gradient index of window word 0
-    float w[W];
-    if constexpr (ALIGNED) {
+    constexpr int V = 4, NS = adj_row_words(NM);
+    __shared__ __align__(16) float tr[4][64 * V * NS];
+    const int T = a.T, L = a.mlen, Q = L / V, H = adj_halo(a.Rs);
+    const int64_t n_thr = (int64_t)(a.rx.n * a.ry.n) * Q;
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
+    if (t < n_thr) {
+        const int s = (int)(t / Q), k0 = (int)(t % Q) * V - H;
+        const float* g = a.grad_out + (size_t)s * T;
+        const auto read4 = [&](int k) {
+            if constexpr (ALIGNED)   // wholly inside the row or wholly in the padding
+                return (k >= 0 && k < T) ? *reinterpret_cast<const float4*>(g + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+            const auto one = [&](int i) { return (i >= 0 && i < T) ? g[i] : 0.f; };
+            return make_float4(one(k), one(k + 1), one(k + 2), one(k + 3));
+        };
+        kconst kc = (kconst)a.mtaps;
+        const int np = taps_adj(a.Rs);
+        float4 mid = read4(k0);
+        float acc[V][NM];
 #pragma unroll
-        for (int q = 0; q < W / 4; ++q) {
-            const int k = kw + 4 * q;
-            const float4 v = (k >= 0 && k < T) ? *reinterpret_cast<const float4*>(g + k) : make_float4(0.f, 0.f, 0.f, 0.f);
-            w[4 * q] = v.x;
-            w[4 * q + 1] = v.y;
-            w[4 * q + 2] = v.z;
-            w[4 * q + 3] = v.w;
+        for (int m = 0; m < NM; ++m) {
+            const float k = kc[m * np];
+            acc[0][m] = (m & 1) ? 0.f : mid.x * k;
+            acc[1][m] = (m & 1) ? 0.f : mid.y * k;
+            acc[2][m] = (m & 1) ? 0.f : mid.z * k;
+            acc[3][m] = (m & 1) ? 0.f : mid.w * k;
         }
-    } else {
+        float4 r0 = mid, l0 = mid;
+        // distances d = b - 3 .. b, `last` of them within the support
+        const auto block = [&](int b, int last) {
+            const float4 r1 = read4(k0 + b), l1 = read4(k0 - b);
+            const float r[8] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w};   // g[k0 + b - 4 + i]
+            const float l[8] = {l1.x, l1.y, l1.z, l1.w, l0.x, l0.y, l0.z, l0.w};   // g[k0 - b + i]
 #pragma unroll
-        for (int q = 0; q < W; ++q) w[q] = (kw + q >= 0 && kw + q < T) ? g[kw + q] : 0.f;
-    }
-    const __attribute__((address_space(4))) float* kc = (const __attribute__((address_space(4))) float*)a.mtaps;
-    float* out = a.moments + (size_t)s * NM * L + j0;
-    // bin j0 + v: g[k0 + d] = w[v + RS + d] (k0 = j0 + v - RS)
+            for (int i = 0; i < 4; ++i) {   // d = b - 3 + i
+                if (i >= last) break;
 #pragma unroll
-    for (int par = 0; par < 2; ++par) {
-        // mirrored sums (even rows) or differences (odd rows) of every bin
-        float x[V][RS];
+                for (int v = 0; v < V; ++v) {
+                    const float hi = r[v + 1 + i], lo = l[v + 3 - i];
+                    const float sum = hi + lo, dif = hi - lo;
+#pragma unroll
+                    for (int m = 0; m < NM; ++m) acc[v][m] = fmaf((m & 1) ? dif : sum, kc[m * np + b + i], acc[v][m]);
+                }
+            }
+            r0 = r1;
+            l0 = l1;
+        };
+        int b = 4;
+#pragma unroll 2
+        for (; b <= a.Rs; b += 4) block(b, 4);
+        // (the rest by count, not by zero taps: nothing past the support is used)
+        if (b - 3 <= a.Rs) block(b, a.Rs - b + 4);
+        float* mine = tr[wave] + lane * V * NS;
 #pragma unroll
         for (int v = 0; v < V; ++v)
 #pragma unroll
-            for (int d = 1; d <= RS; ++d)
-                x[v][d - 1] = par == 0 ? w[v + RS + d] + w[v + RS - d] : w[v + RS + d] - w[v + RS - d];
-        // one row at a time: its kernel in scalar registers
-#pragma unroll 1
-        for (int m = par; m < NM; m += 2) {
-            const int c = m * ND + RS;   // K_m(0)
-            float acc[V];
-#pragma unroll
-            for (int v = 0; v < V; ++v) acc[v] = par == 0 ? w[v + RS] * kc[c] : 0.f;
-#pragma unroll
-            for (int d = 1; d <= RS; ++d) {
-                const float k = kc[c + d];
-#pragma unroll
-                for (int v = 0; v < V; ++v) acc[v] = fmaf(x[v][d - 1], k, acc[v]);
-            }
-            if constexpr (ALIGNED) {
-                // j0 and L are multiples of 4, so j0 + 3 < L
-                *reinterpret_cast<float4*>(out + (size_t)m * L) = make_float4(acc[0], acc[1], acc[2], acc[3]);
-            } else {
-#pragma unroll
-                for (int v = 0; v < V; ++v)
-                    if (j0 + v < L) out[(size_t)m * L + v] = acc[v];
-            }
-        }
+            for (int m = 0; m < NS; ++m) mine[v * NS + m] = m < NM ? acc[v][m] : 0.f;
     }
+    // (a wavefront's LDS operations run in order; its piece is no one else's)
+    __builtin_amdgcn_wave_barrier();
+    const int64_t t0 = t - lane;   // the wavefront's first thread: its output is contiguous
+    if (t0 >= n_thr) return;
+    const int n4 = (int)(n_thr - t0 < 64 ? n_thr - t0 : 64) * NS;
+    float4* dst = reinterpret_cast<float4*>(a.moments + t0 * V * NS);
+    const float4* src = reinterpret_cast<const float4*>(tr[wave]);
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+        if (i * 64 + lane < n4) dst[i * 64 + lane] = src[i * 64 + lane];
 }
 
-template <bool COS, int RS, bool DB>
+// Gather: PPT patches per thread, a range of scan points per workgroup whose
+// correlation rows are staged in LDS a few points at a time.  The patch's
+// albedo weight a is left out of the pair sums (all are linear in it) and
+// joins them at the end.  Wavefronts whose patches all arrive past the window
+// skip the pair.  Bound: VALU (about 80 instructions per pair that reaches the
+// window) and the staging, which reads every row once per block of PPT x 1024
+// patches.  128^2 points and patches, 1024 bins, radius 16: 0.67 -> 0.49 ms;
+// 48 x 40 points, 3840 patches, 1501 bins, radius 31: 522 us by taps, 95 with
+// the correlations.
+template <bool COS, int NM, bool DB>
 __global__ void __launch_bounds__(kBlock) k_adjoint_mom(const SmoothArgs a)
 {
-    constexpr int NM = adj_moments(RS), MT = NM - 2, PPT = kAdjPatches, NB = DB ? 2 : 1;
+    constexpr int NS = adj_row_words(NM), PPT = kAdjPatches, NB = DB ? 2 : 1;
     extern __shared__ __align__(16) unsigned char smem[];
-    const int T = a.T, L = a.mlen, NR = a.rows;
-    // NB buffers of NR scan points' rows [NR][NM][L], then per buffer the
-    // points' offsets (fp64), positions and gains
-    const size_t buf_bytes = ((size_t)NR * NM * L * 4 + 15) & ~(size_t)15;
+    const int T = a.T, L = a.mlen, NR = a.rows, Rs = a.Rs, H = adj_halo(a.Rs);
+    // NB buffers of NR scan points' rows [NR][L][NS], then per buffer the
+    // points' offsets in bins (fp64), positions, gains and cull distances
+    const size_t buf_bytes = (size_t)NR * NS * L * 4;
     double* so = reinterpret_cast<double*>(smem + NB * buf_bytes);
     float* swx = reinterpret_cast<float*>(so + NB * NR);
     float* swy = swx + NB * NR;
     float* sg = swy + NB * NR;
+    float* sc = sg + NB * NR;
     const int n_act = smooth_active(a);
+    // Every workgroup gets patches and scan points from all over the scene,
+    // as near the borders more pairs arrive past the window: the blocks with
+    // records take the pieces of 256 (a 16 x 16-pixel block, one wavefront
+    // each on the four SIMDs) in turn, and the splits the stages of NR points.
+    const int nbx = (n_act + PPT * kBlock - 1) / (PPT * kBlock);
+    if ((int)blockIdx.x >= nbx) return;   // (nothing reads this block's partials)
     const int split = (int)blockIdx.y;
     const int S = a.rx.n * a.ry.n;
-    const int per = (S + a.n_split - 1) / a.n_split;
-    const int s0 = min(S, split * per), s1 = min(S, s0 + per);
-    float4 A[PPT], B[PPT];
+    const auto patch = [&](int i) {
+        return (((int)threadIdx.x / 256 + 4 * i) * nbx + (int)blockIdx.x) * 256 + (int)threadIdx.x % 256;
+    };
+    double px[PPT], py[PPT];
+    float4 B[PPT];       // normal; w: depth
+    float tp[PPT];       // 2 / pz
     bool live[PPT];
-    double gz[PPT], ga[PPT], gnx[PPT], gny[PPT], gnz[PPT];
+    double gz[PPT], ga[PPT], gnx[PPT], gny[PPT], gn[PPT];
 #pragma unroll
     for (int i = 0; i < PPT; ++i) {
-        const int p = ((int)blockIdx.x * PPT + i) * kBlock + (int)threadIdx.x;
+        const int p = patch(i);
         live[i] = p < n_act;
-        A[i] = make_float4(0.f, 0.f, 1.f, 0.f);
+        float4 A = make_float4(0.f, 0.f, 1.f, 0.f);
         B[i] = make_float4(0.f, 0.f, -1.f, 0.f);
         if (live[i]) {
-            A[i] = a.patches[2 * (size_t)p];
+            A = a.patches[2 * (size_t)p];
             B[i] = a.patches[2 * (size_t)p + 1];
         }
-        gz[i] = ga[i] = gnx[i] = gny[i] = gnz[i] = 0.0;
+        B[i].w = A.z;
+        px[i] = (double)A.x;
+        py[i] = (double)A.y;
+        tp[i] = 2.f / A.z;
+        gz[i] = ga[i] = gnx[i] = gny[i] = gn[i] = 0.0;
     }
     // the constants of scan points [j, j + nr) into buffer b
     auto stage_consts = [&](int b, int j, int nr) {
@@ -754,7 +857,8 @@ __global__ void __launch_bounds__(kBlock) k_adjoint_mom(const SmoothArgs a)
             const float wx = canon(a.rx, h / a.ry.n), wy = canon(a.ry, h % a.ry.n);
             double off, g;
             device_leg(wx, wy, a.cx, a.cy, a.s, &off, &g);
-            so[b * NR + threadIdx.x] = off + off;
+            so[b * NR + threadIdx.x] = (off + off) * a.inv;
+            sc[b * NR + threadIdx.x] = cull_r2(a, off + off);
             swx[b * NR + threadIdx.x] = wx;
             swy[b * NR + threadIdx.x] = wy;
             sg[b * NR + threadIdx.x] = (float)(g * g);
@@ -767,9 +871,9 @@ __global__ void __launch_bounds__(kBlock) k_adjoint_mom(const SmoothArgs a)
     // of the contiguous rows, the last one masked past the end)
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = (int)threadIdx.x & 63;
     auto stage_rows_db = [&](int b, int j, int nr) {
-        const float4* s4 = reinterpret_cast<const float4*>(a.moments + (size_t)j * NM * L);
+        const float4* s4 = reinterpret_cast<const float4*>(a.moments + (size_t)j * NS * L);
         float* dst = reinterpret_cast<float*>(smem + b * buf_bytes);
-        const int n4 = nr * NM * (L >> 2);
+        const int n4 = nr * NS * (L >> 2);
         for (int pc = wave; pc * 64 < n4; pc += kBlock / 64) {
             const int i = pc * 64 + lane;
             if (i < n4)
@@ -778,14 +882,18 @@ __global__ void __launch_bounds__(kBlock) k_adjoint_mom(const SmoothArgs a)
                                                  0, 0);
         }
     };
-    const int nst = s1 > s0 ? (s1 - s0 + NR - 1) / NR : 0;
+    const double inv2 = 2.0 * a.inv;
+    const float invf = (float)a.inv, inv2f = (float)inv2;
+    const int n_all = (S + NR - 1) / NR;   // stages of all splits: this one's are split, split + n_split, ...
+    const int nst = split < n_all ? (n_all - split + a.n_split - 1) / a.n_split : 0;
     if (DB && nst > 0) {
-        stage_rows_db(0, s0, min(NR, s1 - s0));
-        stage_consts(0, s0, min(NR, s1 - s0));
+        const int j = split * NR;
+        stage_rows_db(0, j, min(NR, S - j));
+        stage_consts(0, j, min(NR, S - j));
     }
     for (int st = 0; st < nst; ++st) {
-        const int j0 = s0 + st * NR;
-        const int nr = min(NR, s1 - j0);
+        const int j0 = (split + st * a.n_split) * NR;
+        const int nr = min(NR, S - j0);
         const int b = DB ? (st & 1) : 0;
         if (DB) {
             // this wavefront's loads into buffer b have landed; past the
@@ -794,34 +902,29 @@ __global__ void __launch_bounds__(kBlock) k_adjoint_mom(const SmoothArgs a)
             __builtin_amdgcn_s_waitcnt(0);
             __syncthreads();
             if (st + 1 < nst) {
-                stage_rows_db(b ^ 1, j0 + NR, min(NR, s1 - j0 - NR));
-                stage_consts(b ^ 1, j0 + NR, min(NR, s1 - j0 - NR));
+                const int j = j0 + a.n_split * NR;
+                stage_rows_db(b ^ 1, j, min(NR, S - j));
+                stage_consts(b ^ 1, j, min(NR, S - j));
             }
         } else {
             __syncthreads();
-            // stage the correlation rows of scan points [j0, j0 + nr): contiguous
-            float* rowbuf = reinterpret_cast<float*>(smem);
-            const float* src = a.moments + (size_t)j0 * NM * L;
-            if ((L & 3) == 0) {
-                // four loads in flight per thread before their LDS stores (a load
-                // past the end rereads the last element; its store is skipped)
-                const float4* s4 = reinterpret_cast<const float4*>(src);
-                float4* d4 = reinterpret_cast<float4*>(rowbuf);
-                const int n4 = nr * NM * (L >> 2);
-                for (int i0 = threadIdx.x; i0 < n4; i0 += 4 * kBlock) {
-                    const int last = n4 - 1;
-                    const float4 v0 = s4[min(i0, last)];
-                    const float4 v1 = s4[min(i0 + kBlock, last)];
-                    const float4 v2 = s4[min(i0 + 2 * kBlock, last)];
-                    const float4 v3 = s4[min(i0 + 3 * kBlock, last)];
-                    __builtin_amdgcn_sched_barrier(0);
-                    d4[i0] = v0;
-                    if (i0 + kBlock < n4) d4[i0 + kBlock] = v1;
-                    if (i0 + 2 * kBlock < n4) d4[i0 + 2 * kBlock] = v2;
-                    if (i0 + 3 * kBlock < n4) d4[i0 + 3 * kBlock] = v3;
-                }
-            } else {
-                for (int i = threadIdx.x; i < nr * NM * L; i += kBlock) rowbuf[i] = src[i];
+            // stage the correlation rows of scan points [j0, j0 + nr): contiguous,
+            // four loads in flight per thread before their LDS stores (a load
+            // past the end rereads the last element; its store is skipped)
+            const float4* s4 = reinterpret_cast<const float4*>(a.moments + (size_t)j0 * NS * L);
+            float4* d4 = reinterpret_cast<float4*>(smem);
+            const int n4 = nr * NS * (L >> 2);
+            for (int i0 = threadIdx.x; i0 < n4; i0 += 4 * kBlock) {
+                const int last = n4 - 1;
+                const float4 v0 = s4[min(i0, last)];
+                const float4 v1 = s4[min(i0 + kBlock, last)];
+                const float4 v2 = s4[min(i0 + 2 * kBlock, last)];
+                const float4 v3 = s4[min(i0 + 3 * kBlock, last)];
+                __builtin_amdgcn_sched_barrier(0);
+                d4[i0] = v0;
+                if (i0 + kBlock < n4) d4[i0 + kBlock] = v1;
+                if (i0 + 2 * kBlock < n4) d4[i0 + 2 * kBlock] = v2;
+                if (i0 + 3 * kBlock < n4) d4[i0 + 3 * kBlock] = v3;
             }
             stage_consts(0, j0, nr);
             __syncthreads();
@@ -829,48 +932,63 @@ __global__ void __launch_bounds__(kBlock) k_adjoint_mom(const SmoothArgs a)
         const float* rowbuf = reinterpret_cast<const float*>(smem + b * buf_bytes);
         for (int jj = 0; jj < nr; ++jj) {
             // the scan point's constants, read once for the patches below
-            const float wxj = uniform_f(swx[b * NR + jj]), wyj = uniform_f(swy[b * NR + jj]),
-                        gj = uniform_f(sg[b * NR + jj]);
-            const double oj = uniform_d(so[b * NR + jj]);
+            const double wxj = (double)uniform_f(swx[b * NR + jj]), wyj = (double)uniform_f(swy[b * NR + jj]);
+            const float gj = uniform_f(sg[b * NR + jj]), cut = uniform_f(sc[b * NR + jj]);
+            const double oij = uniform_d(so[b * NR + jj]);
+            const float* row = rowbuf + (size_t)jj * L * NS;
 #pragma unroll
             for (int i = 0; i < PPT; ++i) {
                 if (!live[i]) continue;
-                const PairS q = pair_smooth(A[i], B[i], wxj, wyj, oj, gj, a.inv, COS, true);
-                const double k0d = floor(q.u);
-                const int k0 = (int)k0d;   // u >= 0; a saturated conversion fails the test below
-                if ((uint32_t)k0 + (uint32_t)RS > (uint32_t)(T - 1 + 2 * RS)) continue;
-                const float mt = 0.5f - (float)(q.u - k0d);   // -t
-                const float* c = rowbuf + (size_t)jj * NM * L + (k0 + RS);
-                float G0 = c[MT * L], G1 = (float)(MT + 1) * c[(MT + 1) * L];
+                const double ex = px[i] - wxj, ey = py[i] - wyj, ez = (double)B[i].w;
+                const double r2d = fma(ex, ex, fma(ey, ey, ez * ez));
+                const float r2f = (float)r2d;
+                if (__all(r2f >= cut)) continue;
+                const Arrival q = arrival(r2d, r2f, inv2, oij, invf);
+                if ((uint32_t)q.k0 + (uint32_t)Rs > (uint32_t)(T - 1 + 2 * Rs)) continue;
+                const float* c = row + __mul24(q.k0 + H, NS);   // (24 bits hold T + 2 H)
+                float D = c[NM - 1];   // P'(-t), one term behind P(-t)
+                float P = fmaf(D, q.mt, c[NM - 2]);
 #pragma unroll
-                for (int m = MT - 1; m >= 0; --m) {
-                    G0 = fmaf(G0, mt, c[m * L]);
-                    G1 = fmaf(G1, mt, (float)(m + 1) * c[(m + 1) * L]);
+                for (int m = NM - 3; m >= 0; --m) {
+                    D = fmaf(D, q.mt, P);
+                    P = fmaf(P, q.mt, c[m]);
                 }
-                G1 = -G1;
-                // dL/dw = G0, dL/du = w G1
-                const float dz = fmaf(G0, q.dw_dz, q.w * G1 * q.du_dz);
-                gz[i] += (double)dz;
-                ga[i] += (double)(G0 * q.w_a);
+                // dL/dw = G0 = P, dL/du = w G1 = -w P'; w = a wa
+                const float pz = B[i].w, ri4 = q.ri2 * q.ri2;
+                const float du = (inv2f * pz) * q.rinv;
                 if (COS) {
-                    const float gn = G0 * q.dwn;
-                    gnx[i] += (double)(gn * (A[i].x - wxj));
-                    gny[i] += (double)(gn * (A[i].y - wyj));
-                    gnz[i] += (double)(gn * A[i].z);
+                    // wa = g pz^2 c^2 / r^8: d wa / dpz = wa (2 / pz - 8 pz / r^2) - 2 kc n_z,
+                    // d wa / dn = -2 kc (p - w), kc = g pz^2 c / r^8
+                    const float dx = (float)ex, dy = (float)ey;
+                    const float cn = fmaxf(-(B[i].x * dx + B[i].y * dy + B[i].z * pz), 0.f);
+                    const float kc = (gj * pz * pz) * (ri4 * ri4) * cn;
+                    const float wa = kc * cn;
+                    const float h = fmaf(-8.f * pz, q.ri2, tp[i]);
+                    gz[i] += (double)(wa * fmaf(P, h, -D * du));
+                    ga[i] += (double)(P * wa);
+                    const float g = P * kc;
+                    gn[i] += (double)g;
+                    gnx[i] += (double)(g * dx);
+                    gny[i] += (double)(g * dy);
+                } else {
+                    const float wa = gj * ri4;   // d wa / dpz = -4 wa pz / r^2
+                    gz[i] += (double)(wa * fmaf(P, -4.f * pz * q.ri2, -D * du));
+                    ga[i] += (double)(P * wa);
                 }
             }
         }
     }
 #pragma unroll
     for (int i = 0; i < PPT; ++i) {
-        const int p = ((int)blockIdx.x * PPT + i) * kBlock + (int)threadIdx.x;
+        const int p = patch(i);
         if (!live[i]) continue;
+        const double aw = (double)a.patches[2 * (size_t)p].w;
         double* o = a.partial + ((size_t)split * a.n_cap + p) * kAdjStride;
-        o[0] = gz[i];
+        o[0] = aw * (gz[i] - 2.0 * (double)B[i].z * gn[i]);
         o[1] = ga[i];
-        o[2] = gnx[i];
-        o[3] = gny[i];
-        o[4] = gnz[i];
+        o[2] = -2.0 * aw * gnx[i];
+        o[3] = -2.0 * aw * gny[i];
+        o[4] = -2.0 * aw * (double)B[i].w * gn[i];
     }
 }
 
@@ -1026,41 +1144,52 @@ hipError_t launch_smooth(const SmoothArgs& a, int tx, int ty, int64_t n_blocks, 
     return hipErrorInvalidValue;
 }
 
-bool smooth_moments_radius(int rs) { return rs == 12 || rs == 16 || rs == 20; }
-
-template <int RS, bool PITCH>
-static hipError_t launch_smooth_mom_pitch(const SmoothArgs& a, int64_t n_blocks, size_t lds, hipStream_t st)
+hipError_t launch_smooth_prep(const SmoothArgs& a, const MomentFit& f, bool adjoint, hipStream_t st)
 {
-    const void* k = a.cosines ? (const void*)k_smooth_mom<true, RS, PITCH> : (const void*)k_smooth_mom<false, RS, PITCH>;
-    hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    if (a.cosines)
-        hipLaunchKernelGGL((k_smooth_mom<true, RS, PITCH>), dim3((unsigned)n_blocks), dim3(kBlock), lds, st, a);
-    else
-        hipLaunchKernelGGL((k_smooth_mom<false, RS, PITCH>), dim3((unsigned)n_blocks), dim3(kBlock), lds, st, a);
+    const int words = f.n * (adjoint ? taps_adj(f.Rs) : taps_fwd(f.Rs));
+    int nb = (words + kStatBlock - 1) / kStatBlock;
+    if (nb > 16) nb = 16;
+    hipLaunchKernelGGL(k_smooth_prep, dim3((unsigned)(a.n_stats + nb)), dim3(kStatBlock), 0, st, a, f, adjoint ? 1 : 0);
     return hipGetLastError();
 }
 
-template <int RS>
-static hipError_t launch_smooth_mom_rs(const SmoothArgs& a, int64_t n_blocks, size_t lds, hipStream_t st)
+template <int NM, int NP, int WG>
+static hipError_t launch_smooth_mom(const SmoothArgs& a, int64_t n_blocks, hipStream_t st)
 {
-    return a.stride == smooth_mom_pitch(RS) ? launch_smooth_mom_pitch<RS, true>(a, n_blocks, lds, st)
-                                            : launch_smooth_mom_pitch<RS, false>(a, n_blocks, lds, st);
+    if (a.T + 2 * a.Rs > smooth_mom_pitch(NP, NM, WG)) return hipErrorInvalidValue;
+    constexpr size_t lds = smooth_mom_lds(NP, NM, WG);
+    const void* k = a.cosines ? (const void*)k_smooth_mom<true, NM, NP, WG> : (const void*)k_smooth_mom<false, NM, NP, WG>;
+    hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    if (a.cosines)
+        hipLaunchKernelGGL((k_smooth_mom<true, NM, NP, WG>), dim3((unsigned)n_blocks), dim3(kBlock), lds, st, a);
+    else
+        hipLaunchKernelGGL((k_smooth_mom<false, NM, NP, WG>), dim3((unsigned)n_blocks), dim3(kBlock), lds, st, a);
+    return hipGetLastError();
 }
 
-hipError_t launch_smooth_moments(const SmoothArgs& a, int64_t n_blocks, size_t lds, hipStream_t st)
+template <int NM>
+static hipError_t launch_smooth_mom_np(const SmoothArgs& a, int points, int wg, int64_t n_blocks, hipStream_t st)
+{
+    if (wg == 2) {
+        if (points == 3) return launch_smooth_mom<NM, 3, 2>(a, n_blocks, st);
+        if (points == 2) return launch_smooth_mom<NM, 2, 2>(a, n_blocks, st);
+        if (points == 1) return launch_smooth_mom<NM, 1, 2>(a, n_blocks, st);
+    }
+    if (wg == 1 && points == 1) return launch_smooth_mom<NM, 1, 1>(a, n_blocks, st);
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_smooth_moments(const SmoothArgs& a, int moments, int points, int wg, int64_t n_blocks, hipStream_t st)
 {
     if (n_blocks <= 0) return hipSuccess;
     if (n_blocks > 0x7fffffff) return hipErrorInvalidValue;
-    // the flush keeps at most 24 values per thread in registers
-    const SmoothMomShape sh = smooth_mom_shape(a.Rs);
-    if ((int64_t)sh.points * sh.moments * (a.T + 2 * a.Rs) > 24 * (int64_t)kBlock) return hipErrorInvalidValue;
-    if (a.stride < a.T + 2 * a.Rs) return hipErrorInvalidValue;
-    // moment rows, then 2 KiB for the scan points' offsets, the reduction and the taps
-    if (lds < (size_t)sh.points * sh.moments * a.stride * 8 + 2048) return hipErrorInvalidValue;
-    if (a.Rs == 12) return launch_smooth_mom_rs<12>(a, n_blocks, lds, st);
-    if (a.Rs == 16) return launch_smooth_mom_rs<16>(a, n_blocks, lds, st);
-    if (a.Rs == 20) return launch_smooth_mom_rs<20>(a, n_blocks, lds, st);
+    switch (moments) {
+    case 5: return launch_smooth_mom_np<5>(a, points, wg, n_blocks, st);
+    case 6: return launch_smooth_mom_np<6>(a, points, wg, n_blocks, st);
+    case 7: return launch_smooth_mom_np<7>(a, points, wg, n_blocks, st);
+    case 8: return launch_smooth_mom_np<8>(a, points, wg, n_blocks, st);
+    }
     return hipErrorInvalidValue;
 }
 
@@ -1090,53 +1219,51 @@ hipError_t launch_adjoint(const SmoothArgs& a, int64_t patch_blocks, size_t lds,
     return hipSuccess;
 }
 
-template <int RS, bool DB>
+template <int NM, bool DB>
 static hipError_t launch_adjoint_gather(const SmoothArgs& a, const dim3& grid, size_t lds, hipStream_t st)
 {
-    const void* k = a.cosines ? (const void*)k_adjoint_mom<true, RS, DB> : (const void*)k_adjoint_mom<false, RS, DB>;
+    const void* k = a.cosines ? (const void*)k_adjoint_mom<true, NM, DB> : (const void*)k_adjoint_mom<false, NM, DB>;
     hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     if (a.cosines)
-        hipLaunchKernelGGL((k_adjoint_mom<true, RS, DB>), grid, dim3(kBlock), lds, st, a);
+        hipLaunchKernelGGL((k_adjoint_mom<true, NM, DB>), grid, dim3(kBlock), lds, st, a);
     else
-        hipLaunchKernelGGL((k_adjoint_mom<false, RS, DB>), grid, dim3(kBlock), lds, st, a);
+        hipLaunchKernelGGL((k_adjoint_mom<false, NM, DB>), grid, dim3(kBlock), lds, st, a);
     return hipGetLastError();
 }
 
-template <int RS>
-static hipError_t launch_adjoint_mom_rs(const SmoothArgs& a, int64_t patch_blocks, size_t lds, int dbuf, hipStream_t st)
+template <int NM>
+static hipError_t launch_adjoint_mom(const SmoothArgs& a, int64_t patch_blocks, size_t lds, bool dbuf, hipStream_t st)
 {
-    const int S = a.rx.n * a.ry.n;
-    hipLaunchKernelGGL(k_adj_taps<RS>, dim3(1), dim3(256), 0, st, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    if (lds < adj_mom_lds(dbuf ? 2 : 1, a.rows, NM, a.mlen)) return hipErrorInvalidValue;
     // one thread per (scan point, 4 bins of a correlation row)
-    const int64_t n_thr = (int64_t)S * ((a.mlen + 3) / 4);
-    const unsigned blocks = (unsigned)((n_thr + 255) / 256);
-    const bool aligned = (a.T & 3) == 0 && ((uintptr_t)a.grad_out & 15) == 0 && ((uintptr_t)a.moments & 15) == 0;
-    if (aligned)
-        hipLaunchKernelGGL((k_adj_moments<RS, true>), dim3(blocks), dim3(256), 0, st, a);
+    const int64_t n_thr = (int64_t)(a.rx.n * a.ry.n) * (a.mlen / 4);
+    const int64_t blocks = (n_thr + 255) / 256;
+    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+    if ((a.T & 3) == 0 && ((uintptr_t)a.grad_out & 15) == 0)
+        hipLaunchKernelGGL((k_adj_moments<NM, true>), dim3((unsigned)blocks), dim3(256), 0, st, a);
     else
-        hipLaunchKernelGGL((k_adj_moments<RS, false>), dim3(blocks), dim3(256), 0, st, a);
-    e = hipGetLastError();
+        hipLaunchKernelGGL((k_adj_moments<NM, false>), dim3((unsigned)blocks), dim3(256), 0, st, a);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // two row buffers when the plan gave the LDS for them and the rows are
-    // whole, aligned 16-byte pieces; else one (the same rows per stage)
-    const bool db = dbuf && (a.mlen & 3) == 0 && ((uintptr_t)a.moments & 15) == 0 &&
-                    lds >= adj_mom_lds(2, a.rows, adj_moments(RS), a.mlen);
     const dim3 grid((unsigned)patch_blocks, (unsigned)a.n_split);
-    if (db) return launch_adjoint_gather<RS, true>(a, grid, lds, st);
-    return launch_adjoint_gather<RS, false>(a, grid, lds, st);
+    return dbuf ? launch_adjoint_gather<NM, true>(a, grid, lds, st) : launch_adjoint_gather<NM, false>(a, grid, lds, st);
 }
 
-hipError_t launch_adjoint_moments(const SmoothArgs& a, int64_t patch_blocks, size_t lds, int dbuf, hipStream_t st)
+hipError_t launch_adjoint_moments(const SmoothArgs& a, const MomentFit& f, int64_t patch_blocks, size_t lds, bool dbuf,
+                                  hipStream_t st)
 {
     if (patch_blocks <= 0) return hipSuccess;
-    if (patch_blocks > 0x7fffffff || a.n_split > 65535 || a.rows < 1 || a.mlen != a.T + 2 * a.Rs) return hipErrorInvalidValue;
-    if (!smooth_moments_radius(a.Rs) || lds < adj_mom_lds(1, a.rows, adj_moments(a.Rs), a.mlen)) return hipErrorInvalidValue;
-    if (a.Rs == 12) return launch_adjoint_mom_rs<12>(a, patch_blocks, lds, dbuf, st);
-    if (a.Rs == 16) return launch_adjoint_mom_rs<16>(a, patch_blocks, lds, dbuf, st);
-    if (a.Rs == 20) return launch_adjoint_mom_rs<20>(a, patch_blocks, lds, dbuf, st);
+    if (patch_blocks > 0x7fffffff || a.n_split > 65535 || a.rows < 1 || a.mlen != adj_row_bins(a.T, a.Rs))
+        return hipErrorInvalidValue;
+    const hipError_t e = launch_smooth_prep(a, f, true, st);
+    if (e != hipSuccess) return e;
+    switch (f.n) {
+    case 6: return launch_adjoint_mom<6>(a, patch_blocks, lds, dbuf, st);
+    case 7: return launch_adjoint_mom<7>(a, patch_blocks, lds, dbuf, st);
+    case 8: return launch_adjoint_mom<8>(a, patch_blocks, lds, dbuf, st);
+    case 9: return launch_adjoint_mom<9>(a, patch_blocks, lds, dbuf, st);
+    }
     return hipErrorInvalidValue;
 }
 
