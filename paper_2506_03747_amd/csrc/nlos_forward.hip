@@ -813,6 +813,14 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int block_id)
                 Bn = make_float4(0.f, 0.f, -1.f, 0.f);
             }
         }
+        // (a segment that fills up is worked off 64 entries at a time rather
+        // than pair by pair: a wavefront of 1.3e5 records against 8 histograms
+        // of 2048 bins queues 260 pairs, twice its segment, and the forward of
+        // 128^2 points took 1.82 ms so, 1.30 with the drain)
+        if (qn > qw / 2) {
+            guard_drain<CONF>(L, a, hb, Tl, wave, qw, qn);
+            qn = 0;
+        }
         PatchC pc;
         float aw;
         if (prep) {
