@@ -497,8 +497,11 @@ int nlos_lct_forward(const nlos_params* p, const float* depth, const float* albe
  * confocal 4x4, 4x2, 2x2, 2x1, 1x1; non-confocal TL,TX,TY = 2,2,2 / 2,1,2 /
  * 1,1,2 / 1,1,1).  A tuning table, measured by the autotuner, names the unit
  * per class of problems; the first matching entry whose unit fits in LDS is
- * used, otherwise the built-in rule (largest unit that fits and still gives
- * one workgroup per CU).  The table is the library's only shared state: it is
+ * used, two units to a workgroup.  Otherwise a call that runs alone takes the
+ * plan with the least estimated time (one or two units per workgroup, one or
+ * two workgroups per CU); in a list of requests (batched calls, ticks) the
+ * largest unit of which two fit and that still gives each request its share
+ * of workgroups.  The table is the library's only shared state: it is
  * copied, read under a lock, and replaced as a whole.
  */
 typedef struct nlos_tuning_entry {
@@ -510,8 +513,8 @@ typedef struct nlos_tuning_entry {
 
 typedef struct nlos_plan_info {
     int32_t tl, tx, ty;      /* unit */
-    int32_t pair;            /* 1: two units per workgroup over the whole window */
-    int32_t n_split;         /* patch ranges per unit pair */
+    int32_t pair;            /* 1: one or two units per workgroup over the whole window */
+    int32_t n_split;         /* patch ranges per workgroup's units */
     int32_t n_windows;       /* time windows (1 unless a histogram exceeds LDS) */
     int64_t workgroups;
     int64_t lds_bytes;

@@ -3,8 +3,8 @@
 For each class of problems (confocal or not, window length, number of
 histograms) it forces every supported unit shape in turn through the tuning
 table, times the forward operator on a seeded synthetic scene of that class
-(HIP events, median of repeated launches), and keeps the fastest.  The result
-is written as a JSON table that the package installs at import
+(HIP events, median of repeated launches), and keeps the fastest if it beats
+the library's own plan by more than 2%.  The result is written as a JSON table that the package installs at import
 (``load_tuning``); ``python -m paper_2506_03747_amd.autotune [out.json]``.
 
 Timing only chooses among shapes the library already supports; every shape
@@ -75,6 +75,8 @@ def tune(n_patch=192, classes=CLASSES, verbose=True):
             prm, rec, n = _scene(cls, n_patch, seed=1000 + k)
             out = torch.empty(out_shape(prm), dtype=torch.float32, device="cuda")
             key = {f: cls[f] for f in ("confocal", "t_min", "t_max", "h_min", "h_max")}
+            set_tuning([])
+            own = _time(lambda: forward(prm, rec, n, out=out))
             best = None
             for unit in (CONFOCAL_UNITS if cls["confocal"] else NONCONFOCAL_UNITS):
                 set_tuning([dict(key, tl=unit[0], tx=unit[1], ty=unit[2])])
@@ -89,7 +91,7 @@ def tune(n_patch=192, classes=CLASSES, verbose=True):
                           f"unit={unit}: {ms:.4f} ms  {plan}", flush=True)
                 if best is None or ms < best[0]:
                     best = (ms, unit)
-            if best:
+            if best and best[0] < 0.98 * own:
                 entries.append(dict(key, tl=best[1][0], tx=best[1][1], ty=best[1][2]))
             del out
     finally:

@@ -157,12 +157,12 @@ struct Cand {
 int64_t stats_count(int32_t n_patches) { return ((int64_t)n_patches + nlos::kStatBlock - 1) / nlos::kStatBlock; }
 
 // Launch plan.  Histograms are grouped in units (candidate shapes below,
-// largest first); a workgroup owns two units when the histograms of both fit
-// in the 160 KB of LDS over the whole window (taking the largest shape that
-// still gives at least one workgroup per CU), else one unit of one histogram
-// over a window of bins (time windows).  Patches are split over workgroups
-// when there are fewer workgroups than CUs.  Units are ordered by estimated
-// work inside the kernel when their count keeps that cheap.
+// largest first).  A call alone whose two smallest units fit in LDS over the
+// whole window takes the plan with the least estimated time (plan_solo).  In a
+// list of requests, or with a unit named by the tuning table, a workgroup owns
+// two units (of the named shape, or the largest that still gives at least the
+// target of workgroups), and patches are split over workgroups when there are
+// fewer.  Longer histograms: one per workgroup over a window of bins.
 // Tuning table (nlos_set_tuning): the unit shape to use per (geometry,
 // window length, histogram count) class, found by measurement.  Read under a
 // lock by every plan; replaced as a whole.
@@ -182,11 +182,104 @@ bool tuned_unit(bool conf, int32_t T, int64_t H, Cand* c)
     return false;
 }
 
-int make_plan(const nlos_params* p, int32_t n_patches, int R, int64_t target, nlos::Plan* plan)
+constexpr Cand conf_c[] = {{1, 4, 4}, {1, 4, 2}, {1, 2, 2}, {1, 2, 1}, {1, 1, 1}};
+constexpr Cand nc_c[] = {{2, 2, 2}, {2, 1, 2}, {1, 1, 2}, {1, 1, 1}};
+
+// Estimated time, in instruction cycles of a CU, of a call that runs alone with
+// units of shape c: `nu` units per workgroup (two, or one), `half` workgroups of
+// kHalfBlock threads two to a CU, the patches split over `split` workgroups.
+// A workgroup evaluates every 64-record chunk against its units, 16 (8)
+// wavefronts on four SIMDs, then writes its rows out; 256 (512) run at a time,
+// and the last round is rarely full.  Constants: instructions per chunk, unit
+// and pair and the fixed part of a workgroup, fitted to the times of every
+// feasible plan of 144 random problems (6 x 6 to 128 x 128 points, 256 to 1.6e5
+// pixels, 256 to 2048 bins, confocal and not): the plan with the least estimate
+// took 1.025 times the best plan's time in the geometric mean, the rule before
+// (the largest paired unit that gives a workgroup per CU, else split patches)
+// 1.79 times.  Float atomics of split patches: 55 G/s measured.
+double plan_cost(const nlos_params* p, double n, const Cand& c, int nu, bool half, int64_t units, int64_t split)
 {
     const bool conf = is_confocal(p);
-    static const Cand conf_c[] = {{1, 4, 4}, {1, 4, 2}, {1, 2, 2}, {1, 2, 1}, {1, 1, 1}};
-    static const Cand nc_c[] = {{2, 2, 2}, {2, 1, 2}, {1, 1, 2}, {1, 1, 1}};
+    const double nh = (double)c.tl * c.tx * c.ty, T = p->n_bins;
+    const double body = conf ? nh * (16.1 + 3.0 / c.ty + 3.0 / c.tx) : nh * 9.0 + 89.0 * c.tl + 74.0 * c.tx * c.ty;
+    const double per = 23.0 + nu * (11.6 * (conf ? 1.0 : 2.0) + 0.71 * body);
+    const double chunks = std::max(1.0, n / 64.0 / (double)split);
+    const double flush = nh * nu * T * 0.95;
+    const int64_t wg = (nu == 2 ? (units + 1) / 2 : units) * split;
+    const auto rounds = [](double x) {
+        const double up = std::ceil(x);
+        return x > 2.0 ? x + 0.42 * (up - x) : up - 0.41 * (up - x);
+    };
+    double t;
+    if (!half) {
+        const double w = std::max(chunks * per, std::ceil(chunks / 16.0) * per * 5.1) + flush + 11700.0;
+        const double x = (double)wg / kTargetBlocks;
+        // (a unit near the border has fewer pairs in the window: two by a torus
+        // shift even that out)
+        t = w * (nu == 2 ? 1.0 : 1.1) * (x <= 1.0 ? 1.0 : rounds(x));
+    } else if (wg <= kTargetBlocks) {
+        const double w = std::max(chunks * per, std::ceil(chunks / 8.0) * per * 5.1);
+        t = (w * 1.38 + flush + 10700.0) * 1.1;
+    } else {
+        const double w = std::max(2.0 * chunks * per, std::ceil(chunks / 8.0) * per * 5.1) + 1.36 * flush + 10700.0;
+        const double x = (double)wg / (2 * kTargetBlocks);
+        t = w * (x <= 1.0 ? 1.1 : rounds(x));
+    }
+    if (split > 1) t += 10000.0 + (double)n_hist(p) * T * (double)split * 0.044;
+    return t;
+}
+
+// Plan of a call that runs alone over the whole window: the least estimate over
+// the unit shapes, one or two units per workgroup, whole or half workgroups,
+// and patches split where even the smallest shapes leave CUs idle.
+int plan_solo(const nlos_params* p, int32_t n_patches, int stride, nlos::Plan* plan)
+{
+    const bool conf = is_confocal(p);
+    const int64_t L = conf ? 1 : (int64_t)p->laser.nx * p->laser.ny;
+    double best = 0.0;
+    bool any = false;
+    for (int i = 0; i < (conf ? 5 : 4); ++i) {
+        const Cand& c = conf ? conf_c[i] : nc_c[i];
+        const int64_t utx = (p->relay.nx + c.tx - 1) / c.tx, uty = (p->relay.ny + c.ty - 1) / c.ty;
+        const int64_t units = (L + c.tl - 1) / c.tl * utx * uty;
+        for (int kind = 0; kind < 3; ++kind) {   // two units; one; one in a half workgroup
+            const int nu = kind == 0 ? 2 : 1, q_cap = kind == 2 ? kQueueDefault / 2 : kQueueDefault;
+            const size_t lds = nlos::lds_bytes_for(nu * c.tl * c.tx * c.ty, stride, q_cap);
+            if (lds > (kind == 2 ? kLdsMax / 2 : kLdsMax)) continue;
+            const int64_t groups = nu == 2 ? (units + 1) / 2 : units;
+            // (0.6: about what masks leave of a map's pixels)
+            const double n = 0.6 * (double)n_patches;
+            const int64_t most = std::max<int64_t>(
+                1, std::min<int64_t>(kTargetBlocks / std::max<int64_t>(1, groups), n_patches / nlos::kBlock));
+            for (int64_t split = 1; split <= most; split += std::max<int64_t>(1, most - 1)) {   // 1 and the most
+                const double t = plan_cost(p, n, c, nu, kind == 2, units, split);
+                if (any && t >= best) continue;
+                any = true;
+                best = t;
+                plan->tl = c.tl;
+                plan->tx = c.tx;
+                plan->ty = c.ty;
+                plan->pair = nu == 2 ? 1 : 0;
+                plan->one = kind == 0 ? 0 : kind == 1 ? nlos::kBlock : nlos::kHalfBlock;
+                // torus-shift pairing needs an even side in the unit plane (x or y)
+                plan->plan = (nu == 2 && ((utx % 2) == 0 || (uty % 2) == 0)) ? 1 : 0;
+                plan->stride = stride;
+                plan->q_cap = q_cap;
+                plan->lds_bytes = lds;
+                plan->groups = groups;
+                plan->n_split = (int)split;
+                plan->n_blocks = groups * split;
+            }
+        }
+    }
+    return any && plan->n_blocks <= 0x7fffffff ? NLOS_OK : NLOS_EINVAL;
+}
+
+// `solo`: the call runs alone (one launch with the kernel variant that suits
+// it); else the plan is for a list that shares the GPU, `target` workgroups.
+int make_plan(const nlos_params* p, int32_t n_patches, int R, int64_t target, bool solo, nlos::Plan* plan)
+{
+    const bool conf = is_confocal(p);
     const Cand* cands = conf ? conf_c : nc_c;
     const int nc = conf ? 5 : 4;
     // a tuned shape comes first among the candidates (it is used when its
@@ -249,6 +342,7 @@ int make_plan(const nlos_params* p, int32_t n_patches, int R, int64_t target, nl
     plan->tx = c.tx;
     plan->ty = c.ty;
     plan->pair = pair;
+    plan->one = 0;
     plan->tw = tw;
     plan->n_tw = n_tw;
     plan->stride = stride_of(tl_len);
@@ -271,6 +365,7 @@ int make_plan(const nlos_params* p, int32_t n_patches, int R, int64_t target, nl
     plan->n_split = (int)split;
     plan->n_blocks = tiles * split;
     if (plan->n_blocks > 0x7fffffff || units > 0x7fffffff) return NLOS_EINVAL;
+    if (solo && pair && !forced) return plan_solo(p, n_patches, stride_of(T), plan);
     return NLOS_OK;
 }
 
@@ -281,14 +376,15 @@ size_t stats_bytes(int32_t n_patches)
 }
 
 int forward_workspace(const nlos_params* p, int32_t n_patches, size_t* bytes, nlos::Plan* plan_out,
-                      int64_t target = kTargetBlocks)
+                      int64_t target = kTargetBlocks, bool solo = true)
 {
     float taps[nlos::kMaxTaps];
     int32_t R = 0;
     int rc = jitter_taps(p->fwhm_ps, p->bin_ps, taps, &R);
     if (rc != NLOS_OK) return rc;
     nlos::Plan plan;
-    rc = make_plan(p, n_patches, R, target, &plan);
+    // (where only the size is asked for, any plan shows that there is one)
+    rc = make_plan(p, n_patches, R, target, solo && plan_out, &plan);
     if (rc != NLOS_OK) return rc;
     *bytes = stats_bytes(n_patches);
     if (plan_out) *plan_out = plan;
@@ -298,7 +394,8 @@ int forward_workspace(const nlos_params* p, int32_t n_patches, size_t* bytes, nl
 // Checks of one forward request, its plan (for `target` workgroups) and its
 // kernel arguments (all but the summaries pointer); *ws_need = workspace.
 int setup_forward(const nlos_params* p, const float* patches, int32_t n_patches, const int32_t* n_active,
-                  float* out, int64_t target, nlos::FwdArgs* a, nlos::Plan* plan, size_t* ws_need)
+                  float* out, int64_t target, bool solo, nlos::FwdArgs* a, nlos::Plan* plan,
+                  size_t* ws_need)
 {
     int rc = params_ok(p);
     if (rc != NLOS_OK) return rc;
@@ -306,7 +403,7 @@ int setup_forward(const nlos_params* p, const float* patches, int32_t n_patches,
     if (n_patches > 0 && !patches) return NLOS_EINVAL;
     if ((patches && !aligned(patches, 16)) || !aligned(out, 16) || (n_active && !aligned(n_active, 4)))
         return NLOS_EINVAL;
-    rc = forward_workspace(p, n_patches, ws_need, plan, target);
+    rc = forward_workspace(p, n_patches, ws_need, plan, target, solo);
     if (rc != NLOS_OK) return rc;
     rc = fill_args(p, patches, n_patches, n_active, out, a);
     if (rc != NLOS_OK) return rc;
@@ -375,7 +472,7 @@ int plan_batch(const nlos_request* reqs, int32_t n, FwdBatch* b)
         const double pairs = (double)n_hist(&r.params) * (double)std::max(r.n_patches, 1);
         const int64_t target = std::max<int64_t>(1, (int64_t)std::ceil(kTargetBlocks * pairs / total));
         size_t need = 0;
-        const int rc = setup_forward(&r.params, r.patches, r.n_patches, r.n_active, r.out, target, &b->args[i],
+        const int rc = setup_forward(&r.params, r.patches, r.n_patches, r.n_active, r.out, target, false, &b->args[i],
                                      &b->plans[i], &need);
         if (rc != NLOS_OK) return rc;
         work[i] = pairs / (double)std::max<int64_t>(1, b->plans[i].n_blocks);
@@ -1029,7 +1126,7 @@ int nlos_forward(const nlos_params* p, const float* patches, int32_t n_patches, 
     nlos::FwdArgs a;
     nlos::Plan plan;
     size_t need = 0;
-    int rc = setup_forward(p, patches, n_patches, n_active, out, kTargetBlocks, &a, &plan, &need);
+    int rc = setup_forward(p, patches, n_patches, n_active, out, kTargetBlocks, true, &a, &plan, &need);
     if (rc != NLOS_OK) return rc;
     if (ws_bytes < need) return NLOS_ENOSPC;
     if (need > 0 && !ws) return NLOS_EINVAL;
@@ -1100,7 +1197,7 @@ int nlos_tick_plan(const nlos_tick_caps* caps, const nlos_sim_request* reqs, int
         const double pairs = (double)n_hist(&r.params) * (double)npx;
         const int64_t target = std::max<int64_t>(1, (int64_t)std::ceil(kTargetBlocks * pairs / std::max(total, 1.0)));
         size_t need = 0;
-        rc = setup_forward(&r.params, r.patches, npx, r.n_active, r.out, target, &fa[i], &pl[i], &need);
+        rc = setup_forward(&r.params, r.patches, npx, r.n_active, r.out, target, false, &fa[i], &pl[i], &need);
         if (rc != NLOS_OK) return rc;
         const nlos::Plan& plan = pl[i];
         const int v = nlos::tick_variant(plan.tx, plan.ty, fa[i].cosines != 0);
@@ -1259,7 +1356,7 @@ int nlos_forward_noalloc(const nlos_params* p, const float* patches, int32_t n_p
     nlos::FwdArgs a;
     nlos::Plan plan;
     size_t need = 0;
-    int rc = setup_forward(p, patches, n_patches, n_active, out, kTargetBlocks, &a, &plan, &need);
+    int rc = setup_forward(p, patches, n_patches, n_active, out, kTargetBlocks, true, &a, &plan, &need);
     if (rc != NLOS_OK) return rc;
     if (n_patches > NLOS_NOALLOC_MAX_PATCHES || need > kNoAllocScratchBytes) return NLOS_ENOSPC;
     const int dev = device_check();
@@ -1306,7 +1403,7 @@ int nlos_simulate(const nlos_params* p, const nlos_grid* g, const float* depth, 
     nlos::FwdArgs a;
     nlos::Plan plan;
     size_t need_fwd = 0;
-    rc = setup_forward(p, patches, n_patches, n_active, out, kTargetBlocks, &a, &plan, &need_fwd);
+    rc = setup_forward(p, patches, n_patches, n_active, out, kTargetBlocks, true, &a, &plan, &need_fwd);
     if (rc != NLOS_OK) return rc;
     size_t need = 0;
     rc = nlos_simulate_workspace_bytes(p, g, &need);
@@ -1681,12 +1778,12 @@ int nlos_get_plan(const nlos_params* p, int32_t n_patches, nlos_plan_info* info)
     int rc = jitter_taps(p->fwhm_ps, p->bin_ps, taps, &R);
     if (rc != NLOS_OK) return rc;
     nlos::Plan plan;
-    rc = make_plan(p, n_patches, R, kTargetBlocks, &plan);
+    rc = make_plan(p, n_patches, R, kTargetBlocks, true, &plan);
     if (rc != NLOS_OK) return rc;
     info->tl = plan.tl;
     info->tx = plan.tx;
     info->ty = plan.ty;
-    info->pair = plan.pair;
+    info->pair = plan.pair || plan.one ? 1 : 0;
     info->n_split = plan.n_split;
     info->n_windows = plan.n_tw;
     info->workgroups = plan.n_blocks;

@@ -45,7 +45,6 @@ namespace nlos {
 
 typedef unsigned long long u64;
 
-constexpr int kQueueWaves = kBlock / 64;   // the guard queue has one segment per wavefront
 
 size_t lds_bytes_for(int slots, int stride, int q_cap)
 {
@@ -61,7 +60,7 @@ size_t lds_bytes_for(int slots, int stride, int q_cap)
 // LDS layout (8-byte aligned: histograms, queue and fp64 table come first).
 struct Lds {
     u64* hist;
-    uint2* q;       // guard queue: kQueueWaves segments of (record << 8 | slot, increment)
+    uint2* q;       // guard queue: a segment per wavefront of (record << 8 | slot, increment)
     double* so;     // [slots] fp64 path offset o (both device legs)
     long long* row; // [slots] output histogram index, -1: not written
     float* wlx;     // [slots] laser point (confocal: = detector point)
@@ -135,7 +134,7 @@ __device__ __forceinline__ float rect_rect_d2(float ax0, float ax1, float ay0, f
 
 // Block-wide maxima of N non-negative floats, in place (DPP within each
 // wavefront, then LDS; `red` holds N floats per wavefront).
-template <int N>
+template <int N, int BLK>
 __device__ __forceinline__ void block_max(float* v, float* red)
 {
 #pragma unroll
@@ -147,7 +146,7 @@ __device__ __forceinline__ void block_max(float* v, float* red)
 #pragma unroll
     for (int k = 0; k < N; ++k) {
         float m = 0.f;
-        for (int w = 0; w < kBlock / 64; ++w) m = fmaxf(m, red[w * N + k]);
+        for (int w = 0; w < BLK / 64; ++w) m = fmaxf(m, red[w * N + k]);
         v[k] = m;
     }
 }
@@ -368,7 +367,14 @@ template <bool PAIR>
 __device__ __forceinline__ void pick_units(const FwdArgs& a, int grp, int* u)
 {
     if (!PAIR) {
-        u[0] = grp;
+        // from the middle of the wall outwards in x, then y (laser tiles
+        // outermost): most pairs reach the window there, so that the workgroups
+        // with the least work start last
+        const int tx = a.tiles_x, ty = a.tiles_y;
+        const int ky = grp % ty, kx = (grp / ty) % tx, ul = grp / (ty * tx);
+        const int ux = (tx - 1) / 2 + ((kx & 1) ? (kx + 1) / 2 : -(kx / 2));
+        const int uy = (ty - 1) / 2 + ((ky & 1) ? (ky + 1) / 2 : -(ky / 2));
+        u[0] = (ul * tx + ux) * ty + uy;
         return;
     }
     const int tx = a.tiles_x, ty = a.tiles_y, plane = tx * ty;
@@ -500,12 +506,12 @@ __device__ __forceinline__ void flush_segment(const FwdArgs& a, const Lds& L, in
     }
 }
 
-template <int RM, int NS>
+template <int RM, int NS, int BLK>
 __device__ __forceinline__ void flush_rows(const FwdArgs& a, const Lds& L, int Tl, int hb, int t0w, int t1w)
 {
     constexpr int V = kFlushV;
     constexpr int K = 2 * RM + 1;
-    constexpr int n_waves = kBlock / 64;
+    constexpr int n_waves = BLK / 64;
     const int R = a.R;
     const int RMr = RM > 16 ? jitter_rm(R) : RM;   // the radius the host sized the rows for
     const int lead = flush_lead(RMr), Lr = flush_row_logical(Tl, RMr);
@@ -565,31 +571,31 @@ __device__ __forceinline__ void flush_rows(const FwdArgs& a, const Lds& L, int T
 // Flush: histograms (fixed point in LDS) -> float rows -> Gaussian jitter ->
 // output, after every pair of the workgroup has been added (the caller's
 // barrier); one compiled radius per rounded jitter radius.
-template <int NS>
+template <int NS, int BLK>
 __device__ __forceinline__ void flush(const FwdArgs& a, const Lds& L, int hb, int Tl, int t0w, int t1w)
 {
     const int RM = jitter_rm(a.R);
     if (RM == 2) {
-        flush_rows<2, NS>(a, L, Tl, hb, t0w, t1w);
+        flush_rows<2, NS, BLK>(a, L, Tl, hb, t0w, t1w);
     } else if (RM == 4) {
-        flush_rows<4, NS>(a, L, Tl, hb, t0w, t1w);
+        flush_rows<4, NS, BLK>(a, L, Tl, hb, t0w, t1w);
     } else if (RM == 6) {
-        flush_rows<6, NS>(a, L, Tl, hb, t0w, t1w);
+        flush_rows<6, NS, BLK>(a, L, Tl, hb, t0w, t1w);
     } else if (RM == 8) {
-        flush_rows<8, NS>(a, L, Tl, hb, t0w, t1w);
+        flush_rows<8, NS, BLK>(a, L, Tl, hb, t0w, t1w);
     } else if (RM == 12) {
-        flush_rows<12, NS>(a, L, Tl, hb, t0w, t1w);
+        flush_rows<12, NS, BLK>(a, L, Tl, hb, t0w, t1w);
     } else if (RM == 16) {
-        flush_rows<16, NS>(a, L, Tl, hb, t0w, t1w);
+        flush_rows<16, NS, BLK>(a, L, Tl, hb, t0w, t1w);
     } else {
-        flush_rows<17, NS>(a, L, Tl, hb, t0w, t1w);   // any radius past 16: the generic tap loop
+        flush_rows<17, NS, BLK>(a, L, Tl, hb, t0w, t1w);   // any radius past 16: the generic tap loop
     }
 }
 
 // ---------------------------------------------------------------------------
 // The pair kernel.  Slot j of the workgroup: unit k = j / NH, then within the
 // unit (laser l, column c, row r) with j % NH = (l * TX + c) * TY + r.
-template <bool CONF, int TL, int TX, int TY, bool COS, bool WIN, bool PAIR>
+template <bool CONF, int TL, int TX, int TY, bool COS, bool WIN, bool PAIR, int BLK = kBlock>
 __device__ __forceinline__ void forward_body(const FwdArgs& a, int block_id)
 {
     constexpr int ND = TX * TY;
@@ -658,8 +664,8 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int block_id)
 #pragma unroll
     for (int k = 0; k < NU; ++k) unit_on[k] = __builtin_amdgcn_readfirstlane(unit[k] >= 0 ? 1 : 0);
 
-    for (int i = threadIdx.x; i < NS * a.stride / 2; i += kBlock) reinterpret_cast<uint4*>(L.hist)[i] = uint4{0, 0, 0, 0};
-    if (threadIdx.x == 0) *L.next = 2u * (kBlock / 64);
+    for (int i = threadIdx.x; i < NS * a.stride / 2; i += BLK) reinterpret_cast<uint4*>(L.hist)[i] = uint4{0, 0, 0, 0};
+    if (threadIdx.x == 0) *L.next = 2u * (BLK / 64);
     if (threadIdx.x < NS) {
         const int j = threadIdx.x;
         const int k = j / NH, jl = j % NH;
@@ -706,13 +712,13 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int block_id)
     float wbk[NU];
 #pragma unroll
     for (int k = 0; k < NU; ++k) wbk[k] = 0.f;
-    for (int i = threadIdx.x; i < a.n_stats; i += kBlock) {
+    for (int i = threadIdx.x; i < a.n_stats; i += BLK) {
         const StatF c = i == (int)threadIdx.x ? decode_stat(st0a, v4i{st0b.x, st0b.y, st0b.z, 0}) : load_stat(a.stats, i);
 #pragma unroll
         for (int k = 0; k < NU; ++k)
             if (uvalid[k]) wbk[k] = fmaxf(wbk[k], unit_weight_bound<CONF, TL, TX, TY>(a, unit[k], c));
     }
-    block_max<NU>(wbk, L.red);   // includes a barrier: the tables above are visible
+    block_max<NU, BLK>(wbk, L.red);   // includes a barrier: the tables above are visible
     float sk[NU];
 #pragma unroll
     for (int k = 0; k < NU; ++k) sk[k] = wbk[k] > 0.f ? 2147483648.0f / wbk[k] : 1.0f;
@@ -781,7 +787,7 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int block_id)
         cut_r2[k] = rc * rc * 1.00001f;
     }
 
-    const int qw = a.q_cap / kQueueWaves;
+    const int qw = a.q_cap / (BLK / 64);
     int qn = 0;
     // Wavefronts take 64-record chunks from a counter in LDS, so they finish
     // together however unevenly culling thins the chunks.  A wavefront holds
@@ -941,13 +947,24 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int block_id)
     guard_drain<CONF>(L, a, hb, Tl, wave, qw, qn);
     if (a.eval_pairs && lane == 0) atomicAdd(a.eval_pairs, (unsigned long long)n_eval);
     __syncthreads();
-    flush<NS>(a, L, hb, Tl, t0w, t1w);
+    flush<NS, BLK>(a, L, hb, Tl, t0w, t1w);
 }
 
 template <bool CONF, int TL, int TX, int TY, bool COS, bool WIN, bool PAIR>
 __global__ void __launch_bounds__(kBlock) k_forward(const FwdArgs a)
 {
     forward_body<CONF, TL, TX, TY, COS, WIN, PAIR>(a, (int)blockIdx.x);
+}
+
+// One unit per workgroup over the whole window: a larger unit than two fit (its
+// legs shared by more pairs: 64 lasers x 128^2 detectors, 2048 bins, 8.5 ms with
+// two units of 2 x 1 x 2, 7.4 with one of 2 x 2 x 2), or with BLK = kHalfBlock two
+// workgroups per CU, where one sets up or writes out while the other adds and
+// odd unit counts fill the chip better (plan_cost).
+template <bool CONF, int TL, int TX, int TY, bool COS, int BLK>
+__global__ void __launch_bounds__(BLK, 4) k_forward_one(const FwdArgs a)
+{
+    forward_body<CONF, TL, TX, TY, COS, false, false, BLK>(a, (int)blockIdx.x);
 }
 
 // Request of workgroup `block` in a batch: the last i with first[i] <= block
@@ -1131,19 +1148,29 @@ static hipError_t launch_k(K kern, const FwdArgs& a, const Plan& plan, hipStream
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)plan.lds_bytes);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)plan.n_blocks), dim3(kBlock), plan.lds_bytes, st, a);
+    hipLaunchKernelGGL(kern, dim3((unsigned)plan.n_blocks), dim3(plan.one ? plan.one : kBlock), plan.lds_bytes, st, a);
     return hipGetLastError();
 }
 
 template <bool CONF, int TL, int TX, int TY>
 static hipError_t launch_shape(const FwdArgs& a, const Plan& plan, hipStream_t st)
 {
+    if (plan.one == kHalfBlock) {
+        return a.cosines ? launch_k(k_forward_one<CONF, TL, TX, TY, true, kHalfBlock>, a, plan, st)
+                         : launch_k(k_forward_one<CONF, TL, TX, TY, false, kHalfBlock>, a, plan, st);
+    }
+    if (plan.one == kBlock) {
+        return a.cosines ? launch_k(k_forward_one<CONF, TL, TX, TY, true, kBlock>, a, plan, st)
+                         : launch_k(k_forward_one<CONF, TL, TX, TY, false, kBlock>, a, plan, st);
+    }
     if (plan.pair) {
         return a.cosines ? launch_k(k_forward<CONF, TL, TX, TY, true, false, true>, a, plan, st)
                          : launch_k(k_forward<CONF, TL, TX, TY, false, false, true>, a, plan, st);
     }
-    return a.cosines ? launch_k(k_forward<CONF, TL, TX, TY, true, true, false>, a, plan, st)
-                     : launch_k(k_forward<CONF, TL, TX, TY, false, true, false>, a, plan, st);
+    if constexpr (TL * TX * TY == 1)   // (time windows take one histogram per workgroup)
+        return a.cosines ? launch_k(k_forward<CONF, TL, TX, TY, true, true, false>, a, plan, st)
+                         : launch_k(k_forward<CONF, TL, TX, TY, false, true, false>, a, plan, st);
+    return hipErrorInvalidValue;
 }
 
 bool tile_supported(bool confocal, int tx, int ty, int tl)
@@ -1192,8 +1219,10 @@ static hipError_t launch_shape_batch(const BatchList& b, int64_t n_blocks, size_
         return cos ? launch_kb(k_forward_batch<CONF, TL, TX, TY, true, false, true>, b, n_blocks, lds, st)
                    : launch_kb(k_forward_batch<CONF, TL, TX, TY, false, false, true>, b, n_blocks, lds, st);
     }
-    return cos ? launch_kb(k_forward_batch<CONF, TL, TX, TY, true, true, false>, b, n_blocks, lds, st)
-               : launch_kb(k_forward_batch<CONF, TL, TX, TY, false, true, false>, b, n_blocks, lds, st);
+    if constexpr (TL * TX * TY == 1)
+        return cos ? launch_kb(k_forward_batch<CONF, TL, TX, TY, true, true, false>, b, n_blocks, lds, st)
+                   : launch_kb(k_forward_batch<CONF, TL, TX, TY, false, true, false>, b, n_blocks, lds, st);
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_forward_batch(const BatchList& b, int64_t n_blocks, size_t lds, int tl, int tx, int ty,

@@ -31,6 +31,7 @@ __host__ __device__ inline int flush_row_logical(int tl, int RM) { return (flush
 __host__ __device__ inline int flush_row_words(int tl, int RM) { return flush_row_logical(tl, RM) / 8 * 9; }
 
 constexpr int kBlock = 1024;           // threads per workgroup of the pair kernels
+constexpr int kHalfBlock = 512;        // threads of the pair kernel's half-size workgroups
 constexpr int kBlockPx = 16;           // record order: 16x16-pixel blocks, 4 stride-2 phases
 
 // Canonical cell-centred coordinate: fp32(a0 + (i + 0.5) * step), computed in
@@ -322,6 +323,7 @@ struct DebugArgs {
 struct Plan {
     int tx, ty, tl;        // unit: detector points along x, y; laser points
     int pair;              // two units per workgroup
+    int one;               // threads of a workgroup that owns one unit over the whole window; else 0
     int plan;              // torus-shift pairing of units
     int64_t groups;        // workgroups per (time window, patch split)
     int n_split;
