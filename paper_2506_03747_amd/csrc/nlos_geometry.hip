@@ -1,7 +1,8 @@
 // Depth map (+ albedo, + mask) -> patch records (Section 2 depth-to-volume
 // mapping; Algorithm 1 step 2.1), gfx950.
 //
-// Three launches, no host synchronisation:
+// One launch for small maps (k_geom_small); else up to three, no host
+// synchronisation:
 //   1. count:   present pixels per block of the record enumeration order;
 //   2. scan:    one workgroup turns the block counts into offsets and writes
 //               the number of present patches;
@@ -25,11 +26,11 @@ namespace nlos {
 __device__ __forceinline__ bool enum_pixel(const GeomArgs& a, int64_t e, int* ix, int* iy)
 {
     if (e >= a.n_enum) return false;
-    const int64_t chunk = e >> 6;
     const int w = (int)(e & 63);
-    const int phase = (int)(chunk & 3);
-    const int64_t blk = chunk >> 2;
-    const int bxi = (int)(blk / a.by), byi = (int)(blk % a.by);
+    const int phase = (int)(e >> 6) & 3;
+    // (at most 2^24 pixels make at most 2^20 blocks: a 32-bit division)
+    const uint32_t blk = (uint32_t)(e >> 8);
+    const int bxi = (int)(blk / (uint32_t)a.by), byi = (int)(blk - (uint32_t)bxi * (uint32_t)a.by);
     *ix = bxi * kBlockPx + (w >> 3) * 2 + (phase >> 1);
     *iy = byi * kBlockPx + (w & 7) * 2 + (phase & 1);
     return *ix < a.ax.n && *iy < a.ay.n;
@@ -121,6 +122,39 @@ __device__ __forceinline__ void scan_body(const GeomArgs& a)
 
 __global__ void __launch_bounds__(1024) k_geom_scan(const GeomArgs a) { scan_body(a); }
 
+// The record of present pixel (ix, iy) = map index idx from its depth, albedo
+// and neighbours' depths, written at record `off`; its first half.
+__device__ __forceinline__ float4 write_record(const GeomArgs& a, int ix, int iy, int64_t idx, int off, float z,
+                                               float rho, float zxp, float zxm, float zyp, float zym)
+{
+    // central differences inside, one-sided at the borders, 0 for a single
+    // sample
+    const float gx = a.ax.n < 2 ? 0.f
+                     : ix == 0 ? (zxp - z) / a.hx
+                     : ix == a.ax.n - 1 ? (z - zxm) / a.hx
+                     : (zxp - zxm) / (2.f * a.hx);
+    const float gy = a.ay.n < 2 ? 0.f
+                     : iy == 0 ? (zyp - z) / a.hy
+                     : iy == a.ay.n - 1 ? (z - zym) / a.hy
+                     : (zyp - zym) / (2.f * a.hy);
+    const float len = sqrtf(1.f + gx * gx + gy * gy);
+    const float area = a.hx * a.hy * (a.cosines ? len : 1.f);
+    const float4 A = make_float4(canon(a.ax, ix), canon(a.ay, iy), z, rho * area);
+    const float4 B = make_float4(gx / len, gy / len, -1.f / len, __int_as_float((int)idx));
+    a.patches[2 * (int64_t)off] = A;
+    a.patches[2 * (int64_t)off + 1] = B;
+    if (a.prep) {
+        // the constants the pair loop derives from this record, by the same
+        // function, so that it need not derive them per chunk; the coordinates
+        // stay unscaled (the loop scales them per chunk, and the fp64
+        // re-binning of guard-band pairs needs them as recorded)
+        const PatchC pc = patch_consts_scaled(A, B, a.cosines != 0, a.prep_sig);
+        a.prep[2 * (int64_t)off] = make_float4(A.x, A.y, A.z, pc.ap);
+        a.prep[2 * (int64_t)off + 1] = make_float4(pc.mnxs, pc.mnys, pc.c0s, 0.f);
+    }
+    return A;
+}
+
 // Records of one enumeration block at base + (rank among the present pixels
 // before it).  base is the exclusive prefix of the block counts: read from
 // `offsets`, or (offsets null) summed here from the counts.  With `stats`,
@@ -176,33 +210,7 @@ __device__ __forceinline__ void scatter_body(const GeomArgs& a, int blk)
     }
 
     float4 A = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (p) {
-        // central differences inside, one-sided at the borders, 0 for a
-        // single sample (the same operations as before the reads moved up)
-        const float gx = a.ax.n < 2 ? 0.f
-                         : ix == 0 ? (zxp - z) / a.hx
-                         : ix == a.ax.n - 1 ? (z - zxm) / a.hx
-                         : (zxp - zxm) / (2.f * a.hx);
-        const float gy = a.ay.n < 2 ? 0.f
-                         : iy == 0 ? (zyp - z) / a.hy
-                         : iy == a.ay.n - 1 ? (z - zym) / a.hy
-                         : (zyp - zym) / (2.f * a.hy);
-        const float len = sqrtf(1.f + gx * gx + gy * gy);
-        const float area = a.hx * a.hy * (a.cosines ? len : 1.f);
-        A = make_float4(canon(a.ax, ix), canon(a.ay, iy), z, rho * area);
-        const float4 B = make_float4(gx / len, gy / len, -1.f / len, __int_as_float((int)idx));
-        a.patches[2 * (int64_t)off] = A;
-        a.patches[2 * (int64_t)off + 1] = B;
-        if (a.prep) {
-            // the constants the pair loop derives from this record, by the
-            // same function, so that it need not derive them per chunk; the
-            // coordinates stay unscaled (the loop scales them per chunk, and
-            // the fp64 re-binning of guard-band pairs needs them as recorded)
-            const PatchC pc = patch_consts_scaled(A, B, a.cosines != 0, a.prep_sig);
-            a.prep[2 * (int64_t)off] = make_float4(A.x, A.y, A.z, pc.ap);
-            a.prep[2 * (int64_t)off + 1] = make_float4(pc.mnxs, pc.mnys, pc.c0s, 0.f);
-        }
-    }
+    if (p) A = write_record(a, ix, iy, idx, off, z, rho, zxp, zxm, zyp, zym);
     if (!a.stats) return;   // uniform across the block
 
     // Record summaries, one per kStatBlock consecutive records.  The block's
@@ -262,6 +270,104 @@ __device__ __forceinline__ void scatter_body(const GeomArgs& a, int blk)
 }
 
 __global__ void __launch_bounds__(kGeomBlock) k_geom_scatter(const GeomArgs a) { scatter_body(a, (int)blockIdx.x); }
+
+// The whole geometry of a small map (at most kSmallBlocks enumeration blocks)
+// in one launch: workgroup c makes records 256 c .. 256 c + 255 and their
+// summary.  Every workgroup finds the presence of all pixels by itself (9 bytes
+// each, from the L2), so that none waits for another and nothing has to be
+// cleared or counted by an earlier launch.  A thread looks at pixels
+// threadIdx.x + 1024 j of the enumeration.  Bound: latency -- the reads, two
+// barriers and the records' divisions.  Back to back: 24 x 31 pixels 5.9 -> 3.8
+// us and 64 x 64 the same 6.5 as two launches, one of which the host need not
+// make (2.2 us); at 100 x 90 the repeated reads cost more than the launch (10.3
+// against 6.0), so the line lies at 64 x 64.
+__global__ void __launch_bounds__(1024) k_geom_small(const GeomArgs a)
+{
+    constexpr int kWaves = 16, kRounds = kSmallBlocks * kGeomBlock / 1024, kCnt = kRounds * kWaves;
+    static_assert(kCnt == 64, "one wavefront scans the counts");
+    __shared__ int pre[kCnt + 1];
+    __shared__ int part[kWaves][7];
+    const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+    // every round's reads in flight together (past the enumeration they read
+    // map index 0 and use nothing)
+    Samples smp[kRounds];
+    int ix[kRounds], iy[kRounds];
+    bool p[kRounds];
+#pragma unroll
+    for (int j = 0; j < kRounds; ++j) {
+        ix[j] = iy[j] = 0;
+        p[j] = enum_pixel(a, (int64_t)j * 1024 + threadIdx.x, &ix[j], &iy[j]);
+        smp[j] = read_samples(a, p[j] ? (int64_t)ix[j] * a.ay.n + iy[j] : 0);
+    }
+#pragma unroll
+    for (int j = 0; j < kRounds; ++j) asm volatile("" ::"v"(smp[j].z), "v"(smp[j].rho), "v"((int)smp[j].m));
+#pragma unroll
+    for (int j = 0; j < kRounds; ++j) {
+        p[j] = p[j] && is_present(smp[j]);
+        const unsigned long long bal = __ballot(p[j]);
+        if (lane == 0) pre[j * kWaves + wave] = (int)__popcll(bal);
+    }
+    __syncthreads();
+    if (wave == 0) {
+        // exclusive prefix of the counts, in enumeration order
+        const int v = pre[lane];
+        int x = v;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int y = __shfl_up(x, d);
+            x += lane >= d ? y : 0;
+        }
+        pre[lane] = x - v;
+        if (lane == 63) pre[kCnt] = x;
+    }
+    __syncthreads();
+    const int total = pre[kCnt], first = (int)blockIdx.x * kStatBlock;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *a.n_active = total;
+    int v[7] = {INT32_MAX, INT32_MIN, INT32_MAX, INT32_MIN, INT32_MAX, INT32_MIN, 0};
+#pragma unroll
+    for (int j = 0; j < kRounds; ++j) {
+        const int base = pre[j * kWaves + wave], end = pre[j * kWaves + wave + 1];
+        if (end <= first || base >= first + kStatBlock) continue;   // uniform: none of this workgroup's
+        const unsigned long long bal = __ballot(p[j]);
+        const int off = base + (int)__popcll(bal & ((1ull << lane) - 1ull));
+        if (!p[j] || off < first || off >= first + kStatBlock) continue;
+        const int64_t idx = (int64_t)ix[j] * a.ay.n + iy[j];
+        const float* D = a.depth + idx;
+        const float zxp = D[ix[j] + 1 < a.ax.n ? (int64_t)a.ay.n : 0], zxm = D[ix[j] > 0 ? -(int64_t)a.ay.n : 0];
+        const float zyp = D[iy[j] + 1 < a.ay.n ? 1 : 0], zym = D[iy[j] > 0 ? -1 : 0];
+        const float4 A = write_record(a, ix[j], iy[j], idx, off, smp[j].z, smp[j].rho, zxp, zxm, zyp, zym);
+        v[0] = min(v[0], ord_f(A.x));
+        v[1] = max(v[1], ord_f(A.x));
+        v[2] = min(v[2], ord_f(A.y));
+        v[3] = max(v[3], ord_f(A.y));
+        v[4] = min(v[4], ord_f(A.z));
+        v[5] = max(v[5], ord_f(A.w));
+        ++v[6];
+    }
+    if (!a.stats || (int)blockIdx.x >= a.n_stats) return;   // uniform
+    const int w[7] = {wave_reduce_i<0>(v[0]), wave_reduce_i<1>(v[1]), wave_reduce_i<0>(v[2]), wave_reduce_i<1>(v[3]),
+                      wave_reduce_i<0>(v[4]), wave_reduce_i<1>(v[5]), wave_reduce_i<2>(v[6])};
+    if (lane < 7) {
+        int x = w[0];
+#pragma unroll
+        for (int f = 1; f < 7; ++f) x = lane == f ? w[f] : x;
+        part[wave][lane] = x;
+    }
+    __syncthreads();
+    if (threadIdx.x < 8) {
+        // x0, x1, y0, y1, z0, amax, count, pad
+        const int f = (int)threadIdx.x;
+        int x = f < 7 ? part[0][f] : 0;
+        if (f < 7) {
+#pragma unroll
+            for (int q = 1; q < kWaves; ++q) {
+                const int y = part[q][f];
+                x = f == 6 ? x + y : ((f & 1) ? max(x, y) : min(x, y));
+            }
+        }
+        reinterpret_cast<int32_t*>(a.stats + blockIdx.x)[f] = x;
+    }
+}
 
 // Batched geometry: the enumeration blocks of all depth maps in one launch
 // per phase (count, scan with one workgroup per map, scatter).
@@ -356,11 +462,16 @@ hipError_t launch_tick_geometry(const TickList* list, int grid, hipStream_t st)
     return hipGetLastError();
 }
 
-// Two launches (count, scatter) when the scatter can sum the counts itself
-// (a.offsets null), three (count, scan, scatter) otherwise.
+// One launch for small maps, two (count, scatter) when the scatter can sum the
+// counts itself (a.offsets null), three (count, scan, scatter) otherwise.
 hipError_t launch_geometry(const GeomArgs& a, hipStream_t st)
 {
     if (a.n_blocks <= 0) return hipErrorInvalidValue;
+    if (a.n_blocks <= kSmallBlocks) {
+        const int64_t n = (int64_t)a.ax.n * a.ay.n;   // most records
+        hipLaunchKernelGGL(k_geom_small, dim3((unsigned)((n + kStatBlock - 1) / kStatBlock)), dim3(1024), 0, st, a);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_geom_count, dim3(a.n_blocks), dim3(kGeomBlock), 0, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -66,6 +66,7 @@ struct GeomArgs {
     float prep_sig;        // the pair loop's bins per metre (its scale of coordinates)
 };
 constexpr int kGeomBlock = 256;
+constexpr int kSmallBlocks = 16;   // up to this many blocks, one launch does the whole geometry
 
 // Summary of kStatBlock consecutive patch records: lateral bounding box,
 // smallest depth, largest a, record count.  Used to bound the pair weights
