@@ -71,7 +71,7 @@ def _dev(t: Optional[torch.Tensor], dtype, name: str):
         return None
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a GPU torch tensor (no CPU fallback)")
-    if t.dtype != dtype:
+    if t.dtype is not dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
@@ -79,12 +79,14 @@ def _dev(t: Optional[torch.Tensor], dtype, name: str):
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(stream) -> C.c_void_p:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+def _stream(stream) -> int:
+    if stream is None:
+        # the current stream's handle without a Stream object (0.3 us, not 2.8)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def patches_from_depth(depth: torch.Tensor, grid, albedo: Optional[torch.Tensor] = None,
