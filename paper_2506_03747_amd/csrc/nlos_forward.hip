@@ -145,9 +145,7 @@ __device__ __forceinline__ void block_max(float* v, float* red)
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < N; ++k) {
-        float m = 0.f;
-        for (int w = 0; w < BLK / 64; ++w) m = fmaxf(m, red[w * N + k]);
-        v[k] = m;
+        v[k] = wave_max_f(red[((int)threadIdx.x & (BLK / 64 - 1)) * N + k]);
     }
 }
 
@@ -304,8 +302,19 @@ __device__ __forceinline__ float approx_coord(const Axis& ax, int i)
 constexpr int kScaleBlockConf = 4;      // scan points per side of a confocal scale block
 constexpr int kScaleBlockNonconf = 2;   // detectors per side and lasers of a non-confocal one
 
+// A unit by its tile coordinates: laser tile, column tile, row tile (ul < 0:
+// no unit).  The workgroup's number is taken apart once, in pick_units: a
+// division by a number known only at run time is some twenty instructions in a
+// chain, and the set-up is a chain of latencies (with the rows' table moved to
+// the last wavefront and the bound's last step made a reduction: 8 x 8 lasers
+// over 128^2 detectors 7.58 -> 7.38 ms, 3 x 2 over 33 x 29 32.2 -> 30.9 us, a
+// frame of 64^2 points 59.6 -> 58.9).
+struct Unit {
+    int ul, ux, uy;
+};
+
 template <bool CONF, int TL, int TX, int TY>
-__device__ __forceinline__ UnitRect unit_rect(const FwdArgs& a, int u)
+__device__ __forceinline__ UnitRect unit_rect(const FwdArgs& a, const Unit& u)
 {
     static_assert(CONF ? (kScaleBlockConf % TX == 0 && kScaleBlockConf % TY == 0)
                        : (kScaleBlockNonconf % TX == 0 && kScaleBlockNonconf % TY == 0 &&
@@ -313,11 +322,8 @@ __device__ __forceinline__ UnitRect unit_rect(const FwdArgs& a, int u)
                   "units tile the scale blocks");
     constexpr int B = CONF ? kScaleBlockConf : kScaleBlockNonconf;
     UnitRect R;
-    const int uy = u % a.tiles_y;
-    const int ux = (u / a.tiles_y) % a.tiles_x;
-    const int ul = u / (a.tiles_y * a.tiles_x);
-    const int ix0 = (ux * TX) / B * B, ix1 = min(ix0 + B, a.rx.n) - 1;
-    const int iy0 = (uy * TY) / B * B, iy1 = min(iy0 + B, a.ry.n) - 1;
+    const int ix0 = (u.ux * TX) / B * B, ix1 = min(ix0 + B, a.rx.n) - 1;
+    const int iy0 = (u.uy * TY) / B * B, iy1 = min(iy0 + B, a.ry.n) - 1;
     R.dx0 = approx_coord(a.rx, ix0);
     R.dx1 = approx_coord(a.rx, ix1);
     R.dy0 = approx_coord(a.ry, iy0);
@@ -329,11 +335,16 @@ __device__ __forceinline__ UnitRect unit_rect(const FwdArgs& a, int u)
         R.ly1 = R.dy1;
     } else {
         const int n_laser = a.lx.n * a.ly.n;
-        const int l0 = (ul * TL) / B * B;
+        const int l0 = (u.ul * TL) / B * B;
         R.lx0 = R.ly0 = 3.0e38f;
         R.lx1 = R.ly1 = -3.0e38f;
+        int lxi = l0 / a.ly.n, lyi = l0 - lxi * a.ly.n;
         for (int l = l0; l < min(l0 + B, n_laser); ++l) {
-            const float x = approx_coord(a.lx, l / a.ly.n), y = approx_coord(a.ly, l % a.ly.n);
+            const float x = approx_coord(a.lx, lxi), y = approx_coord(a.ly, lyi);
+            if (++lyi == a.ly.n) {
+                lyi = 0;
+                ++lxi;
+            }
             R.lx0 = fminf(R.lx0, x);
             R.lx1 = fmaxf(R.lx1, x);
             R.ly0 = fminf(R.ly0, y);
@@ -347,7 +358,7 @@ __device__ __forceinline__ UnitRect unit_rect(const FwdArgs& a, int u)
 // a_max / (r_l,min^2 r_d,min^2) over the record summaries (cosine factors
 // are at most 1).
 template <bool CONF, int TL, int TX, int TY>
-__device__ __forceinline__ float unit_weight_bound(const FwdArgs& a, int u, const StatF& c)
+__device__ __forceinline__ float unit_weight_bound(const FwdArgs& a, const Unit& u, const StatF& c)
 {
     const UnitRect R = unit_rect<CONF, TL, TX, TY>(a, u);
     if (c.count <= 0) return 0.f;
@@ -357,49 +368,54 @@ __device__ __forceinline__ float unit_weight_bound(const FwdArgs& a, int u, cons
     return c.amax / (rl2 * rd2);
 }
 
-// Units of this workgroup: u[0] and, when paired, u[1] (-1 if none).
+// Units of this workgroup: u[0] and, when paired, u[1] (ul = -1 if none).
 // Paired units are the unit (x, y) of a laser tile and the unit shifted by
 // half the unit grid in both directions (torus shift): a unit near the middle
 // of the wall -- where most pairs land in the window -- goes with one near the
 // border.  Groups enumerate the half of the grid the shift maps onto the
 // other half; grids with both sides odd pair g with n-1-g in unit order.
 template <bool PAIR>
-__device__ __forceinline__ void pick_units(const FwdArgs& a, int grp, int* u)
+__device__ __forceinline__ void pick_units(const FwdArgs& a, int grp, Unit* u)
 {
     if (!PAIR) {
         // from the middle of the wall outwards in x, then y (laser tiles
         // outermost): most pairs reach the window there, so that the workgroups
         // with the least work start last
         const int tx = a.tiles_x, ty = a.tiles_y;
-        const int ky = grp % ty, kx = (grp / ty) % tx, ul = grp / (ty * tx);
+        const int col = grp / ty, ky = grp - col * ty;
+        const int ul = col / tx, kx = col - ul * tx;
         const int ux = (tx - 1) / 2 + ((kx & 1) ? (kx + 1) / 2 : -(kx / 2));
         const int uy = (ty - 1) / 2 + ((ky & 1) ? (ky + 1) / 2 : -(ky / 2));
-        u[0] = (ul * tx + ux) * ty + uy;
+        u[0] = Unit{ul, ux, uy};
         return;
     }
     const int tx = a.tiles_x, ty = a.tiles_y, plane = tx * ty;
     if (a.plan) {
         const int half = plane / 2;
-        const int ul = grp / half, h = grp % half;
+        const int ul = grp / half, h = grp - ul * half;
         int ux, uy, vx, vy;
         if ((ty & 1) == 0) {
             ux = h / (ty / 2);
-            uy = h % (ty / 2);
-            vx = (ux + tx / 2) % tx;
+            uy = h - ux * (ty / 2);
+            vx = ux + tx / 2;
+            if (vx >= tx) vx -= tx;
             vy = uy + ty / 2;
         } else {
-            ux = h % (tx / 2);
             uy = h / (tx / 2);
+            ux = h - uy * (tx / 2);
             vx = ux + tx / 2;
-            vy = (uy + ty / 2) % ty;
+            vy = uy + ty / 2;
+            if (vy >= ty) vy -= ty;
         }
-        u[0] = ul * plane + ux * ty + uy;
-        u[1] = ul * plane + vx * ty + vy;
+        u[0] = Unit{ul, ux, uy};
+        u[1] = Unit{ul, vx, vy};
         return;
     }
-    const int partner = a.n_units - 1 - grp;
-    u[0] = grp;
-    u[1] = partner != grp ? partner : -1;
+    // (unit n - 1 - g is unit g seen from the other end of every axis)
+    const int col = grp / ty, uy = grp - col * ty;
+    const int ul = col / tx, ux = col - ul * tx;
+    u[0] = Unit{ul, ux, uy};
+    u[1] = Unit{a.n_units - 1 - grp != grp ? a.tiles_l - 1 - ul : -1, tx - 1 - ux, ty - 1 - uy};
 }
 
 // floor(d / 8) for any sign, at compile time where d is a constant
@@ -643,36 +659,46 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int block_id)
         st0b = *(const __attribute__((address_space(1))) v3i*)(g + 2 * (size_t)threadIdx.x + 1);
     }
 
-    int id = block_id;
-    const int split = id % a.n_split;
-    id /= a.n_split;
-    const int twi = id % a.n_tw;
-    const int grp = id / a.n_tw;
+    // (most launches split neither the records nor the bins: no division)
+    int grp = block_id, split = 0, twi = 0;
+    if (a.n_split > 1) {
+        grp = block_id / a.n_split;
+        split = block_id - grp * a.n_split;
+    }
+    if (a.n_tw > 1) {
+        const int id = grp;
+        grp = id / a.n_tw;
+        twi = id - grp * a.n_tw;
+    }
     const int t0w = twi * a.tw, t1w = min(a.T, t0w + a.tw);
     const int hbw = max(0, t0w - a.R), hew = min(a.T, t1w + a.R);
     const int hb = WIN ? hbw : 0, Tl = WIN ? hew - hbw : a.T;
-    const int chunk = (n_act + a.n_split - 1) / a.n_split;
+    const int chunk = a.n_split > 1 ? (n_act + a.n_split - 1) / a.n_split : n_act;
     const int pb = min(n_act, split * chunk), pe = min(n_act, pb + chunk);
     const int n_laser = a.lx.n * a.ly.n;
 
-    int unit[NU];
+    Unit unit[NU];
     pick_units<PAIR>(a, grp, unit);
     bool uvalid[NU];
 #pragma unroll
-    for (int k = 0; k < NU; ++k) uvalid[k] = unit[k] >= 0;
+    for (int k = 0; k < NU; ++k) uvalid[k] = unit[k].ul >= 0;
     int unit_on[NU];   // the same, made scalar for the pair loop's per-chunk test
 #pragma unroll
-    for (int k = 0; k < NU; ++k) unit_on[k] = __builtin_amdgcn_readfirstlane(unit[k] >= 0 ? 1 : 0);
+    for (int k = 0; k < NU; ++k) unit_on[k] = __builtin_amdgcn_readfirstlane(unit[k].ul >= 0 ? 1 : 0);
 
     for (int i = threadIdx.x; i < NS * a.stride / 2; i += BLK) reinterpret_cast<uint4*>(L.hist)[i] = uint4{0, 0, 0, 0};
     if (threadIdx.x == 0) *L.next = 2u * (BLK / 64);
-    if (threadIdx.x < NS) {
-        const int j = threadIdx.x;
+    // the rows' table by the last wavefront: the first ones have the summaries'
+    // bound to find, and the fp64 legs are a chain as long as that one
+    if (threadIdx.x >= BLK - 64 && threadIdx.x < BLK - 64 + NS) {
+        const int j = (int)threadIdx.x - (BLK - 64);
         const int k = j / NH, jl = j % NH;
         // (NU <= 2: selects, so that the small arrays stay in registers)
         const bool kv = k == 0 ? uvalid[0] : uvalid[NU - 1];
-        const int u = kv ? (k == 0 ? unit[0] : unit[NU - 1]) : unit[0];
-        const int uy = u % a.tiles_y, ux = (u / a.tiles_y) % a.tiles_x, ul = u / (a.tiles_y * a.tiles_x);
+        const bool first = k == 0 || !kv;
+        const int ul = first ? unit[0].ul : unit[NU - 1].ul;
+        const int ux = first ? unit[0].ux : unit[NU - 1].ux;
+        const int uy = first ? unit[0].uy : unit[NU - 1].uy;
         const int dj = jl % ND;
         const int ix_u = ux * TX + dj / TY, iy_u = uy * TY + dj % TY, l_u = ul * TL + jl / ND;
         L.row[j] = (kv && ix_u < a.rx.n && iy_u < a.ry.n && l_u < (CONF ? 1 : n_laser))
@@ -694,7 +720,8 @@ __device__ __forceinline__ void forward_body(const FwdArgs& a, int block_id)
             L.gg[j] = (float)(g_d * g_d);
         } else {
             const int l = min(ul * TL + jl / ND, n_laser - 1);
-            const float lx = canon(a.lx, l / a.ly.n), ly = canon(a.ly, l % a.ly.n);
+            const int lxi = l / a.ly.n;
+            const float lx = canon(a.lx, lxi), ly = canon(a.ly, l - lxi * a.ly.n);
             double off_l, g_l;
             device_leg(lx, ly, a.cx, a.cy, a.s, &off_l, &g_l);
             L.so[j] = off_l + off_d;
