@@ -718,9 +718,12 @@ __global__ void __launch_bounds__(kBlock) k_adjoint(const SmoothArgs a)
 // every odd row.  The kernels are scalar reads (written by an earlier launch).
 // The 4 NS values of a thread go through LDS (its own wavefront's piece), so
 // that the stores are contiguous over the wavefront.  ALIGNED: T a multiple of
-// 4 and the gradient 16-byte aligned; else single reads.
+// 4 and the gradient 16-byte aligned; else the same 16-byte reads at addresses
+// that are multiples of 4, and single ones at the ends of a row (all reads
+// single: 48 x 40 points, 1501 bins, radius 31, 55 us; so, 38).
 // Bound: HBM, NS words written per bin and point (128^2 points, 1056 bins of 7
-// words: 484 MB in 107 us).
+// words: 484 MB in 107 us), and past a radius of about 24 the 8 to 11
+// operations per tap and bin.
 template <int NM, bool ALIGNED>
 __global__ void __launch_bounds__(256) k_adj_moments(const SmoothArgs a)
 {
@@ -734,10 +737,25 @@ __global__ void __launch_bounds__(256) k_adj_moments(const SmoothArgs a)
         const int s = (int)(t / Q), k0 = (int)(t % Q) * V - H;
         const float* g = a.grad_out + (size_t)s * T;
         const auto read4 = [&](int k) {
-            if constexpr (ALIGNED)   // wholly inside the row or wholly in the padding
+            if constexpr (ALIGNED) {   // wholly inside the row or wholly in the padding
                 return (k >= 0 && k < T) ? *reinterpret_cast<const float4*>(g + k) : make_float4(0.f, 0.f, 0.f, 0.f);
-            const auto one = [&](int i) { return (i >= 0 && i < T) ? g[i] : 0.f; };
-            return make_float4(one(k), one(k + 1), one(k + 2), one(k + 3));
+            } else {
+                // one 16-byte read at the nearest four bins of the row that
+                // exist; the lanes at its ends read theirs singly instead
+                struct __attribute__((packed, aligned(4))) Four {
+                    float x, y, z, w;
+                };
+                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (T >= 4) {
+                    const Four f = *reinterpret_cast<const Four*>(g + min(max(k, 0), T - 4));
+                    v = make_float4(f.x, f.y, f.z, f.w);
+                }
+                if (k < 0 || k + 4 > T) {
+                    const auto one = [&](int i) { return (i >= 0 && i < T) ? g[i] : 0.f; };
+                    v = make_float4(one(k), one(k + 1), one(k + 2), one(k + 3));
+                }
+                return v;
+            }
         };
         kconst kc = (kconst)a.mtaps;
         const int np = taps_adj(a.Rs);
