@@ -376,9 +376,8 @@ __device__ __forceinline__ float cull_r2(const SmoothArgs& a, double o)
 // bins, 10.9 on random ones and 8.6 more per lane that shares a bin; here 13
 // on average, NM of them per pair -- with VALU (about 50 instructions per pair
 // that reaches the window) close behind.  128^2 points and patches, 1024 bins:
-// radius 16 (NM = 6) 0.80 -> 0.66 ms, radius 12 (8 -> 7 terms) 1.32 -> 0.97;
-// 48 x 40 points, 3840 patches, 1501 bins, radius 31: 185 us by taps, 87 by
-// moments.
+// radius 16 (NM = 6) 0.80 -> 0.65 ms; 48 x 40 points, 3840 patches, 1501 bins,
+// radius 31: 185 us by taps, 69 by moments.
 template <bool COS, int NM, int NP, int WG>
 __global__ void __launch_bounds__(kBlock, 4 * WG) k_smooth_mom(const SmoothArgs a)
 {
@@ -505,24 +504,26 @@ __global__ void __launch_bounds__(kBlock, 4 * WG) k_smooth_mom(const SmoothArgs 
     // multiples of four floats), taps as scalars.  The sums run over m downwards,
     // then e; the largest row's, last, four taps at a time, so that few additions
     // round at the size of the result.
+    // Rows with fewer groups of bins than threads leave wavefronts over: the taps
+    // are then dealt to up to four sets of wavefronts, whose sums meet in LDS
+    // (the rows are no longer read) and are added in the order of the taps (four
+    // to six of sixteen wavefronts at work: the two cases above 0.69 ms and 84 us).
     const float inv_sc = 1.0f / s;
     constexpr int V = 4;
-    const int nseg = (T + V - 1) / V, npp = taps_fwd(Rs);
+    const int nseg = (T + V - 1) / V, npp = taps_fwd(Rs), n_out = NP * nseg;
     kconst kt = (kconst)a.mtaps;
     const bool vec_out = !a.atomic_out && (T & 3) == 0 && ((uintptr_t)a.out & 15) == 0;
-    for (int o = threadIdx.x; o < NP * nseg; o += kBlock) {
-        const int c = o / nseg, k0 = (o - c * nseg) * V;
-        if (tx0 + c >= a.rx.n) continue;
-        float acc[V];
+    // taps e0 .. e1 - 1 of output group o (multiples of four)
+    const auto convolve = [&](int c, int k0, int e0, int e1, float (&acc)[V]) {
 #pragma unroll
         for (int v = 0; v < V; ++v) acc[v] = 0.f;
 #pragma unroll
         for (int m = NM - 1; m >= 0; --m) {
             const float4* f4 = reinterpret_cast<const float4*>(F + (size_t)(c * NM + m) * 2 * PITCH + k0);
             kconst tm = kt + m * npp;
-            float4 lo = f4[0];
+            float4 lo = f4[e0 / 4];
 #pragma unroll 4
-            for (int e = 0; e < npp; e += 4) {
+            for (int e = e0; e < e1; e += 4) {
                 const float4 hi = f4[e / 4 + 1];
                 const float w[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
                 float part[V];
@@ -544,10 +545,12 @@ __global__ void __launch_bounds__(kBlock, 4 * WG) k_smooth_mom(const SmoothArgs 
                 lo = hi;
             }
         }
+    };
+    const auto store = [&](int c, int k0, const float (&acc)[V]) {
         float* dst = a.out + ((size_t)(tx0 + c) * a.ry.n + ty0) * (size_t)T + k0;
         if (vec_out && k0 + V <= T) {
             *reinterpret_cast<float4*>(dst) = make_float4(acc[0] * inv_sc, acc[1] * inv_sc, acc[2] * inv_sc, acc[3] * inv_sc);
-            continue;
+            return;
         }
 #pragma unroll
         for (int v = 0; v < V; ++v) {
@@ -557,7 +560,38 @@ __global__ void __launch_bounds__(kBlock, 4 * WG) k_smooth_mom(const SmoothArgs 
             else
                 dst[v] = acc[v] * inv_sc;
         }
+    };
+    float acc[V];
+    const int span = (n_out + 63) / 64;                       // wavefronts per set
+    const int sets = min(4, (kBlock / 64) / span);            // (0: more groups than threads)
+    if (sets <= 1) {
+        for (int o = threadIdx.x; o < n_out; o += kBlock) {
+            const int c = o / nseg, k0 = (o - c * nseg) * V;
+            if (tx0 + c >= a.rx.n) continue;
+            convolve(c, k0, 0, npp, acc);
+            store(c, k0, acc);
+        }
+        return;
     }
+    const int set = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6) / span);
+    const int o = (int)threadIdx.x - set * span * 64;
+    const int c = o / nseg, k0 = (o - c * nseg) * V;
+    const bool on = set < sets && o < n_out && tx0 + c < a.rx.n;
+    const int per = (npp / 4 + sets - 1) / sets * 4;
+    if (on) convolve(c, k0, min(npp, set * per), min(npp, (set + 1) * per), acc);
+    __syncthreads();
+    float4* part = reinterpret_cast<float4*>(smem);           // [sets - 1][n_out]
+    if (on && set > 0) part[(set - 1) * n_out + o] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+    __syncthreads();
+    if (!on || set > 0) return;
+    for (int i = 0; i + 1 < sets; ++i) {
+        const float4 q = part[i * n_out + o];
+        acc[0] += q.x;
+        acc[1] += q.y;
+        acc[2] += q.z;
+        acc[3] += q.w;
+    }
+    store(c, k0, acc);
 }
 
 // ---------------------------------------------------------------------------
