@@ -5,13 +5,13 @@
 // into the scan point's time histogram and then blur each histogram with the
 // Gaussian jitter of Section 2 (Algorithm 1, step 2.3) while writing it out.
 //
-// Work decomposition (one workgroup = 16 waves = 1024 lanes):
+// Work decomposition (one workgroup = 16 waves = 1024 lanes, or 8 waves where
+// two workgroups per CU are estimated to be faster):
 //   * histograms are grouped in units -- TX x TY detector points (times TL
-//     laser points, non-confocal); a workgroup owns one unit, or two when
-//     units are few: then every workgroup estimates the work of all units from
-//     summaries of the records, sorts the estimates in LDS and takes the k-th
-//     lightest with the k-th heaviest unit, which evens out the load when a
-//     workgroup per CU is all there is;
+//     laser points, non-confocal); a workgroup owns one unit, or two half the
+//     unit grid apart, so that a unit near the middle of the wall goes with one
+//     near the border: the host picks unit shape, pairing and workgroup size by
+//     an estimate of the time;
 //   * the histograms live in LDS for the whole pass, over one window of
 //     output bins;
 //   * each lane owns one patch at a time (coalesced 32-byte record loads; the
@@ -22,8 +22,8 @@
 //     arrivals lies past the window;
 //   * a pair is evaluated in fp32 (one v_rsq_f32 per leg); pairs whose fp32
 //     arrival lies within the guard band of a bin edge go to an LDS queue and
-//     are re-binned in fp64 before the flush (queue overflow re-bins in
-//     place), so every bin equals the fp64 one;
+//     are re-binned in fp64 before the flush (a queue that fills up is worked
+//     off in the loop), so every bin equals the fp64 one;
 //   * histograms accumulate in 64-bit fixed point with LDS integer atomics
 //     (ds_add_u64): a pair adds round(w * s) as a 32-bit increment, with
 //     s = 2^31 / W and W >= every weight the workgroup's units can see
@@ -133,7 +133,10 @@ __device__ __forceinline__ float rect_rect_d2(float ax0, float ax1, float ay0, f
 }
 
 // Block-wide maxima of N non-negative floats, in place (DPP within each
-// wavefront, then LDS; `red` holds N floats per wavefront).
+// wavefront, then LDS; `red` holds N floats per wavefront).  One value ends
+// in a second reduction over lanes (8 x 8 lasers 7.38 -> 7.28 ms); with two, the
+// scalars it takes are missed by the kernel of all paired variants (a serving
+// tick of 6 requests 206.5 -> 212.7 us), so every lane reads them all.
 template <int N, int BLK>
 __device__ __forceinline__ void block_max(float* v, float* red)
 {
@@ -143,9 +146,15 @@ __device__ __forceinline__ void block_max(float* v, float* red)
         if ((threadIdx.x & 63) == 0) red[(threadIdx.x >> 6) * N + k] = v[k];
     }
     __syncthreads();
+    if constexpr (N == 1) {
+        v[0] = wave_max_f(red[(int)threadIdx.x & (BLK / 64 - 1)]);
+    } else {
 #pragma unroll
-    for (int k = 0; k < N; ++k) {
-        v[k] = wave_max_f(red[((int)threadIdx.x & (BLK / 64 - 1)) * N + k]);
+        for (int k = 0; k < N; ++k) {
+            float m = 0.f;
+            for (int w = 0; w < BLK / 64; ++w) m = fmaxf(m, red[w * N + k]);
+            v[k] = m;
+        }
     }
 }
 
@@ -306,7 +315,7 @@ constexpr int kScaleBlockNonconf = 2;   // detectors per side and lasers of a no
 // no unit).  The workgroup's number is taken apart once, in pick_units: a
 // division by a number known only at run time is some twenty instructions in a
 // chain, and the set-up is a chain of latencies (with the rows' table moved to
-// the last wavefront and the bound's last step made a reduction: 8 x 8 lasers
+// the last wavefront and a single unit's bound made a reduction: 8 x 8 lasers
 // over 128^2 detectors 7.58 -> 7.38 ms, 3 x 2 over 33 x 29 32.2 -> 30.9 us, a
 // frame of 64^2 points 59.6 -> 58.9).
 struct Unit {
