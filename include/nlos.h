@@ -501,7 +501,9 @@ int nlos_lct_forward(const nlos_params* p, const float* depth, const float* albe
  * plan with the least estimated time (one or two units per workgroup, one or
  * two workgroups per CU); in a list of requests (batched calls, ticks) the
  * largest unit of which two fit and that still gives each request its share
- * of workgroups.  The table is the library's only shared state: it is
+ * of workgroups, or the least estimate where none does or the request is the
+ * list's only one; a list splits a request's patches over workgroups (whose
+ * parts meet in float atomics) only where the call alone does.  The table is the library's only shared state: it is
  * copied, read under a lock, and replaced as a whole.
  */
 typedef struct nlos_tuning_entry {

@@ -160,9 +160,10 @@ int64_t stats_count(int32_t n_patches) { return ((int64_t)n_patches + nlos::kSta
 // largest first).  A call alone whose two smallest units fit in LDS over the
 // whole window takes the plan with the least estimated time (plan_solo).  In a
 // list of requests, or with a unit named by the tuning table, a workgroup owns
-// two units (of the named shape, or the largest that still gives at least the
-// target of workgroups), and patches are split over workgroups when there are
-// fewer.  Longer histograms: one per workgroup over a window of bins.
+// two units: of the named shape, patches split over workgroups when they are
+// fewer than the target; else of the largest shape that gives the target of
+// workgroups, or what plan_share estimates where none does.  Longer histograms:
+// one per workgroup over a window of bins.
 // Tuning table (nlos_set_tuning): the unit shape to use per (geometry,
 // window length, histogram count) class, found by measurement.  Read under a
 // lock by every plan; replaced as a whole.
@@ -185,19 +186,20 @@ bool tuned_unit(bool conf, int32_t T, int64_t H, Cand* c)
 constexpr Cand conf_c[] = {{1, 4, 4}, {1, 4, 2}, {1, 2, 2}, {1, 2, 1}, {1, 1, 1}};
 constexpr Cand nc_c[] = {{2, 2, 2}, {2, 1, 2}, {1, 1, 2}, {1, 1, 1}};
 
-// Estimated time, in instruction cycles of a CU, of a call that runs alone with
-// units of shape c: `nu` units per workgroup (two, or one), `half` workgroups of
-// kHalfBlock threads two to a CU, the patches split over `split` workgroups.
-// A workgroup evaluates every 64-record chunk against its units, 16 (8)
-// wavefronts on four SIMDs, then writes its rows out; 256 (512) run at a time,
-// and the last round is rarely full.  Constants: instructions per chunk, unit
+// Estimated time, in instruction cycles of a CU, of a call that has `cus` CUs
+// (all of them: it runs alone) with units of shape c: `nu` units per workgroup
+// (two, or one), `half` workgroups of kHalfBlock threads two to a CU, the
+// patches split over `split` workgroups.  A workgroup evaluates every 64-record
+// chunk against its units, 16 (8) wavefronts on four SIMDs, then writes its rows
+// out; `cus` (twice as many) run at a time, and the last round is rarely full.  Constants: instructions per chunk, unit
 // and pair and the fixed part of a workgroup, fitted to the times of every
 // feasible plan of 144 random problems (6 x 6 to 128 x 128 points, 256 to 1.6e5
 // pixels, 256 to 2048 bins, confocal and not): the plan with the least estimate
 // took 1.025 times the best plan's time in the geometric mean, the rule before
 // (the largest paired unit that gives a workgroup per CU, else split patches)
 // 1.79 times.  Float atomics of split patches: 55 G/s measured.
-double plan_cost(const nlos_params* p, double n, const Cand& c, int nu, bool half, int64_t units, int64_t split)
+double plan_cost(const nlos_params* p, double n, const Cand& c, int nu, bool half, int64_t units, int64_t split,
+                 int64_t cus)
 {
     const bool conf = is_confocal(p);
     const double nh = (double)c.tl * c.tx * c.ty, T = p->n_bins;
@@ -213,16 +215,16 @@ double plan_cost(const nlos_params* p, double n, const Cand& c, int nu, bool hal
     double t;
     if (!half) {
         const double w = std::max(chunks * per, std::ceil(chunks / 16.0) * per * 5.1) + flush + 11700.0;
-        const double x = (double)wg / kTargetBlocks;
+        const double x = (double)wg / (double)cus;
         // (a unit near the border has fewer pairs in the window: two by a torus
         // shift even that out)
         t = w * (nu == 2 ? 1.0 : 1.1) * (x <= 1.0 ? 1.0 : rounds(x));
-    } else if (wg <= kTargetBlocks) {
+    } else if (wg <= cus) {
         const double w = std::max(chunks * per, std::ceil(chunks / 8.0) * per * 5.1);
         t = (w * 1.38 + flush + 10700.0) * 1.1;
     } else {
         const double w = std::max(2.0 * chunks * per, std::ceil(chunks / 8.0) * per * 5.1) + 1.36 * flush + 10700.0;
-        const double x = (double)wg / (2 * kTargetBlocks);
+        const double x = (double)wg / (double)(2 * cus);
         t = w * (x <= 1.0 ? 1.1 : rounds(x));
     }
     if (split > 1) t += 10000.0 + (double)n_hist(p) * T * (double)split * 0.044;
@@ -252,7 +254,7 @@ int plan_solo(const nlos_params* p, int32_t n_patches, int stride, nlos::Plan* p
             const int64_t most = std::max<int64_t>(
                 1, std::min<int64_t>(kTargetBlocks / std::max<int64_t>(1, groups), n_patches / nlos::kBlock));
             for (int64_t split = 1; split <= most; split += std::max<int64_t>(1, most - 1)) {   // 1 and the most
-                const double t = plan_cost(p, n, c, nu, kind == 2, units, split);
+                const double t = plan_cost(p, n, c, nu, kind == 2, units, split, kTargetBlocks);
                 if (any && t >= best) continue;
                 any = true;
                 best = t;
@@ -273,6 +275,44 @@ int plan_solo(const nlos_params* p, int32_t n_patches, int stride, nlos::Plan* p
         }
     }
     return any && plan->n_blocks <= 0x7fffffff ? NLOS_OK : NLOS_EINVAL;
+}
+
+// Unit shape and split of a list's only request, or of one whose share of
+// workgroups no shape that fits gives: the least estimate on `target` CUs.  The patches are
+// split only where the call alone splits them too (its estimate has all CUs),
+// so that both give the same bits wherever the call alone has no float atomics.
+// A tick of one request of 16 x 16 points, 128 x 128 pixels, 512 bins takes 97 us
+// with the largest unit split 16 ways, 37 so; of 8 x 8 points, 256 x 256 pixels,
+// 1024 bins 237 and 54; of 25 x 22 points, 84 x 19 pixels, 895 bins 39 with the
+// largest shape that gives 256 workgroups, 33 so.  Lists whose requests all have
+// a shape that gives their share are left to that rule (8 requests of 32^2 to
+// 128^2 points 469 us both ways).
+void plan_share(const nlos_params* p, int32_t n_patches, int stride, int64_t target, int* chosen, int64_t* split)
+{
+    const bool conf = is_confocal(p);
+    const Cand* cands = conf ? conf_c : nc_c;
+    const int64_t L = conf ? 1 : (int64_t)p->laser.nx * p->laser.ny;
+    nlos::Plan alone;
+    const bool may_split = plan_solo(p, n_patches, stride, &alone) == NLOS_OK && alone.n_split > 1;
+    double best = 0.0;
+    bool any = false;
+    for (int i = 0; i < (conf ? 5 : 4); ++i) {
+        const Cand& c = cands[i];
+        if (nlos::lds_bytes_for(2 * c.tl * c.tx * c.ty, stride, kQueueDefault) > kLdsMax) continue;
+        const int64_t units = (L + c.tl - 1) / c.tl * ((p->relay.nx + c.tx - 1) / c.tx) *
+                              (int64_t)((p->relay.ny + c.ty - 1) / c.ty);
+        const int64_t groups = (units + 1) / 2;
+        const int64_t most =
+            may_split ? std::max<int64_t>(1, std::min<int64_t>(target / groups, n_patches / nlos::kBlock)) : 1;
+        for (int64_t sp = 1; sp <= most; sp += std::max<int64_t>(1, most - 1)) {
+            const double t = plan_cost(p, 0.6 * (double)n_patches, c, 2, false, units, sp, target);
+            if (any && t >= best) continue;
+            any = true;
+            best = t;
+            *chosen = i;
+            *split = sp;
+        }
+    }
 }
 
 // `solo`: the call runs alone (one launch with the kernel variant that suits
@@ -310,16 +350,21 @@ int make_plan(const nlos_params* p, int32_t n_patches, int R, int64_t target, bo
         return ((L + c.tl - 1) / c.tl) * (int64_t)((p->relay.nx + c.tx - 1) / c.tx) *
                (int64_t)((p->relay.ny + c.ty - 1) / c.ty);
     };
+    // (a list of one request has all CUs, where the last round of workgroups counts)
+    const bool estimate = !solo && !forced && target >= kTargetBlocks;
     int chosen = -1, largest = -1;
     for (int i = 0; i < nc; ++i) {
         const int slots = 2 * cands[i].tl * cands[i].tx * cands[i].ty;
         if (nlos::lds_bytes_for(slots, stride_of(T), q_cap) > kLdsMax) continue;
         if (largest < 0) largest = i;
-        if ((forced && i == 0) || (units_of(cands[i]) + 1) / 2 >= target) {
+        if ((forced && i == 0) || (!estimate && (units_of(cands[i]) + 1) / 2 >= target)) {
             chosen = i;
             break;
         }
     }
+    int64_t share_split = 0;   // from plan_share
+    if (chosen < 0 && largest >= 0 && !solo && !forced)
+        plan_share(p, n_patches, stride_of(T), target, &chosen, &share_split);
     if (chosen < 0) chosen = largest;
     int tw = T, n_tw = 1, pair = 1;
     if (chosen < 0) {
@@ -357,7 +402,9 @@ int make_plan(const nlos_params* p, int32_t n_patches, int R, int64_t target, bo
     plan->groups = groups;
     const int64_t tiles = groups * n_tw;
     int64_t split = 1;
-    if (tiles < target) {
+    if (share_split > 0) {
+        split = share_split;
+    } else if (tiles < target) {
         split = (target + tiles - 1) / tiles;
         const int64_t by_patches = std::max<int64_t>(1, n_patches / nlos::kBlock);
         split = std::min(split, by_patches);

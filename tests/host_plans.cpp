@@ -1,0 +1,22 @@
+// The library's host-side planning, reached from the tests: the planning
+// functions are internal to nlos_abi.cpp, which is compiled in here; the kernel
+// launchers it names come from the library and are never called.
+#include "nlos_abi.cpp"
+
+// Plan of the pair kernel for a call alone (solo) or a list's request with a
+// share of `target` workgroups: unit, pair, threads of a workgroup of one unit,
+// workgroups per split, split, windows, workgroups, LDS bytes.
+extern "C" int host_forward_plan(const nlos_params* p, int32_t n_patches, int64_t target, int32_t solo, int64_t* out)
+{
+    float taps[nlos::kMaxTaps];
+    int32_t R = 0;
+    int rc = jitter_taps(p->fwhm_ps, p->bin_ps, taps, &R);
+    if (rc != NLOS_OK) return rc;
+    nlos::Plan plan;
+    rc = make_plan(p, n_patches, R, target, solo != 0, &plan);
+    if (rc != NLOS_OK) return rc;
+    const int64_t v[10] = {plan.tl, plan.tx, plan.ty, plan.pair, plan.one, plan.groups, plan.n_split, plan.n_tw,
+                           plan.n_blocks, (int64_t)plan.lds_bytes};
+    std::memcpy(out, v, sizeof(v));
+    return NLOS_OK;
+}

@@ -1,0 +1,30 @@
+"""The plans that the library's host side chooses, without a GPU."""
+import random
+
+import host_plans
+from host_plans import forward_plan, params
+
+
+def _problems(n, seed):
+    rng = random.Random(seed)
+    for _ in range(n):
+        lasers = (rng.randint(1, 4), rng.randint(1, 4)) if rng.random() < 0.3 else (0, 0)
+        yield (params(int(2 ** rng.uniform(0, 6.5)), int(2 ** rng.uniform(0, 6.5)), int(2 ** rng.uniform(5, 14.5)),
+                      bin_ps=rng.uniform(2.0, 16.0), laser=lasers), int(2 ** rng.uniform(0, 18)))
+
+
+def test_lists_split_only_where_the_call_alone_does():
+    """A request in a list (any share of the GPU) has its patches split over
+    workgroups only where the call alone has: elsewhere both give the same bits."""
+    seen = 0
+    for prm, n in _problems(400, 1):
+        alone = forward_plan(prm, n)
+        for target in (1, 3, 17, 60, 85, 128, 200, 256):
+            got = forward_plan(prm, n, target, solo=False)
+            assert got["one"] == 0 and got["n_windows"] == alone["n_windows"]
+            assert alone["n_split"] > 1 or got["n_split"] == 1, (prm.relay.nx, prm.relay.ny, prm.n_bins, n, target)
+            seen += got["n_split"] > 1
+    assert seen > 20
+    one = params(16, 16, 512)
+    assert forward_plan(one, 128 * 128)["n_split"] == 1
+    assert forward_plan(one, 128 * 128, 256, solo=False)["n_split"] == 1
