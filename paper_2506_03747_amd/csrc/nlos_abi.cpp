@@ -322,18 +322,6 @@ int make_plan(const nlos_params* p, int32_t n_patches, int R, int64_t target, bo
     const bool conf = is_confocal(p);
     const Cand* cands = conf ? conf_c : nc_c;
     const int nc = conf ? 5 : 4;
-    // a tuned shape comes first among the candidates (it is used when its
-    // histograms fit in LDS; the usual rule decides otherwise)
-    Cand tuned_list[6];
-    Cand tuned;
-    if (tuned_unit(conf, p->n_bins, n_hist(p), &tuned)) {
-        int k = 0;
-        tuned_list[k++] = tuned;
-        for (int i = 0; i < nc; ++i)
-            if (cands[i].tl != tuned.tl || cands[i].tx != tuned.tx || cands[i].ty != tuned.ty) tuned_list[k++] = cands[i];
-        cands = tuned_list;
-    }
-    const bool forced = cands == tuned_list;
     const int T = p->n_bins;
     const int64_t L = conf ? 1 : (int64_t)p->laser.nx * p->laser.ny;
     int q_cap = kQueueDefault;
@@ -346,6 +334,19 @@ int make_plan(const nlos_params* p, int32_t n_patches, int R, int64_t target, bo
     auto stride_of = [RM](int tl) {
         return std::max((tl + 2) & ~1, ((nlos::flush_row_words(tl, RM) + 1) / 2 + 1) & ~1);
     };
+    // a tuned shape comes first among the candidates where two such units fit in
+    // LDS; without one, or where they do not, the usual rules decide
+    Cand tuned_list[6];
+    Cand tuned;
+    if (tuned_unit(conf, p->n_bins, n_hist(p), &tuned) &&
+        nlos::lds_bytes_for(2 * tuned.tl * tuned.tx * tuned.ty, stride_of(T), q_cap) <= kLdsMax) {
+        int k = 0;
+        tuned_list[k++] = tuned;
+        for (int i = 0; i < nc; ++i)
+            if (cands[i].tl != tuned.tl || cands[i].tx != tuned.tx || cands[i].ty != tuned.ty) tuned_list[k++] = cands[i];
+        cands = tuned_list;
+    }
+    const bool forced = cands == tuned_list;
     auto units_of = [&](const Cand& c) {
         return ((L + c.tl - 1) / c.tl) * (int64_t)((p->relay.nx + c.tx - 1) / c.tx) *
                (int64_t)((p->relay.ny + c.ty - 1) / c.ty);

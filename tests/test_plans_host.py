@@ -28,3 +28,24 @@ def test_lists_split_only_where_the_call_alone_does():
     one = params(16, 16, 512)
     assert forward_plan(one, 128 * 128)["n_split"] == 1
     assert forward_plan(one, 128 * 128, 256, solo=False)["n_split"] == 1
+
+
+def test_tuned_unit_that_does_not_fit_leaves_the_plan():
+    """A tuning entry whose unit does not fit in LDS twice changes nothing: a
+    call alone and a list's request take the plans they take without it."""
+    nat = host_plans._native
+    prm = params(18, 17, 1400)                   # two units of 4 x 2 histograms need more than 160 KB
+    plans = [dict(solo=True), dict(solo=False), dict(target=40, solo=False)]
+    want = [forward_plan(prm, 30000, **kw) for kw in plans]
+    L = host_plans.lib()
+    try:
+        for unit in ((1, 4, 4), (1, 4, 2)):
+            tab = (nat.TuningEntry * 1)(nat.TuningEntry(1, 1, 1 << 20, 1, 1 << 40, *unit))
+            assert L.nlos_set_tuning(tab, 1) == 0
+            assert [forward_plan(prm, 30000, **kw) for kw in plans] == want
+        tab = (nat.TuningEntry * 1)(nat.TuningEntry(1, 1, 1 << 20, 1, 1 << 40, 1, 2, 1))
+        assert L.nlos_set_tuning(tab, 1) == 0
+        got = forward_plan(prm, 30000)
+        assert (got["tx"], got["ty"], got["pair"]) == (2, 1, 1)
+    finally:
+        L.nlos_set_tuning(None, 0)
