@@ -381,7 +381,8 @@ int nlos_tick_graph_destroy(nlos_tick_graph* graph);
  * Arrivals outside the window still reach in-window bins within Rs.
  * Requires fwhm_ps > 0 and sigma * 6 <= 1024 bins; one T-bin histogram of
  * 64-bit bins must fit in LDS (T <= ~20000).  For sigma >= 1.2 bins (when the
- * rows fit in LDS) the Gaussian samples are taken as polynomials in the
+ * rows fit in LDS, and unless n_patches is so small that the direct sum is
+ * estimated to be cheaper) the Gaussian samples are taken as polynomials in the
  * sub-bin offset t = u - floor(u) - 1/2 of 8 terms (sigma < 1.6), 7 (< 2.5),
  * 6 (< 4.9) or 5: each pair adds w (-t)^m, and the rows are convolved with the
  * polynomials' coefficients; they are within 2.5e-8 (relative L2 over the
@@ -394,10 +395,11 @@ int nlos_forward_smooth(const nlos_params* p, const float* patches, int32_t n_pa
                         const int32_t* n_active, float* out, void* ws, size_t ws_bytes, void* stream);
 
 /* Workspace of nlos_adjoint: per-record partial gradients (fp64) of each
- * range of scan points; for sigma >= 1.2 bins it starts with the correlations
- * of the upstream gradient rows with the polynomials' coefficients (fp32
- * [nx*ny][T + 2 radius][n | 1], both sizes rounded up to 4, n one more than the
- * forward's terms).  256-byte aligned. */
+ * range of scan points; where the adjoint goes by correlations (sigma >= 1.2
+ * bins, and enough scan points and records that they are estimated to be the
+ * cheaper way) it starts with those of the upstream gradient rows with the
+ * polynomials' coefficients (fp32 [nx*ny][T + 2 radius][n | 1], T and the radius
+ * rounded up to 4, n one more than the forward's terms).  256-byte aligned. */
 int nlos_adjoint_workspace_bytes(const nlos_params* p, int32_t n_patches, size_t* bytes);
 
 /*
@@ -409,7 +411,7 @@ int nlos_adjoint_workspace_bytes(const nlos_params* p, int32_t n_patches, size_t
  * (records past *n_active get zeros).  Per pair dL/dw = sum_k G N(x_k) and
  * dL/du = w sum_k G (x_k / sigma^2) N(x_k), x_k = k + 1/2 - u, chained
  * through w(z, n, a) and u(z).  The step of the support with floor(u) is
- * not differentiated (below the tail at 6 sigma).  For sigma >= 1.2 bins both
+ * not differentiated (below the tail at 6 sigma).  By correlations both
  * sums are evaluated as a polynomial in the sub-bin offset and its derivative,
  * from precomputed correlations of G with the coefficients.  Deterministic:
  * partial sums per scan range are added in a fixed order.

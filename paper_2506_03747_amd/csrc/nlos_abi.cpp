@@ -737,19 +737,14 @@ struct SmoothPlan {
 
 size_t smooth_lds(int nh, int stride) { return (size_t)nh * stride * 8 + (size_t)nh * 12 + 64 * 4 + 64; }
 
-int smooth_plan(const nlos_params* p, int32_t n_patches, int rs, SmoothPlan* sp, int* split)
+// By moments, where one scan point's rows (with a halo of rs bins on both sides)
+// fit.  Two workgroups per CU before more points in one, as one's write-out then
+// runs under the other's adds: 128^2 points and patches at radius 12, 1024 bins,
+// 0.96 ms with two of one point, 1.13 with one of two; 64^2 points, 512 bins at
+// radius 16, 64 us with two of three, 72 with two of two, 93 with one of three.
+bool smooth_plan_moments(const nlos_params* p, int32_t n_patches, int rs, SmoothPlan* sp, int* split)
 {
-    static const int shapes[5][2] = {{4, 4}, {4, 2}, {2, 2}, {2, 1}, {1, 1}};
     const int T = p->n_bins;
-    // moments of the sub-bin offset when the width takes them and the rows of
-    // one scan point (with a halo of rs bins on both sides) fit.  Two
-    // workgroups per CU before more points in one, as one's write-out then runs
-    // under the other's adds: 128^2 points and patches at radius 12, 1024 bins,
-    // 0.96 ms with two of one point, 1.13 with one of two; 64^2 points, 512
-    // bins at radius 16, 64 us with two of three, 72 with two of two, 93 with
-    // one of three.
-    sp->stride = T;
-    sp->taps_bytes = 0;
     sp->moments = n_patches > 0 ? nlos::smooth_moments(smooth_sigma(p)) : 0;
     int points = 0;
     for (const auto& s : {std::pair<int, int>{2, 3}, {2, 2}, {2, 1}, {1, 1}}) {
@@ -758,22 +753,32 @@ int smooth_plan(const nlos_params* p, int32_t n_patches, int rs, SmoothPlan* sp,
         points = s.second;
         break;
     }
-    if (points > 0) {
-        sp->taps_bytes = ((size_t)sp->moments * nlos::taps_fwd(rs) * 4 + 255) & ~(size_t)255;
-        sp->tx = points;
-        sp->ty = 1;
-        sp->tiles = (int64_t)((p->relay.nx + sp->tx - 1) / sp->tx) * p->relay.ny;
-        int64_t sv = 1;
-        if (sp->tiles < kTargetBlocks) {
-            sv = (kTargetBlocks + sp->tiles - 1) / sp->tiles;
-            sv = std::min<int64_t>(sv, std::max<int64_t>(1, n_patches / nlos::kBlock));
-        }
-        *split = (int)sv;
-        sp->n_blocks = sp->tiles * sv;
-        sp->lds = 0;
-        return NLOS_OK;
+    if (points == 0) return false;
+    sp->taps_bytes = ((size_t)sp->moments * nlos::taps_fwd(rs) * 4 + 255) & ~(size_t)255;
+    sp->tx = points;
+    sp->ty = 1;
+    sp->tiles = (int64_t)((p->relay.nx + sp->tx - 1) / sp->tx) * p->relay.ny;
+    int64_t sv = 1;
+    if (sp->tiles < kTargetBlocks) {
+        sv = (kTargetBlocks + sp->tiles - 1) / sp->tiles;
+        sv = std::min<int64_t>(sv, std::max<int64_t>(1, n_patches / nlos::kBlock));
     }
+    *split = (int)sv;
+    sp->n_blocks = sp->tiles * sv;
+    sp->lds = 0;
+    sp->stride = T;
+    return true;
+}
+
+// By taps, where a histogram of T bins fits in LDS.
+bool smooth_plan_taps(const nlos_params* p, int32_t n_patches, SmoothPlan* sp, int* split)
+{
+    static const int shapes[5][2] = {{4, 4}, {4, 2}, {2, 2}, {2, 1}, {1, 1}};
+    const int T = p->n_bins;
     sp->moments = 0;
+    sp->wg = 0;
+    sp->taps_bytes = 0;
+    sp->stride = T;
     int chosen = -1, largest = -1;
     for (int i = 0; i < 5; ++i) {
         if (smooth_lds(shapes[i][0] * shapes[i][1], T) > kLdsMax) continue;
@@ -786,7 +791,7 @@ int smooth_plan(const nlos_params* p, int32_t n_patches, int rs, SmoothPlan* sp,
         }
     }
     if (chosen < 0) chosen = largest;
-    if (chosen < 0) return NLOS_EINVAL;   // one histogram of T bins does not fit in LDS
+    if (chosen < 0) return false;
     sp->tx = shapes[chosen][0];
     sp->ty = shapes[chosen][1];
     sp->tiles = (int64_t)((p->relay.nx + sp->tx - 1) / sp->tx) * ((p->relay.ny + sp->ty - 1) / sp->ty);
@@ -798,6 +803,55 @@ int smooth_plan(const nlos_params* p, int32_t n_patches, int rs, SmoothPlan* sp,
     *split = (int)sv;
     sp->n_blocks = sp->tiles * sv;
     sp->lds = smooth_lds(sp->tx * sp->ty, T);
+    return true;
+}
+
+// Estimated time in us of the smooth forward for at most 1024 records (one per
+// thread): the moments convolve every bin with 2 Rs + 1 taps of each row,
+// whatever the number of records; the taps pay 2 Rs + 1 adds per pair.  Rounds
+// of workgroups, each a fixed part, the steps of one wavefront's chain, what the
+// wavefronts share, and its rows' clearing and write-out.  Constants fitted to
+// 260 problems (1 x 1 to 130 x 130 points, 4 to 1024 records, 250 to 3300 bins,
+// 1.2 to 40 bins of sigma); on 38 others the cheaper estimate took 1.01 times
+// the faster route's time in the geometric mean (worst 1.24), moments always
+// 1.30, taps always 1.57.  48 x 40 points, 1024 bins, radius 16, 256 records:
+// 44 us by moments, 26 by taps; 100 x 100 points, 1400 bins, radius 8: 341 and
+// 112; 48 x 40 points, 700 bins, radius 30, 1024 records: 33 and 57.
+double smooth_cost(const nlos_params* p, int32_t n_patches, int rs, const SmoothPlan& sp)
+{
+    const double T = p->n_bins, nh = (double)sp.tx * sp.ty;
+    const double taps = std::min(2.0 * rs + 1.0, sp.moments ? 1e9 : T);
+    const int per_cu = sp.moments ? sp.wg : sp.lds > kLdsMax / 2 ? 1 : 2;
+    const double x = (double)sp.n_blocks / (double)(kTargetBlocks * per_cu), rounds = x < 3.0 ? std::ceil(x) : x + 0.5;
+    if (!sp.moments) {
+        const bool compiled = rs == 12 || rs == 16 || rs == 20;
+        const double waves = std::ceil((double)n_patches / 64.0);
+        const double add = compiled ? 0.0627 + 0.00455 * per_cu * waves : 0.0872 + 0.00311 * per_cu * waves;
+        return 5.2 + rounds * (2.88 + nh * taps * add + 0.388e-3 * per_cu * nh * T);
+    }
+    const double m = sp.moments, groups = nh * std::ceil(T / 4.0);
+    const double sets = std::max(1.0, std::min(4.0, std::floor(16.0 / std::ceil(groups / 64.0))));
+    const double chain = m * taps * std::ceil(groups / nlos::kBlock) / sets;
+    return 5.83 + rounds * (3.71 + 0.0271 * chain + 3.7e-6 * per_cu * m * taps * groups +
+                            2.94e-5 * per_cu * nh * m * n_patches + 0.0589 * nh) +
+           7.52e-6 * (double)sp.n_blocks * nh * T;
+}
+
+// The route: moments of the sub-bin offset where the width takes them and they
+// fit, but for few records the cheaper estimate (the taps need a workgroup per
+// CU for that, and enough bins that a wavefront's pairs do not meet in them).
+int smooth_plan(const nlos_params* p, int32_t n_patches, int rs, SmoothPlan* sp, int* split)
+{
+    if (!smooth_plan_moments(p, n_patches, rs, sp, split))
+        return smooth_plan_taps(p, n_patches, sp, split) ? NLOS_OK : NLOS_EINVAL;
+    SmoothPlan t;
+    int t_split = 1;
+    if (n_patches <= nlos::kBlock && p->n_bins >= 256 && n_hist(p) >= kTargetBlocks &&
+        smooth_plan_taps(p, n_patches, &t, &t_split) &&
+        smooth_cost(p, n_patches, rs, t) < smooth_cost(p, n_patches, rs, *sp)) {
+        *sp = t;
+        *split = t_split;
+    }
     return NLOS_OK;
 }
 
@@ -821,8 +875,9 @@ int adjoint_rows(int T)
 size_t adjoint_lds(int rows, int T) { return (((size_t)rows * T * 4 + 15) & ~(size_t)15) + (size_t)rows * 24; }
 
 // Plan of the adjoint: by moments (correlation rows computed once per scan
-// point, in the workspace ahead of the partials) when the width takes them and
-// one scan point's rows fit in LDS, else the tap gather.
+// point, in the workspace ahead of the partials) when the width takes them, one
+// scan point's rows fit in LDS and the estimate is the cheaper one, else the tap
+// gather.
 struct AdjPlan {
     int moments;       // correlation rows per scan point, 0: by taps
     int rows, split, mlen;
@@ -833,45 +888,90 @@ struct AdjPlan {
     size_t lds;
 };
 
-int adjoint_plan(const nlos_params* p, int32_t n_patches, int rs, AdjPlan* ap)
+bool adjoint_plan_moments(const nlos_params* p, int32_t n_patches, int rs, AdjPlan* ap)
 {
     const int T = p->n_bins;
     const int64_t S = (int64_t)p->relay.nx * p->relay.ny;
+    const int nf = nlos::smooth_moments(smooth_sigma(p));
+    if (nf == 0) return false;
+    const int L = nlos::adj_row_bins(T, rs), nm = nlos::adj_moments(nf);
+    // double-buffered staging when two buffers of at least one scan point fit
+    ap->moments = 0;
+    for (int buffers = 2; buffers >= 1 && !ap->moments; --buffers) {
+        int rows = 5;
+        while (rows >= 1 && nlos::adj_mom_lds(buffers, rows, nm, L) > kLdsMax) --rows;
+        if (rows < 1) continue;
+        ap->moments = nm;
+        ap->rows = rows;
+        ap->dbuf = buffers == 2;
+    }
+    if (!ap->moments) return false;
+    ap->mlen = L;
+    const int64_t per_block = (int64_t)nlos::kAdjPatches * nlos::kBlock;
+    ap->pbk = ((int64_t)n_patches + per_block - 1) / per_block;
+    const int64_t pb = std::max<int64_t>(1, ap->pbk);
+    int64_t sv = (2 * kTargetBlocks + pb - 1) / pb;
+    ap->split = (int)std::max<int64_t>(1, std::min<int64_t>(sv, std::min<int64_t>(S, 65535)));
+    ap->taps_bytes = ((size_t)nm * nlos::taps_adj(rs) * 4 + 255) & ~(size_t)255;
+    ap->c_bytes = ap->taps_bytes + (((size_t)S * nlos::adj_row_words(nm) * L * 4 + 255) & ~(size_t)255);
+    ap->lds = nlos::adj_mom_lds(ap->dbuf ? 2 : 1, ap->rows, nm, L);
+    return true;
+}
+
+bool adjoint_plan_taps(const nlos_params* p, int32_t n_patches, AdjPlan* ap)
+{
     ap->moments = 0;
     ap->dbuf = 0;
     ap->mlen = 0;
     ap->c_bytes = 0;
     ap->taps_bytes = 0;
-    const int nf = nlos::smooth_moments(smooth_sigma(p));
-    if (nf > 0) {
-        const int L = nlos::adj_row_bins(T, rs), nm = nlos::adj_moments(nf);
-        // double-buffered staging when two buffers of at least one scan point fit
-        for (int buffers = 2; buffers >= 1 && !ap->moments; --buffers) {
-            int rows = 5;
-            while (rows >= 1 && nlos::adj_mom_lds(buffers, rows, nm, L) > kLdsMax) --rows;
-            if (rows < 1) continue;
-            ap->moments = nm;
-            ap->rows = rows;
-            ap->dbuf = buffers == 2;
-        }
-        if (ap->moments) {
-            ap->mlen = L;
-            const int64_t per_block = (int64_t)nlos::kAdjPatches * nlos::kBlock;
-            ap->pbk = ((int64_t)n_patches + per_block - 1) / per_block;
-            const int64_t pb = std::max<int64_t>(1, ap->pbk);
-            int64_t sv = (2 * kTargetBlocks + pb - 1) / pb;
-            ap->split = (int)std::max<int64_t>(1, std::min<int64_t>(sv, std::min<int64_t>(S, 65535)));
-            ap->taps_bytes = ((size_t)nm * nlos::taps_adj(rs) * 4 + 255) & ~(size_t)255;
-            ap->c_bytes = ap->taps_bytes + (((size_t)S * nlos::adj_row_words(nm) * L * 4 + 255) & ~(size_t)255);
-            ap->lds = nlos::adj_mom_lds(ap->dbuf ? 2 : 1, ap->rows, nm, L);
-            return NLOS_OK;
-        }
-    }
-    ap->rows = adjoint_rows(T);
-    if (ap->rows < 1) return NLOS_EINVAL;
+    ap->rows = adjoint_rows(p->n_bins);
+    if (ap->rows < 1) return false;
     ap->split = adjoint_split(p, n_patches);
     ap->pbk = ((int64_t)n_patches + nlos::kBlock - 1) / nlos::kBlock;
-    ap->lds = adjoint_lds(ap->rows, T);
+    ap->lds = adjoint_lds(ap->rows, p->n_bins);
+    return true;
+}
+
+// Estimated time of the adjoint in us: the correlations cost a pass over every
+// scan point's rows whatever the number of records, the taps 2 Rs + 1 reads per
+// pair.  Launches, the chain of one workgroup's scan points (the wavefronts with
+// records share it), bytes written and staged, and the partials.  Constants
+// fitted to 750 problems (as at smooth_cost, up to 16900 records); on 200 others
+// the cheaper estimate took 1.01 times the faster route's time in the geometric
+// mean, moments always 1.31, taps always 1.11.  20 x 20 points, 1024 bins, radius
+// 16, 256 records: 39 us by moments, 31 by taps; 8 x 8 points, 300 bins, radius
+// 8, 4096 records: 26 and 14; 100 x 100 points, 700 bins, radius 30, 256 records:
+// 114 and 267.
+double adjoint_cost(const nlos_params* p, int32_t n_patches, int rs, const AdjPlan& ap)
+{
+    const double T = p->n_bins, S = (double)p->relay.nx * p->relay.ny, n = n_patches;
+    const double pb = (double)std::max<int64_t>(1, ap.pbk);
+    const double partials = 1e-6 * ap.split * n * nlos::kAdjStride * sizeof(double);
+    const double per_cu = ap.lds > kLdsMax / 2 ? 1.0 : 2.0;
+    if (!ap.moments) {
+        const bool compiled = rs == 12 || rs == 16 || rs == 20;
+        const double chain = std::ceil(pb * ap.split / (kTargetBlocks * per_cu)) * std::ceil(S / ap.split) *
+                             std::min(2.0 * rs + 1.0, T);
+        const double waves = std::min(16.0, std::ceil(n / 64.0)) * per_cu / 16.0;
+        return 8.79 + chain * (compiled ? 0.0884 + 0.00685 * waves : 0.0903 + 0.01205 * waves) + 1.03e-6 * pb * S * T +
+               0.438 * partials + 0.0287 * ap.split;
+    }
+    const double words = 1e-6 * S * nlos::adj_row_words(ap.moments) * ap.mlen, stages = std::ceil(S / ap.rows);
+    const double chain = std::ceil(pb * std::min((double)ap.split, stages) / (kTargetBlocks * per_cu)) * ap.rows *
+                         std::ceil(stages / ap.split);
+    return 14.81 + 0.0283 * rs * ap.moments + 0.372 * words + 2.87e-8 * S * ap.mlen * rs * ap.moments +
+           0.476 * pb * words + 0.145 * chain * std::min(4.0, std::ceil(n / nlos::kBlock)) + 0.331 * partials +
+           0.0311 * ap.split;
+}
+
+int adjoint_plan(const nlos_params* p, int32_t n_patches, int rs, AdjPlan* ap)
+{
+    AdjPlan t;
+    const bool mom = adjoint_plan_moments(p, n_patches, rs, ap), taps = adjoint_plan_taps(p, n_patches, &t);
+    if (!mom && !taps) return NLOS_EINVAL;
+    // (an estimate of the taps that is near the other's is more often too low)
+    if (!mom || (taps && adjoint_cost(p, n_patches, rs, t) < 0.95 * adjoint_cost(p, n_patches, rs, *ap))) *ap = t;
     return NLOS_OK;
 }
 

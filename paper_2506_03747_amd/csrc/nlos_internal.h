@@ -360,7 +360,7 @@ struct MomentFit {
 // polynomials (relative L2 over the support, root mean square over the bin)
 // stays below 2.5e-8, a quarter of what fp32 weights leave: 8 terms down to
 // 1.2 bins (1.2e-8), 7 from 1.6 (2.0e-8), 6 from 2.5 (2.4e-8), 5 from 4.9
-// (2.3e-8).  Below 1.2 bins the support has at most 15 taps and the direct
+// (2.3e-8).  Below 1.2 bins the support has at most 17 taps and the direct
 // sum costs as much.  The adjoint takes one more (adj_moments), as it uses the
 // polynomial's derivative too.
 inline int smooth_moments(double sigma)

@@ -14,17 +14,18 @@
 // k_smooth_mom   forward for sigma >= 1.2 bins: 5 to 8 moments of the sub-bin
 //                offset per pair into LDS rows, then a convolution of each
 //                moment row with its kernel, four bins per thread.
-// k_smooth       forward otherwise, or where the moment rows of one scan point
-//                do not fit in LDS: a workgroup owns a tile of scan points
-//                (LDS rows of 64-bit fixed-point bins), a lane one patch;
-//                2 Rs + 1 LDS adds per pair, Gaussian samples by a
+// k_smooth       forward otherwise, where the moment rows of one scan point do
+//                not fit in LDS, or for few records: a workgroup owns a tile of
+//                scan points (LDS rows of 64-bit fixed-point bins), a lane one
+//                patch; 2 Rs + 1 LDS adds per pair, Gaussian samples by a
 //                three-exponential recurrence.
 // k_adj_moments, k_adjoint_mom   adjoint for the same widths: the upstream
 //                gradient's correlations with the polynomials' kernels once
 //                per scan point, then per pair a polynomial in the sub-bin
 //                offset and its derivative.
-// k_adjoint      gather otherwise: a lane owns one patch and loops over a range of scan
-//                points whose upstream-gradient rows are staged in LDS; per
+// k_adjoint      gather otherwise, or for few records or scan points: a lane
+//                owns one patch and loops over a range of scan points whose
+//                upstream-gradient rows are staged in LDS; per
 //                pair G0 = sum g N(x), G1 = sum g (x / sigma^2) N(x) give
 //                dL/dw = G0 and dL/du = w G1; per-record partial gradients
 //                (fp64) per scan range, summed in a fixed order afterwards

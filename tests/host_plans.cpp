@@ -20,3 +20,35 @@ extern "C" int host_forward_plan(const nlos_params* p, int32_t n_patches, int64_
     std::memcpy(out, v, sizeof(v));
     return NLOS_OK;
 }
+
+// Plan of the smooth forward: moment rows per scan point (0: by taps), tile,
+// tiles, splits, workgroups, workgroups per CU (moments), bytes of the kernels' table.
+extern "C" int host_smooth_plan(const nlos_params* p, int32_t n_patches, int64_t* out)
+{
+    nlos::SmoothArgs a;
+    int rc = smooth_setup(p, nullptr, 0, nullptr, &a);
+    if (rc != NLOS_OK) return rc;
+    SmoothPlan sp;
+    int split = 1;
+    rc = smooth_plan(p, n_patches, a.Rs, &sp, &split);
+    if (rc != NLOS_OK) return rc;
+    const int64_t v[8] = {sp.moments, sp.tx, sp.ty, sp.tiles, split, sp.n_blocks, sp.wg, (int64_t)sp.taps_bytes};
+    std::memcpy(out, v, sizeof(v));
+    return NLOS_OK;
+}
+
+// Plan of the adjoint: correlation rows per scan point (0: by taps), scan points
+// per stage, splits, patch blocks, two row buffers, bytes ahead of the partials,
+// LDS bytes.
+extern "C" int host_adjoint_plan(const nlos_params* p, int32_t n_patches, int64_t* out)
+{
+    nlos::SmoothArgs a;
+    int rc = smooth_setup(p, nullptr, 0, nullptr, &a);
+    if (rc != NLOS_OK) return rc;
+    AdjPlan ap;
+    rc = adjoint_plan(p, n_patches, a.Rs, &ap);
+    if (rc != NLOS_OK) return rc;
+    const int64_t v[7] = {ap.moments, ap.rows, ap.split, ap.pbk, ap.dbuf, (int64_t)ap.c_bytes, (int64_t)ap.lds};
+    std::memcpy(out, v, sizeof(v));
+    return NLOS_OK;
+}

@@ -40,3 +40,21 @@ def forward_plan(prm, n_patches, target=256, solo=True):
     rc = lib().host_forward_plan(C.byref(prm), n_patches, C.c_int64(target), int(solo), out)
     assert rc == 0, rc
     return dict(zip(FORWARD, out))
+
+
+SMOOTH = ("moments", "tx", "ty", "tiles", "split", "workgroups", "per_cu", "table_bytes")
+ADJOINT = ("moments", "rows", "split", "patch_blocks", "two_buffers", "head_bytes", "lds_bytes")
+
+
+def smooth_plan(prm, n_patches):
+    out = (C.c_int64 * len(SMOOTH))()
+    rc = lib().host_smooth_plan(C.byref(prm), n_patches, out)
+    assert rc == 0, rc
+    return dict(zip(SMOOTH, out))
+
+
+def adjoint_plan(prm, n_patches):
+    out = (C.c_int64 * len(ADJOINT))()
+    rc = lib().host_adjoint_plan(C.byref(prm), n_patches, out)
+    assert rc == 0, rc
+    return dict(zip(ADJOINT, out))

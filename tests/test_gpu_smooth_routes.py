@@ -1,0 +1,84 @@
+"""The smooth forward and its adjoint on both sides of the rule that chooses
+between moments and taps by the numbers of records and scan points: scans large
+enough that the adjoint goes by moments at every number of terms (rows of whole
+and ragged length, one and two row buffers, several blocks of records), and few
+records under a wide scan by taps.  Against the fp64 oracle, with the bars of
+the other smooth tests."""
+import math
+
+import numpy as np
+import pytest
+
+import host_plans
+import oracle
+from gpu_helpers import assert_parity, to_gpu
+from pins_smooth import smooth_scene
+from test_gpu_smooth import _assert_record_grads
+
+pytestmark = pytest.mark.gpu
+
+
+def case(seed, sigma, T, forward, adjoint, **kw):
+    # arrivals at 3.3 to 6 ns cross most of the window
+    bin_ps = max(2.0, 6200.0 / T)
+    return forward, adjoint, dict(seed=seed, n_bins=T, bin_ps=bin_ps,
+                                  fwhm_ps=sigma * bin_ps * 2.0 * math.sqrt(2.0 * math.log(2.0)), **kw)
+
+
+# (terms of the forward, of the adjoint; 0: by taps)
+CASES = [
+    case(740, 1.4, 300, 8, 9, scan=(48, 40), patches=(52, 44)), case(741, 2.0, 301, 7, 8, scan=(47, 41), patches=(52, 44)),
+    case(742, 2.65, 402, 6, 7, scan=(50, 38), patches=(65, 70)), case(743, 5.2, 403, 5, 6, scan=(61, 47), patches=(40, 30)),
+    case(744, 7.0, 1500, 5, 6, scan=(40, 30), patches=(50, 50)),
+    case(745, 5.0, 3300, 5, 6, scan=(30, 24), patches=(70, 61)),              # one scan point's rows, one buffer
+    case(746, 3.0, 600, 6, 7, scan=(1, 1500), patches=(60, 60), cosines=False, standoff_m=0.4),
+    case(747, 2.65, 900, 0, 0, scan=(48, 40), patches=(9, 11)),               # a compiled radius
+    case(748, 3.5, 1801, 0, 7, scan=(30, 20), patches=(32, 32)),              # a record per thread
+    case(749, 3.5, 1801, 6, 7, scan=(30, 20), patches=(50, 41)),              # and more
+    case(750, 1.3, 2000, 0, 0, scan=(16, 16), patches=(13, 17)),
+]
+
+
+@pytest.mark.parametrize("forward,adjoint,kw", CASES, ids=[str(c[2]["seed"]) for c in CASES])
+def test_smooth_routes(forward, adjoint, kw):
+    import torch
+    import paper_2506_03747_amd as nl
+    sc = smooth_scene(**kw)
+    prm = nl.params_of(sc)
+    assert host_plans.smooth_plan(prm, sc.n_patch_total)["moments"] == forward
+    assert host_plans.adjoint_plan(prm, sc.n_patch_total)["moments"] == adjoint
+    depth, albedo, mask = to_gpu(sc)
+    rec, n = nl.patches_from_depth(depth, sc.patch_grid, albedo, mask, cosines=sc.cosines)
+    tau = nl.forward_smooth(prm, rec, n)
+    G = np.random.default_rng(kw["seed"]).standard_normal((sc.n_scan, sc.n_bins)).astype(np.float32)
+    gr = nl.adjoint(prm, rec, n, torch.from_numpy(G).cuda())
+    torch.cuda.synchronize()
+    assert_parity(tau.cpu().numpy(), oracle.forward_smooth(sc), what=f"smooth {kw}")
+    k = int(n.item())
+    idx = rec[:k].cpu().numpy()[:, 7].view(np.int32)
+    want = oracle.adjoint_records(sc, G.astype(np.float64))[idx]
+    _assert_record_grads(gr[:k].cpu().numpy().astype(np.float64), want, f"adjoint {kw['seed']}")
+    assert not gr[k:].cpu().numpy().any()
+
+
+def test_correlations_keep_to_their_support():
+    """An infinite upstream value reaches the records within the support of its
+    bin and no others, by the correlations too."""
+    import torch
+    import paper_2506_03747_amd as nl
+    sc = smooth_scene(760, scan=(48, 40), patches=(52, 44), n_bins=512, bin_ps=12.0, fwhm_ps=12.0 * 2.6 * 2.3548200450309493)
+    prm = nl.params_of(sc)
+    assert host_plans.adjoint_plan(prm, sc.n_patch_total)["moments"]
+    depth, albedo, mask = to_gpu(sc)
+    rec, n = nl.patches_from_depth(depth, sc.patch_grid, albedo, mask)
+    k = int(n.item())
+    point = 777
+    bins = nl.debug_bins(prm, rec, n)[point, :k].cpu().numpy()
+    at = int(np.sort(bins)[k // 3])
+    G = torch.zeros((sc.n_scan, sc.n_bins), device="cuda")
+    G[point, at] = float("inf")
+    gr = nl.adjoint(prm, rec, n, G)[:k].cpu().numpy()
+    away = np.abs(bins - at) > math.ceil(6 * 2.6)
+    assert away.any() and not away.all()
+    assert np.isfinite(gr[away]).all() and not gr[away].any()
+    assert not np.isfinite(gr[~away][:, 3]).any()

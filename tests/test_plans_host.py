@@ -1,8 +1,10 @@
 """The plans that the library's host side chooses, without a GPU."""
 import random
 
+import pytest
+
 import host_plans
-from host_plans import forward_plan, params
+from host_plans import adjoint_plan, forward_plan, params, smooth_plan
 
 
 def _problems(n, seed):
@@ -49,3 +51,29 @@ def test_tuned_unit_that_does_not_fit_leaves_the_plan():
         assert (got["tx"], got["ty"], got["pair"]) == (2, 1, 1)
     finally:
         L.nlos_set_tuning(None, 0)
+
+
+# scan, bins, ps per bin, FWHM in ps, records -> by moments (measured faster by more than a tenth)
+SMOOTH_ROUTES = [((48, 40), 1024, 8.0, 50.0, 256, False), ((48, 40), 1600, 5.0, 60.0, 64, False),
+                 ((100, 100), 1400, 8.0, 25.0, 1024, False), ((100, 100), 3000, 3.0, 50.0, 576, False),
+                 ((20, 20), 2048, 4.0, 60.0, 16, False), ((100, 100), 700, 6.0, 70.0, 64, True),
+                 ((48, 40), 700, 6.0, 70.0, 1024, True), ((8, 8), 1024, 8.0, 50.0, 16, True),
+                 ((48, 40), 1600, 5.0, 60.0, 4096, True), ((128, 128), 1024, 8.0, 50.0, 16384, True)]
+ADJOINT_ROUTES = [((8, 8), 300, 16.0, 46.0, 4096, False), ((20, 20), 1024, 8.0, 50.0, 256, False),
+                  ((100, 100), 1400, 8.0, 25.0, 1024, False), ((48, 40), 300, 16.0, 46.0, 256, False),
+                  ((100, 100), 700, 6.0, 70.0, 16, True), ((48, 40), 1600, 5.0, 60.0, 2304, True),
+                  ((100, 100), 400, 8.0, 50.0, 256, True), ((128, 128), 1024, 8.0, 50.0, 16384, True)]
+
+
+@pytest.mark.parametrize("scan,T,bin_ps,fwhm_ps,n,moments", SMOOTH_ROUTES)
+def test_smooth_forward_route(scan, T, bin_ps, fwhm_ps, n, moments):
+    """Few records: the taps' work per pair is less than the moments' per bin."""
+    assert (smooth_plan(params(*scan, T, bin_ps, fwhm_ps), n)["moments"] > 0) == moments
+
+
+@pytest.mark.parametrize("scan,T,bin_ps,fwhm_ps,n,moments", ADJOINT_ROUTES)
+def test_adjoint_route(scan, T, bin_ps, fwhm_ps, n, moments):
+    """Few records or scan points: no pass of correlations over every row."""
+    plan = adjoint_plan(params(*scan, T, bin_ps, fwhm_ps), n)
+    assert (plan["moments"] > 0) == moments
+    assert (plan["head_bytes"] > 0) == moments
