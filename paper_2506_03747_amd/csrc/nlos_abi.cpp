@@ -806,35 +806,33 @@ bool smooth_plan_taps(const nlos_params* p, int32_t n_patches, SmoothPlan* sp, i
     return true;
 }
 
-// Estimated time in us of the smooth forward for at most 1024 records (one per
-// thread): the moments convolve every bin with 2 Rs + 1 taps of each row,
-// whatever the number of records; the taps pay 2 Rs + 1 adds per pair.  Rounds
-// of workgroups, each a fixed part, the steps of one wavefront's chain, what the
-// wavefronts share, and its rows' clearing and write-out.  Constants fitted to
-// 260 problems (1 x 1 to 130 x 130 points, 4 to 1024 records, 250 to 3300 bins,
-// 1.2 to 40 bins of sigma); on 38 others the cheaper estimate took 1.01 times
-// the faster route's time in the geometric mean (worst 1.24), moments always
-// 1.30, taps always 1.57.  48 x 40 points, 1024 bins, radius 16, 256 records:
-// 44 us by moments, 26 by taps; 100 x 100 points, 1400 bins, radius 8: 341 and
-// 112; 48 x 40 points, 700 bins, radius 30, 1024 records: 33 and 57.
-double smooth_cost(const nlos_params* p, int32_t n_patches, int rs, const SmoothPlan& sp)
+// Estimated time in us of the smooth forward for at most 4096 records: the
+// moments convolve every bin with 2 Rs + 1 taps of each row, whatever the number
+// of records; the taps pay 2 Rs + 1 adds per pair.  Rounds of workgroups, each a
+// fixed part, the steps of one wavefront's chain, what the wavefronts share, and
+// its rows' clearing and write-out.  Constants fitted to 308 problems (256 to
+// 16900 points, 4 to 4096 records, 256 to 3300 bins, 1.2 to 40 bins of sigma); on
+// 38 others the cheaper estimate took 1.015 times the faster way's time in the
+// geometric mean (worst 1.24), moments always 1.30, taps always 1.48.  48 x 40
+// points, 1024 bins, radius 16, 256 records: 44 us by moments, 26 by taps; 100 x
+// 100 points, 1400 bins, radius 8, 1024 records: 360 and 147; 48 x 40 points, 700
+// bins, radius 30, 1024 records: 33 and 57.
+double smooth_cost(const nlos_params* p, int32_t n_patches, int rs, const SmoothPlan& sp, int split)
 {
-    const double T = p->n_bins, nh = (double)sp.tx * sp.ty;
-    const double taps = std::min(2.0 * rs + 1.0, sp.moments ? 1e9 : T);
+    const double T = p->n_bins, nh = (double)sp.tx * sp.ty, n = std::ceil((double)n_patches / split);
     const int per_cu = sp.moments ? sp.wg : sp.lds > kLdsMax / 2 ? 1 : 2;
     const double x = (double)sp.n_blocks / (double)(kTargetBlocks * per_cu), rounds = x < 3.0 ? std::ceil(x) : x + 0.5;
+    const double taps = sp.moments ? 2.0 * rs + 1.0 : std::min(2.0 * rs + 1.0, T);
     if (!sp.moments) {
         const bool compiled = rs == 12 || rs == 16 || rs == 20;
-        const double waves = std::ceil((double)n_patches / 64.0);
-        const double add = compiled ? 0.0627 + 0.00455 * per_cu * waves : 0.0872 + 0.00311 * per_cu * waves;
-        return 5.2 + rounds * (2.88 + nh * taps * add + 0.388e-3 * per_cu * nh * T);
+        const double add = (compiled ? 0.0724 : 0.0859) * std::ceil(n / nlos::kBlock) + 0.00295 * per_cu * std::ceil(n / 64.0);
+        return 5.5 + rounds * (2.66 + nh * taps * add + 0.427e-3 * per_cu * nh * T);
     }
     const double m = sp.moments, groups = nh * std::ceil(T / 4.0);
     const double sets = std::max(1.0, std::min(4.0, std::floor(16.0 / std::ceil(groups / 64.0))));
     const double chain = m * taps * std::ceil(groups / nlos::kBlock) / sets;
-    return 5.83 + rounds * (3.71 + 0.0271 * chain + 3.7e-6 * per_cu * m * taps * groups +
-                            2.94e-5 * per_cu * nh * m * n_patches + 0.0589 * nh) +
-           7.52e-6 * (double)sp.n_blocks * nh * T;
+    return 5.9 + rounds * (4.0 + 0.0267 * chain + 5.43e-6 * per_cu * m * taps * groups + 3.14e-5 * per_cu * nh * m * n) +
+           (split > 1 ? 16.5e-6 : 6.86e-6) * (double)sp.n_blocks * nh * T;
 }
 
 // The route: moments of the sub-bin offset where the width takes them and they
@@ -846,9 +844,9 @@ int smooth_plan(const nlos_params* p, int32_t n_patches, int rs, SmoothPlan* sp,
         return smooth_plan_taps(p, n_patches, sp, split) ? NLOS_OK : NLOS_EINVAL;
     SmoothPlan t;
     int t_split = 1;
-    if (n_patches <= nlos::kBlock && p->n_bins >= 256 && n_hist(p) >= kTargetBlocks &&
+    if (n_patches <= 4 * nlos::kBlock && p->n_bins >= 256 && n_hist(p) >= kTargetBlocks &&
         smooth_plan_taps(p, n_patches, &t, &t_split) &&
-        smooth_cost(p, n_patches, rs, t) < smooth_cost(p, n_patches, rs, *sp)) {
+        smooth_cost(p, n_patches, rs, t, t_split) < smooth_cost(p, n_patches, rs, *sp, *split)) {
         *sp = t;
         *split = t_split;
     }

@@ -56,7 +56,7 @@ def test_tuned_unit_that_does_not_fit_leaves_the_plan():
 # scan, bins, ps per bin, FWHM in ps, records -> by moments (measured faster by more than a tenth)
 SMOOTH_ROUTES = [((48, 40), 1024, 8.0, 50.0, 256, False), ((48, 40), 1600, 5.0, 60.0, 64, False),
                  ((100, 100), 1400, 8.0, 25.0, 1024, False), ((100, 100), 3000, 3.0, 50.0, 576, False),
-                 ((20, 20), 2048, 4.0, 60.0, 16, False), ((100, 100), 700, 6.0, 70.0, 64, True),
+                 ((20, 20), 2048, 4.0, 60.0, 16, False), ((48, 40), 1400, 8.0, 25.0, 2304, False), ((100, 100), 700, 6.0, 70.0, 64, True),
                  ((48, 40), 700, 6.0, 70.0, 1024, True), ((8, 8), 1024, 8.0, 50.0, 16, True),
                  ((48, 40), 1600, 5.0, 60.0, 4096, True), ((128, 128), 1024, 8.0, 50.0, 16384, True)]
 ADJOINT_ROUTES = [((8, 8), 300, 16.0, 46.0, 4096, False), ((20, 20), 1024, 8.0, 50.0, 256, False),
