@@ -749,6 +749,7 @@ bool smooth_plan_moments(const nlos_params* p, int32_t n_patches, int rs, Smooth
     int points = 0;
     for (const auto& s : {std::pair<int, int>{2, 3}, {2, 2}, {2, 1}, {1, 1}}) {
         if (sp->moments == 0 || T + 2 * rs > nlos::smooth_mom_pitch(s.second, sp->moments, s.first)) continue;
+        if (s.second > p->relay.nx) continue;   // (a wall row has no more)
         sp->wg = s.first;
         points = s.second;
         break;

@@ -439,6 +439,7 @@ __global__ void __launch_bounds__(kBlock, 4 * WG) k_smooth_mom(const SmoothArgs 
     cut = uniform_f(cut);
     const double inv2 = 2.0 * a.inv, wyd = (double)wy;
     const float invf = (float)a.inv;
+    const int n_pts = NP > 1 ? min(NP, a.rx.n - tx0) : 1;   // (fewer at the wall's end)
 
     for (int base = pb; base < pe; base += kBlock) {
         const int p = base + (int)threadIdx.x;
@@ -455,6 +456,7 @@ __global__ void __launch_bounds__(kBlock, 4 * WG) k_smooth_mom(const SmoothArgs 
         const float aw = COS ? A.w * (A.z * A.z) : A.w;
 #pragma unroll
         for (int c = 0; c < NP; ++c) {
+            if (c >= n_pts) break;   // uniform
             const double ex = px - (double)wx[c];
             const double r2d = fma(ex, ex, yz2);
             const Arrival q = arrival(r2d, (float)r2d, inv2, oi[c], invf);

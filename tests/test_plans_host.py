@@ -77,3 +77,11 @@ def test_adjoint_route(scan, T, bin_ps, fwhm_ps, n, moments):
     plan = adjoint_plan(params(*scan, T, bin_ps, fwhm_ps), n)
     assert (plan["moments"] > 0) == moments
     assert (plan["head_bytes"] > 0) == moments
+
+
+@pytest.mark.parametrize("nx,points", [(1, 1), (2, 2), (3, 3), (4, 3), (50, 3)])
+def test_smooth_points_per_workgroup_exist(nx, points):
+    """Short rows leave room for three scan points per workgroup; a narrow scan
+    gets no more than it has along x."""
+    plan = smooth_plan(params(nx, 4000 // nx, 400, 8.0, 50.0), 5000)
+    assert plan["moments"] == 6 and plan["tx"] == points
