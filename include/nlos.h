@@ -399,7 +399,8 @@ int nlos_forward_smooth(const nlos_params* p, const float* patches, int32_t n_pa
  * bins, and enough scan points and records that they are estimated to be the
  * cheaper way) it starts with those of the upstream gradient rows with the
  * polynomials' coefficients (fp32 [nx*ny][T + 2 radius][n | 1], T and the radius
- * rounded up to 4, n one more than the forward's terms).  256-byte aligned. */
+ * rounded up to 4, n one more than the forward's terms; at most 4 GiB, longer
+ * scans go piece by piece).  256-byte aligned. */
 int nlos_adjoint_workspace_bytes(const nlos_params* p, int32_t n_patches, size_t* bytes);
 
 /*

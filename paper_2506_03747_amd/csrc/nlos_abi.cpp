@@ -873,6 +873,14 @@ int adjoint_rows(int T)
 
 size_t adjoint_lds(int rows, int T) { return (((size_t)rows * T * 4 + 15) & ~(size_t)15) + (size_t)rows * 24; }
 
+// Correlation rows held at a time: they take 20 to 36 bytes for each of the
+// output's 4, so a scan that needs more goes piece by piece, the records'
+// gradients adding up in their partials.  (A row is at most 160 KB of LDS, so
+// that a piece always fills the GPU.)  512^2 points, 64^2 patches, 1500 bins,
+// radius 31, 11 GB of rows: 6.19 ms whole, 6.35 in three pieces (with 1 GiB, 90000
+// points of 2000 bins 2.81 whole and 3.12 in five).
+constexpr size_t kAdjRowBytes = (size_t)4 << 30;
+
 // Plan of the adjoint: by moments (correlation rows computed once per scan
 // point, in the workspace ahead of the partials) when the width takes them, one
 // scan point's rows fit in LDS and the estimate is the cheaper one, else the tap
@@ -882,7 +890,8 @@ struct AdjPlan {
     int rows, split, mlen;
     int dbuf;          // moment gather: two row buffers, one filled while the other is read
     int64_t pbk;       // patch blocks of the gather
-    size_t c_bytes;    // kernel taps, then correlation rows [S][mlen][adj_row_words] fp32
+    int64_t piece;     // scan points whose correlation rows are held at a time
+    size_t c_bytes;    // kernel taps, then correlation rows [piece][mlen][adj_row_words] fp32
     size_t taps_bytes; // the taps' share of c_bytes
     size_t lds;
 };
@@ -912,7 +921,9 @@ bool adjoint_plan_moments(const nlos_params* p, int32_t n_patches, int rs, AdjPl
     int64_t sv = (2 * kTargetBlocks + pb - 1) / pb;
     ap->split = (int)std::max<int64_t>(1, std::min<int64_t>(sv, std::min<int64_t>(S, 65535)));
     ap->taps_bytes = ((size_t)nm * nlos::taps_adj(rs) * 4 + 255) & ~(size_t)255;
-    ap->c_bytes = ap->taps_bytes + (((size_t)S * nlos::adj_row_words(nm) * L * 4 + 255) & ~(size_t)255);
+    const size_t row = (size_t)nlos::adj_row_words(nm) * L * 4;
+    ap->piece = std::min<int64_t>(S, (int64_t)(kAdjRowBytes / row));
+    ap->c_bytes = ap->taps_bytes + (((size_t)ap->piece * row + 255) & ~(size_t)255);
     ap->lds = nlos::adj_mom_lds(ap->dbuf ? 2 : 1, ap->rows, nm, L);
     return true;
 }
@@ -922,6 +933,7 @@ bool adjoint_plan_taps(const nlos_params* p, int32_t n_patches, AdjPlan* ap)
     ap->moments = 0;
     ap->dbuf = 0;
     ap->mlen = 0;
+    ap->piece = 0;
     ap->c_bytes = 0;
     ap->taps_bytes = 0;
     ap->rows = adjoint_rows(p->n_bins);
@@ -1762,7 +1774,7 @@ int nlos_adjoint(const nlos_params* p, const float* patches, int32_t n_patches, 
     a.rows = ap.rows;
     hipStream_t st = (hipStream_t)stream;
     hipError_t e = ap.moments ? nlos::launch_adjoint_moments(a, moment_fit(smooth_sigma(p), a.Rs, ap.moments), ap.pbk,
-                                                             ap.lds, ap.dbuf != 0, st)
+                                                             ap.lds, ap.dbuf != 0, ap.piece, st)
                               : nlos::launch_adjoint(a, ap.pbk, ap.lds, st);
     if (e != hipSuccess) return hip_fail(e);
     e = nlos::launch_adjoint_reduce(a, grad_patches, st);

@@ -277,9 +277,10 @@ struct SmoothArgs {
     int32_t cosines;
     ChunkStat* stats;
     int32_t n_stats;
-    float* moments;            // adjoint by moments: [S][mlen][adj_row_words(n)] correlations
+    float* moments;            // adjoint by moments: [sn][mlen][adj_row_words(n)] correlations
     float* mtaps;              // by moments: kernels K_m(d), [n][taps_fwd(Rs)] or [n][taps_adj(Rs)]
     int32_t mlen;              // adj_row_bins(T, Rs)
+    int32_t s0, sn;            // adjoint by moments: this launch's scan points s0 .. s0 + sn - 1
 };
 
 // Record gradients -> map gradients (depth-stencil adjoint).
@@ -399,8 +400,9 @@ inline size_t adj_mom_lds(int buffers, int rows, int n, int bins)
 {
     return (size_t)buffers * rows * ((size_t)adj_row_words(n) * bins * 4 + 24);
 }
+// `piece`: scan points whose correlations the workspace holds at a time.
 hipError_t launch_adjoint_moments(const SmoothArgs& a, const MomentFit& f, int64_t patch_blocks, size_t lds, bool dbuf,
-                                  hipStream_t st);
+                                  int64_t piece, hipStream_t st);
 hipError_t launch_adjoint(const SmoothArgs& a, int64_t patch_blocks, size_t lds, hipStream_t st);
 hipError_t launch_adjoint_reduce(const SmoothArgs& a, float* grad_rec, hipStream_t st);
 hipError_t launch_grad_maps(const GradMapArgs& g, hipStream_t st);

@@ -767,7 +767,7 @@ __global__ void __launch_bounds__(256) k_adj_moments(const SmoothArgs a)
     constexpr int V = 4, NS = adj_row_words(NM);
     __shared__ __align__(16) float tr[4][64 * V * NS];
     const int T = a.T, L = a.mlen, Q = L / V, H = adj_halo(a.Rs);
-    const int64_t n_thr = (int64_t)(a.rx.n * a.ry.n) * Q;
+    const int64_t n_thr = (int64_t)a.sn * Q;
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
     if (t < n_thr) {
@@ -858,7 +858,10 @@ __global__ void __launch_bounds__(256) k_adj_moments(const SmoothArgs a)
 // patches.  128^2 points and patches, 1024 bins, radius 16: 0.67 -> 0.49 ms;
 // 48 x 40 points, 3840 patches, 1501 bins, radius 31: 522 us by taps, 95 with
 // the correlations.
-template <bool COS, int NM, bool DB>
+// PIECE: the launch takes sn scan points from s0 on and adds to the partials of
+// the pieces before (an instance of its own: the offset and the sum in one kernel
+// for all cost the whole scans of these sizes 0.5 and 6%).
+template <bool COS, int NM, bool DB, bool PIECE>
 __global__ void __launch_bounds__(kBlock) k_adjoint_mom(const SmoothArgs a)
 {
     constexpr int NS = adj_row_words(NM), PPT = kAdjPatches, NB = DB ? 2 : 1;
@@ -880,7 +883,7 @@ __global__ void __launch_bounds__(kBlock) k_adjoint_mom(const SmoothArgs a)
     const int nbx = (n_act + PPT * kBlock - 1) / (PPT * kBlock);
     if ((int)blockIdx.x >= nbx) return;   // (nothing reads this block's partials)
     const int split = (int)blockIdx.y;
-    const int S = a.rx.n * a.ry.n;
+    const int S = PIECE ? a.sn : a.rx.n * a.ry.n;
     const auto patch = [&](int i) {
         return (((int)threadIdx.x / 256 + 4 * i) * nbx + (int)blockIdx.x) * 256 + (int)threadIdx.x % 256;
     };
@@ -908,7 +911,7 @@ __global__ void __launch_bounds__(kBlock) k_adjoint_mom(const SmoothArgs a)
     // the constants of scan points [j, j + nr) into buffer b
     auto stage_consts = [&](int b, int j, int nr) {
         if ((int)threadIdx.x < nr) {
-            const int h = j + (int)threadIdx.x;
+            const int h = (PIECE ? a.s0 : 0) + j + (int)threadIdx.x;
             const float wx = canon(a.rx, h / a.ry.n), wy = canon(a.ry, h % a.ry.n);
             double off, g;
             device_leg(wx, wy, a.cx, a.cy, a.s, &off, &g);
@@ -1039,11 +1042,17 @@ __global__ void __launch_bounds__(kBlock) k_adjoint_mom(const SmoothArgs a)
         if (!live[i]) continue;
         const double aw = (double)a.patches[2 * (size_t)p].w;
         double* o = a.partial + ((size_t)split * a.n_cap + p) * kAdjStride;
-        o[0] = aw * (gz[i] - 2.0 * (double)B[i].z * gn[i]);
-        o[1] = ga[i];
-        o[2] = -2.0 * aw * gnx[i];
-        o[3] = -2.0 * aw * gny[i];
-        o[4] = -2.0 * aw * (double)B[i].w * gn[i];
+        const auto put = [&](int k, double v) {
+            if constexpr (PIECE)
+                o[k] = a.s0 > 0 ? o[k] + v : v;
+            else
+                o[k] = v;
+        };
+        put(0, aw * (gz[i] - 2.0 * (double)B[i].z * gn[i]));
+        put(1, ga[i]);
+        put(2, -2.0 * aw * gnx[i]);
+        put(3, -2.0 * aw * gny[i]);
+        put(4, -2.0 * aw * (double)B[i].w * gn[i]);
     }
 }
 
@@ -1274,50 +1283,64 @@ hipError_t launch_adjoint(const SmoothArgs& a, int64_t patch_blocks, size_t lds,
     return hipSuccess;
 }
 
-template <int NM, bool DB>
+template <int NM, bool DB, bool PIECE>
 static hipError_t launch_adjoint_gather(const SmoothArgs& a, const dim3& grid, size_t lds, hipStream_t st)
 {
-    const void* k = a.cosines ? (const void*)k_adjoint_mom<true, NM, DB> : (const void*)k_adjoint_mom<false, NM, DB>;
+    const void* k =
+        a.cosines ? (const void*)k_adjoint_mom<true, NM, DB, PIECE> : (const void*)k_adjoint_mom<false, NM, DB, PIECE>;
     hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     if (a.cosines)
-        hipLaunchKernelGGL((k_adjoint_mom<true, NM, DB>), grid, dim3(kBlock), lds, st, a);
+        hipLaunchKernelGGL((k_adjoint_mom<true, NM, DB, PIECE>), grid, dim3(kBlock), lds, st, a);
     else
-        hipLaunchKernelGGL((k_adjoint_mom<false, NM, DB>), grid, dim3(kBlock), lds, st, a);
+        hipLaunchKernelGGL((k_adjoint_mom<false, NM, DB, PIECE>), grid, dim3(kBlock), lds, st, a);
     return hipGetLastError();
 }
 
 template <int NM>
-static hipError_t launch_adjoint_mom(const SmoothArgs& a, int64_t patch_blocks, size_t lds, bool dbuf, hipStream_t st)
+static hipError_t launch_adjoint_mom(SmoothArgs a, int64_t patch_blocks, size_t lds, bool dbuf, int64_t piece,
+                                     hipStream_t st)
 {
     if (lds < adj_mom_lds(dbuf ? 2 : 1, a.rows, NM, a.mlen)) return hipErrorInvalidValue;
-    // one thread per (scan point, 4 bins of a correlation row)
-    const int64_t n_thr = (int64_t)(a.rx.n * a.ry.n) * (a.mlen / 4);
-    const int64_t blocks = (n_thr + 255) / 256;
-    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    if ((a.T & 3) == 0 && ((uintptr_t)a.grad_out & 15) == 0)
-        hipLaunchKernelGGL((k_adj_moments<NM, true>), dim3((unsigned)blocks), dim3(256), 0, st, a);
-    else
-        hipLaunchKernelGGL((k_adj_moments<NM, false>), dim3((unsigned)blocks), dim3(256), 0, st, a);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const dim3 grid((unsigned)patch_blocks, (unsigned)a.n_split);
-    return dbuf ? launch_adjoint_gather<NM, true>(a, grid, lds, st) : launch_adjoint_gather<NM, false>(a, grid, lds, st);
+    const int64_t S = (int64_t)a.rx.n * a.ry.n;
+    for (int64_t s0 = 0; s0 < S; s0 += piece) {
+        a.s0 = (int32_t)s0;
+        a.sn = (int32_t)(S - s0 < piece ? S - s0 : piece);
+        // one thread per (scan point, 4 bins of a correlation row)
+        const int64_t blocks = ((int64_t)a.sn * (a.mlen / 4) + 255) / 256;
+        if (blocks * 256 > UINT32_MAX) return hipErrorInvalidValue;
+        if ((a.T & 3) == 0 && ((uintptr_t)a.grad_out & 15) == 0)   // (then so is every piece's)
+            hipLaunchKernelGGL((k_adj_moments<NM, true>), dim3((unsigned)blocks), dim3(256), 0, st, a);
+        else
+            hipLaunchKernelGGL((k_adj_moments<NM, false>), dim3((unsigned)blocks), dim3(256), 0, st, a);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        const dim3 grid((unsigned)patch_blocks, (unsigned)a.n_split);
+        if (piece >= S)
+            e = dbuf ? launch_adjoint_gather<NM, true, false>(a, grid, lds, st)
+                     : launch_adjoint_gather<NM, false, false>(a, grid, lds, st);
+        else
+            e = dbuf ? launch_adjoint_gather<NM, true, true>(a, grid, lds, st)
+                     : launch_adjoint_gather<NM, false, true>(a, grid, lds, st);
+        if (e != hipSuccess) return e;
+        a.grad_out += (size_t)a.sn * a.T;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_adjoint_moments(const SmoothArgs& a, const MomentFit& f, int64_t patch_blocks, size_t lds, bool dbuf,
-                                  hipStream_t st)
+                                  int64_t piece, hipStream_t st)
 {
     if (patch_blocks <= 0) return hipSuccess;
-    if (patch_blocks > 0x7fffffff || a.n_split > 65535 || a.rows < 1 || a.mlen != adj_row_bins(a.T, a.Rs))
+    if (patch_blocks > 0x7fffffff || a.n_split > 65535 || a.rows < 1 || a.mlen != adj_row_bins(a.T, a.Rs) || piece < 1)
         return hipErrorInvalidValue;
     const hipError_t e = launch_smooth_prep(a, f, true, st);
     if (e != hipSuccess) return e;
     switch (f.n) {
-    case 6: return launch_adjoint_mom<6>(a, patch_blocks, lds, dbuf, st);
-    case 7: return launch_adjoint_mom<7>(a, patch_blocks, lds, dbuf, st);
-    case 8: return launch_adjoint_mom<8>(a, patch_blocks, lds, dbuf, st);
-    case 9: return launch_adjoint_mom<9>(a, patch_blocks, lds, dbuf, st);
+    case 6: return launch_adjoint_mom<6>(a, patch_blocks, lds, dbuf, piece, st);
+    case 7: return launch_adjoint_mom<7>(a, patch_blocks, lds, dbuf, piece, st);
+    case 8: return launch_adjoint_mom<8>(a, patch_blocks, lds, dbuf, piece, st);
+    case 9: return launch_adjoint_mom<9>(a, patch_blocks, lds, dbuf, piece, st);
     }
     return hipErrorInvalidValue;
 }

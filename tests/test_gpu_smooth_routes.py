@@ -82,3 +82,35 @@ def test_correlations_keep_to_their_support():
     assert away.any() and not away.all()
     assert np.isfinite(gr[away]).all() and not gr[away].any()
     assert not np.isfinite(gr[~away][:, 3]).any()
+
+
+def test_adjoint_in_pieces():
+    """A scan whose correlation rows take more than 4 GiB goes in pieces:
+    sampled records against the oracle, an upstream gradient in the first and
+    last piece only adding up to that of both."""
+    import torch
+    import paper_2506_03747_amd as nl
+    sc = smooth_scene(761, scan=(300, 270), patches=(44, 40), n_bins=2000, bin_ps=3.1,
+                      fwhm_ps=3.1 * 2.65 * 2.3548200450309493)
+    prm = nl.params_of(sc)
+    plan = host_plans.adjoint_plan(prm, sc.n_patch_total)
+    one = -(-plan["head_bytes"] // sc.n_scan)
+    assert plan["moments"] == 7 and one < 7 * 4 * sc.n_bins     # not every scan point's rows are held
+    depth, albedo, mask = to_gpu(sc)
+    rec, n = nl.patches_from_depth(depth, sc.patch_grid, albedo, mask)
+    k = int(n.item())
+    G = np.zeros((sc.n_scan, sc.n_bins), np.float32)
+    rng = np.random.default_rng(761)
+    rows = np.r_[0:150, sc.n_scan // 2:sc.n_scan // 2 + 150, sc.n_scan - 150:sc.n_scan]
+    G[rows] = rng.standard_normal((rows.size, sc.n_bins))
+    got = nl.adjoint(prm, rec, n, torch.from_numpy(G).cuda())[:k].cpu().numpy().astype(np.float64)
+    idx = rec[:k].cpu().numpy()[:, 7].view(np.int32)
+    some = rng.choice(k, 48, replace=False)
+    want = oracle.adjoint_records(sc, G.astype(np.float64), subset=idx[some])
+    _assert_record_grads(got[some], want, "adjoint in pieces")
+    parts = []
+    for part in (rows[:150], rows[150:300], rows[300:]):
+        g = torch.zeros((sc.n_scan, sc.n_bins), device="cuda")
+        g[torch.from_numpy(part).cuda()] = torch.from_numpy(G[part]).cuda()
+        parts.append(nl.adjoint(prm, rec, n, g)[:k].cpu().numpy().astype(np.float64))
+    assert np.linalg.norm(sum(parts) - got) <= 1e-6 * np.linalg.norm(got)

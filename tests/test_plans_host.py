@@ -1,4 +1,5 @@
 """The plans that the library's host side chooses, without a GPU."""
+import ctypes as C
 import random
 
 import pytest
@@ -85,3 +86,16 @@ def test_smooth_points_per_workgroup_exist(nx, points):
     gets no more than it has along x."""
     plan = smooth_plan(params(nx, 4000 // nx, 400, 8.0, 50.0), 5000)
     assert plan["moments"] == 6 and plan["tx"] == points
+
+
+def test_adjoint_workspace_is_bounded():
+    """The correlations' share of the workspace stays within 4 GiB however
+    many scan points there are (the rest is the records' partials)."""
+    nat = host_plans._native
+    for scan, T, fwhm in (((512, 512), 2048, 83.0), ((2000, 1000), 1024, 50.0), ((256, 256), 3300, 160.0)):
+        prm = params(*scan, T, 8.0, fwhm)
+        plan = adjoint_plan(prm, 10000)
+        assert plan["moments"] and plan["head_bytes"] <= (4 << 30) + (1 << 20), plan
+        need = C.c_size_t(0)
+        assert nat.lib().nlos_adjoint_workspace_bytes(C.byref(prm), 10000, C.byref(need)) == 0
+        assert need.value == plan["head_bytes"] + plan["split"] * 10000 * 40
