@@ -768,7 +768,8 @@ bool smooth_plan_moments(const nlos_params* p, int32_t n_patches, int rs, Smooth
     sp->n_blocks = sp->tiles * sv;
     sp->lds = 0;
     sp->stride = T;
-    return true;
+    // (a launch has fewer than 2^32 threads; the taps' tiles hold more points)
+    return sp->n_blocks * nlos::kBlock <= (int64_t)UINT32_MAX;
 }
 
 // By taps, where a histogram of T bins fits in LDS.

@@ -99,3 +99,12 @@ def test_adjoint_workspace_is_bounded():
         need = C.c_size_t(0)
         assert nat.lib().nlos_adjoint_workspace_bytes(C.byref(prm), 10000, C.byref(need)) == 0
         assert need.value == plan["head_bytes"] + plan["split"] * 10000 * 40
+
+
+@pytest.mark.parametrize("scan,T", [((2050, 2050), 1000), ((4096, 4096), 100), ((2048, 2047), 1000)])
+def test_smooth_launch_holds_every_scan(scan, T):
+    """One launch has fewer than 2^32 threads: scans whose moment rows would need
+    more workgroups of 1024 than that allows go by taps."""
+    plan = smooth_plan(params(*scan, T, 8.0, 50.0), 5000)
+    assert plan["workgroups"] * 1024 < 1 << 32
+    assert (plan["moments"] > 0) == (scan == (2048, 2047))
