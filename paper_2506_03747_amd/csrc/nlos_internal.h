@@ -413,6 +413,17 @@ hipError_t launch_noise_scale(const float* tau, int64_t n, double nr_db, double*
 hipError_t launch_poisson(const float* tau, int64_t n, const double* sigma_n, uint64_t seed, float* out,
                           hipStream_t st);
 constexpr int kNoiseMomentBlocks = 1024;
+constexpr int kNoiseBlock = 256;
+constexpr int kNoiseTile = 2048;   // elements per workgroup (their places fit 16 bits)
+// Elements per workgroup of the sampler: whole tiles fill their wavefronts best;
+// short ones where whole ones would leave CUs idle.
+inline int noise_tile(int64_t n) { return n >= (int64_t)1024 * kNoiseTile ? kNoiseTile : kNoiseBlock; }
+// Elements of the next launch of `left` ones: a launch has fewer than 2^32 threads.
+inline int64_t noise_launch(int64_t left, int tile)
+{
+    const int64_t most = (int64_t)(UINT32_MAX / kNoiseBlock) * tile;
+    return left < most ? left : most;
+}
 
 // By samples: pixels in any order, their count and largest weight.
 struct LctPixel {

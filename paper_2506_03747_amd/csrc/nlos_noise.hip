@@ -20,12 +20,11 @@
 
 #include <cstdint>
 
+#include "nlos_internal.h"
+
 namespace nlos {
 
 namespace {
-
-constexpr int kNoiseBlock = 256;
-constexpr int kNoiseTile = 2048;   // elements per workgroup (their places fit 16 bits)
 
 struct Moments {
     double n, mean, m2;
@@ -319,7 +318,7 @@ __device__ int64_t ptrs_count(double lam, uint64_t seed, int64_t i, uint64_t c[4
 // with each proposal's generator run again for the exact test; tiles of 512,
 // 1024 and 4096 elements are 1.4, 1.04 and 1.1 times slower).
 __global__ void __launch_bounds__(kNoiseBlock)
-    k_poisson(const float* tau, int64_t n, int tile, const double* sigma_n, uint64_t seed, float* out)
+    k_poisson(const float* tau, int64_t n, int tile, int64_t first, const double* sigma_n, uint64_t seed, float* out)
 {
     __shared__ float st[kNoiseTile];
     __shared__ uint16_t list[kNoiseTile], rest[kNoiseTile];
@@ -369,7 +368,7 @@ __global__ void __launch_bounds__(kNoiseBlock)
         const int e = rej ? list[m - 1 - j] : list[j];
         const double lam = (double)st[e] * sn;
         uint64_t c[4];
-        philox4x64_10(c, base + e, 0ull, seed);
+        philox4x64_10(c, first + base + e, 0ull, seed);
         int64_t got;
         if (!rej) {
             got = poisson_inversion(lam, uniform_of(c[0]));
@@ -383,7 +382,7 @@ __global__ void __launch_bounds__(kNoiseBlock)
                     rest[atomicAdd(&count[2], 1)] = (uint16_t)e;
                     continue;
                 }
-                got = ptrs_count(lam, seed, base + e, c);
+                got = ptrs_count(lam, seed, first + base + e, c);
             }
         }
         out[base + e] = (float)((double)got / sn);
@@ -394,8 +393,8 @@ __global__ void __launch_bounds__(kNoiseBlock)
     for (int j = tid; j < n_rest; j += kNoiseBlock) {
         const int e = rest[j];
         uint64_t c[4];
-        philox4x64_10(c, base + e, 0ull, seed);
-        out[base + e] = (float)((double)ptrs_count((double)st[e] * sn, seed, base + e, c) / sn);
+        philox4x64_10(c, first + base + e, 0ull, seed);
+        out[base + e] = (float)((double)ptrs_count((double)st[e] * sn, seed, first + base + e, c) / sn);
     }
 }
 
@@ -413,13 +412,17 @@ hipError_t launch_poisson(const float* tau, int64_t n, const double* sigma_n, ui
                           hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    // whole tiles fill their wavefronts best; short ones where whole ones would
-    // leave CUs idle
-    const int tile = n >= (int64_t)1024 * kNoiseTile ? kNoiseTile : kNoiseBlock;
-    const int64_t blocks = (n + tile - 1) / tile;
-    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_poisson, dim3((unsigned)blocks), dim3(kNoiseBlock), 0, st, tau, n, tile, sigma_n, seed, out);
-    return hipGetLastError();
+    // element i's uniforms belong to i, whichever launch draws it
+    const int tile = noise_tile(n);
+    for (int64_t first = 0; first < n;) {
+        const int64_t m = noise_launch(n - first, tile);
+        hipLaunchKernelGGL(k_poisson, dim3((unsigned)((m + tile - 1) / tile)), dim3(kNoiseBlock), 0, st, tau + first, m,
+                           tile, first, sigma_n, seed, out + first);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        first += m;
+    }
+    return hipSuccess;
 }
 
 }  // namespace nlos

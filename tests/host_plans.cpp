@@ -52,3 +52,17 @@ extern "C" int host_adjoint_plan(const nlos_params* p, int32_t n_patches, int64_
     std::memcpy(out, v, sizeof(v));
     return NLOS_OK;
 }
+
+// Launches of the noise sampler over n elements: their number; the largest one's threads.
+extern "C" int64_t host_noise_launches(int64_t n, int64_t* threads)
+{
+    const int tile = nlos::noise_tile(n);
+    int64_t count = 0;
+    *threads = 0;
+    for (int64_t first = 0; first < n; ++count) {
+        const int64_t m = nlos::noise_launch(n - first, tile);
+        *threads = std::max<int64_t>(*threads, (m + tile - 1) / tile * nlos::kNoiseBlock);
+        first += m;
+    }
+    return count;
+}

@@ -108,3 +108,14 @@ def test_smooth_launch_holds_every_scan(scan, T):
     plan = smooth_plan(params(*scan, T, 8.0, 50.0), 5000)
     assert plan["workgroups"] * 1024 < 1 << 32
     assert (plan["moments"] > 0) == (scan == (2048, 2047))
+
+
+@pytest.mark.parametrize("n,launches", [(1, 1), ((1 << 21) - 1, 1), (1 << 33, 1), (1 << 35, 2), (70 << 30, 3)])
+def test_noise_launches_hold_every_array(n, launches):
+    """An array of any size that fits the card is drawn in launches of fewer than
+    2^32 threads each."""
+    f = host_plans.lib().host_noise_launches
+    f.restype = C.c_int64
+    threads = C.c_int64(0)
+    assert f(C.c_int64(n), C.byref(threads)) == launches
+    assert 0 < threads.value < 1 << 32
