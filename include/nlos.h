@@ -481,7 +481,7 @@ int nlos_poisson_noise(const float* tau, int64_t n, const double* sigma_n, uint6
  * [j^2, (j+1)^2) divided by (J dz)^3; Gaussian jitter.  Output float
  * [N][N][M].  The convolution is the sum over the volume's samples (at most
  * one per pixel) and the cone's layers, in 64-bit fixed point; its workspace
- * is about 18 N^2 + 8 M bytes, 256-byte aligned.  Thin, wide volumes
+ * is about 34 N^2 + 8 M bytes, 256-byte aligned.  Thin, wide volumes
  * (N^2 > 1500 M) and rows of more than 16384 bins go through fp64 FFTs
  * instead: the first such call for a size creates and keeps an FFT plan (the
  * FFT library allocates its tables then), later calls allocate nothing, a

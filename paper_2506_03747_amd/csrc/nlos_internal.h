@@ -425,16 +425,21 @@ inline int64_t noise_launch(int64_t left, int tile)
     return left < most ? left : most;
 }
 
-// By samples: pixels in any order, their count and largest weight.
-struct LctPixel {
-    double w;        // albedo / (J M)
+// By samples: each pixel's weight, then the present ones in any order.
+struct LctSample {
+    double w;        // albedo / (J M), 0 where absent
     uint32_t c;      // coarse v-sample
-    uint32_t xy;     // x << 16 | y
+    uint32_t pad;
+};
+struct LctPixel {
+    unsigned long long inc;   // round(w 2^62 / sum of all weights)
+    uint32_t c;
+    uint32_t xy;              // x << 16 | y
 };
 struct LctList {
-    unsigned long long max_bits;   // bits of the largest weight
+    double unit;     // an increment's weight (0: no pixels; no number: an infinite weight)
     int32_t n;
-    int32_t ties;                  // 1: an offset has two nearest layers
+    int32_t ties;    // 1: an offset has two nearest layers
 };
 constexpr int kLctPer = 16;             // time bins per thread, through registers
 constexpr int kLctV = 5;                // consecutive outputs per lane in the jitter
@@ -445,10 +450,10 @@ bool lct_by_samples(const LctArgs& a);
 // u64 words per row: M bins, R zeros on either side, odd so that rows of a
 // power of two start on different banks.
 __host__ __device__ inline int lct_pitch(const LctArgs& a) { return (a.M + 2 * a.R) | 1; }
-// Workspace: the cone's table, then the pixels, the time bins' gains and the
-// list's head at these byte offsets.
+// Workspace: the cone's table, then the pixels, the time bins' gains, the list's
+// head, the samples and the weights' sums at these byte offsets.
 struct LctLayout {
-    size_t pix, gain, list, bytes;
+    size_t pix, gain, list, smp, part, bytes;
 };
 LctLayout lct_samples_layout(const LctArgs& a);
 hipError_t launch_lct_samples(const LctArgs& a, void* ws, float* out, hipStream_t st);

@@ -11,8 +11,9 @@
 // transforms spend their time streaming zeros.  Two evaluations:
 //
 //   by samples (lct_by_samples; every size but thin, wide volumes)
-//   k_lct_cone    the cone's layer of each lateral offset |dx|, |dy|.
-//   k_lct_pixels  present pixels: coarse v-sample and weight, compacted.
+//   k_lct_samples each pixel's coarse v-sample and weight, and their sums.
+//   k_lct_list    the cone's layer of each lateral offset |dx|, |dy|; present
+//                 pixels with their weights in fixed point, compacted.
 //   k_lct_sum     a workgroup per row piece of scan points: every pixel's
 //                 weight into the points' LDS rows, then the time resampling,
 //                 the jitter and the write-out.
@@ -171,61 +172,78 @@ __global__ void k_lct_jitter(const LctArgs a, const double* pre, float* out)
 // depends on the offset's squares only): the layer nearest its distance, M
 // when that is past the window, and kLctTie when the next layer is as near.
 constexpr uint32_t kLctTie = 0x8000u;
-constexpr double kLctInt = 4503599627370496.0;   // 2^52
 
-__global__ void __launch_bounds__(256) k_lct_cone(const LctArgs a, uint16_t* tab, double* gain, LctList* list)
+// The samples and the sum of each workgroup's 256 weights.
+__global__ void __launch_bounds__(256) k_lct_samples(const LctArgs a, LctSample* smp, double* part, LctList* list)
 {
-    const int N = a.N, M = a.M;
+    __shared__ double red[4];
     const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (p == 0) {
+        list->n = 0;
+        list->ties = 0;
+    }
+    int c = 0;
+    double w = 0.0;
+    if (p < (int64_t)a.N * a.N) {
+        if (!lct_sample(a, p, &c, &w)) w = 0.0;
+        smp[p] = LctSample{w, (uint32_t)c, 0u};
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) w += __shfl_xor(w, d);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = w;
+    __syncthreads();
+    if (threadIdx.x == 0) part[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
+}
+
+// The sum of all weights, by every workgroup for itself and in the same order
+// everywhere; the cone's table; present pixels, appended in any order (every
+// later sum is of integers), one counter add per wavefront.
+__global__ void __launch_bounds__(256) k_lct_list(const LctArgs a, const LctSample* smp, const double* part,
+                                                  uint16_t* tab, double* gain, LctPixel* pix, LctList* list)
+{
+    __shared__ double red[4];
+    const int N = a.N, M = a.M, lane = (int)threadIdx.x & 63;
+    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const bool in = p < (int64_t)N * N;
+    const LctSample q = in ? smp[p] : LctSample{0.0, 0u, 0u};
+    double total = 0.0;
+    for (unsigned i = threadIdx.x; i < gridDim.x; i += 256) total += part[i];
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) total += __shfl_xor(total, d);
+    if (lane == 0) red[threadIdx.x >> 6] = total;
     for (int64_t j = p; j < M; j += (int64_t)gridDim.x * 256) {
         // time bin j: over the 2 j + 1 fine samples of its span and (J dz)^3
         const double t = (double)(j + 1) * a.dz;
         gain[j] = 1.0 / ((double)(2 * j + 1) * (t * t * t));
     }
-    if (p == 0) {
-        list->n = 0;
-        list->max_bits = 0ull;
-        list->ties = 0;
+    bool tie = false;
+    if (in) {
+        double zs, kf;
+        const double best = lct_cone_best(a, (int)(p / N), (int)(p % N), &zs, &kf);
+        // (a nearest layer of 0 .. M - 1 is kf or kf + 1; past the grid kf >= M)
+        const bool lo = kf < (double)M && fabs(zs - kf / (double)M) == best;
+        const bool hi = kf + 1.0 < (double)M && fabs(zs - (kf + 1.0) / (double)M) == best;
+        tie = lo && hi;
+        uint32_t v = (uint32_t)M;
+        if (hi) v = (uint32_t)kf + 1u;
+        if (lo) v = (uint32_t)kf | (hi ? kLctTie : 0u);
+        tab[p] = (uint16_t)v;
     }
-    if (p >= (int64_t)N * N) return;
-    double zs, kf;
-    const double best = lct_cone_best(a, (int)(p / N), (int)(p % N), &zs, &kf);
-    // (a nearest layer of 0 .. M - 1 is kf or kf + 1; past the grid kf >= M)
-    const bool lo = kf < (double)M && fabs(zs - kf / (double)M) == best;
-    const bool hi = kf + 1.0 < (double)M && fabs(zs - (kf + 1.0) / (double)M) == best;
-    uint32_t v = (uint32_t)M;
-    if (hi) v = (uint32_t)kf + 1u;
-    if (lo) v = (uint32_t)kf | (hi ? kLctTie : 0u);
-    tab[p] = (uint16_t)v;
-}
-
-// Present pixels, appended in any order (every later sum is of integers): one
-// counter add and one maximum per wavefront.  Also whether the table has ties.
-__global__ void __launch_bounds__(256)
-    k_lct_pixels(const LctArgs a, const uint16_t* tab, LctPixel* pix, LctList* list)
-{
-    const int N = a.N;
-    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (p < (int64_t)N * N && (tab[p] & kLctTie)) list->ties = 1;
-    int c = 0;
-    double w = 0.0;
-    const bool on = p < (int64_t)N * N && lct_sample(a, p, &c, &w);
+    if (__any(tie) && lane == 0) list->ties = 1;
+    __syncthreads();
+    // (enlarged by more than its rounding: no sum of increments passes 2^62 + N^2 / 2)
+    total = (((red[0] + red[1]) + red[2]) + red[3]) * (1.0 + 0x1p-24);
+    if (p == 0) list->unit = isfinite(total) ? total * 0x1p-62 : __longlong_as_double(0x7ff8000000000000ll);
+    const bool on = q.w > 0.0;
     const unsigned long long m = __ballot(on);
     if (m == 0ull) return;
-    const int lane = (int)threadIdx.x & 63;
-    double mx = w;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) mx = fmax(mx, __shfl_xor(mx, d));
     int base = 0;
-    if (lane == 0) {
-        base = atomicAdd(&list->n, (int)__popcll(m));
-        // (weights are positive: their bits order as they do)
-        atomicMax(&list->max_bits, (unsigned long long)__double_as_longlong(mx));
-    }
+    if (lane == 0) base = atomicAdd(&list->n, (int)__popcll(m));
     base = __builtin_amdgcn_readfirstlane(base);
     if (on) {
-        const int64_t i = base + __popcll(m & ((1ull << lane) - 1ull));
-        pix[i] = LctPixel{w, (uint32_t)c, (uint32_t)(p / N) << 16 | (uint32_t)(p % N)};
+        const double x = isfinite(total) ? rint(q.w * (0x1p62 / total)) : 0.0;
+        pix[base + __popcll(m & ((1ull << lane) - 1ull))] =
+            LctPixel{(unsigned long long)x, q.c, (uint32_t)(p / N) << 16 | (uint32_t)(p % N)};
     }
 }
 
@@ -234,20 +252,27 @@ __global__ void __launch_bounds__(256)
 // c + layer(|x' - x|, |y' - y|) of each row: per pair a table address, a
 // 16-bit table read (2 N^2 bytes, mostly from the L1; a copy in LDS measured
 // no faster and took the second workgroup's room), add, compare, ds_add_u64.
-// Weights are fixed point, w s rounded to an integer of at most 2^51 with s at
-// most 2^62 / (N^2 max w), so that a row's sums cannot wrap and do not depend
-// on the order: a sample is within 2^-52 of the largest weight (2^-63 N^2
-// where N > 45), below the noise of fp64 transforms.
+// Weights are fixed point, w s rounded to an integer, so that a row's sums do
+// not depend on the order.  s is 2^62 over the sum of all weights: no bin can
+// wrap, a sample is within 2^-63 of that sum, and one bright pixel among dim
+// ones costs them no bits (2^62 / (N^2 max w) did: beside one 10^10 times
+// brighter a pixel kept 16 at N = 64).  Root mean square error of the rows
+// against that of fp64 transforms (smooth surface, albedo 0.05 to 1): before the
+// resampling 0.41 of it at N = 64, 0.57 at 128, 0.92 at 384, 1.65 at 512 (0.8,
+// 1.6, 2.6 and 4.7 with the former scale); after it, relative to the output,
+// 1 to 3 10^-16 against 3 10^-10 to 8 10^-12, as it amplifies the transforms'
+// noise in the first bins.
 // Bound: the LDS adds (bank conflicts included) and VALU, about 15 cycles per
 // wavefront and pair; then the write-out's fp64 resampling and jitter.  128^2
 // points and pixels, 1024 bins: 13.2 ms by transforms; 367 us with 1024
 // threads, a table read and add at a time; 220 us with the reads of all rows
-// before the adds and the jitter from a sliding window; 170 us (back to back) with four
+// before the adds and the jitter from a sliding window; 168 us (back to back) with four
 // workgroups of 512 threads per CU, so that one's write-out runs under
-// another's adds.
+// another's adds; 163 with the weights made integers once per pixel instead of
+// once per workgroup.
 template <int NP, bool TIES>
 __device__ __forceinline__ void lct_add(const LctPixel* __restrict__ pix, int n, const uint16_t* __restrict__ tab,
-                                        int N, int M, int x1, int y1, double s,
+                                        int N, int M, int x1, int y1,
                                         unsigned long long* rows, int pitch, int tid, int nthr)
 {
     if (tid >= n) return;
@@ -255,9 +280,7 @@ __device__ __forceinline__ void lct_add(const LctPixel* __restrict__ pix, int n,
     for (int i = tid; i < n; i += nthr) {
         const int x = (int)(q.xy >> 16), y = (int)(q.xy & 0xffffu);
         const uint32_t c = q.c;
-        // round(w s) < 2^51 as the low bits of w s + 2^52
-        const unsigned long long inc =
-            (unsigned long long)__double_as_longlong(fma(q.w, s, kLctInt)) & 0x000fffffffffffffull;
+        const unsigned long long inc = q.inc;
         q = pix[min(i + nthr, n - 1)];   // the next one lands while this one is added
         const int row = abs(x1 - x) * N;
         // every row's table entry before any add, so that one wait serves all
@@ -290,21 +313,18 @@ __global__ void __launch_bounds__(1024) k_lct_sum(const LctArgs a, const uint16_
     const int nt = (N + NP - 1) / NP;
     const int x1 = (int)blockIdx.x / nt, y1 = (int)(blockIdx.x % nt) * NP;
     const int n = list->n;
-    const double wmax = __longlong_as_double((long long)list->max_bits);
-    const double per = fmin(4611686018427387904.0 / ((double)N * (double)N), 2251799813685248.0);
-    const double s = wmax > 0.0 ? per / wmax : 0.0;
+    const double unit = list->unit;
     for (int i = tid; i < NP * pitch; i += nthr) rows[i] = 0ull;
     const bool ties = list->ties != 0;
     __syncthreads();
     if (ties)
-        lct_add<NP, true>(pix, n, tab, N, M, x1, y1, s, rows + R, pitch, tid, nthr);
+        lct_add<NP, true>(pix, n, tab, N, M, x1, y1, rows + R, pitch, tid, nthr);
     else
-        lct_add<NP, false>(pix, n, tab, N, M, x1, y1, s, rows + R, pitch, tid, nthr);
+        lct_add<NP, false>(pix, n, tab, N, M, x1, y1, rows + R, pitch, tid, nthr);
     __syncthreads();
     // time bin j: the mean over its fine v-span [j^2, (j + 1)^2) (at most three
     // coarse samples), over (J dz)^3; in place, through registers
     // (an infinite weight leaves no number anywhere, as the transforms do)
-    const double inv = !(wmax > 0.0) ? 0.0 : isfinite(wmax) ? wmax / per : __longlong_as_double(0x7ff8000000000000ll);
     const int lm = 31 - __clz(M);
     double pre[kLctPer];
 #pragma unroll
@@ -318,7 +338,7 @@ __global__ void __launch_bounds__(1024) k_lct_sum(const LctArgs a, const uint16_
         const int c0 = lo >> lm, c1 = (hi - 1) >> lm;
         double sum = 0.0;
         for (int c = c0; c <= c1; ++c) sum += (double)(min(hi, (c + 1) << lm) - max(lo, c << lm)) * (double)col[c];
-        pre[e] = sum * inv * gain[j];
+        pre[e] = sum * unit * gain[j];
     }
     __syncthreads();
     double* rowd = reinterpret_cast<double*>(rows);
@@ -391,7 +411,9 @@ LctLayout lct_samples_layout(const LctArgs& a)
     l.pix = (n2 * 2 + 255) & ~(size_t)255;
     l.gain = l.pix + ((n2 * sizeof(LctPixel) + 255) & ~(size_t)255);
     l.list = l.gain + (((size_t)a.M * 8 + 255) & ~(size_t)255);
-    l.bytes = l.list + 256;
+    l.smp = l.list + 256;
+    l.part = l.smp + ((n2 * sizeof(LctSample) + 255) & ~(size_t)255);
+    l.bytes = l.part + (((n2 + 255) / 256 * 8 + 255) & ~(size_t)255);
     return l;
 }
 
@@ -403,7 +425,8 @@ static hipError_t launch_lct_sum(const LctArgs& a, const LctShape& sh, const uin
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh.lds);
     if (e != hipSuccess) return e;
     const unsigned blocks = (unsigned)(a.N * ((a.N + NP - 1) / NP));
-    hipLaunchKernelGGL(k_lct_sum<NP>, dim3(blocks), dim3((unsigned)sh.threads), sh.lds, st, a, tab, pix, gain, list, out);
+    hipLaunchKernelGGL(k_lct_sum<NP>, dim3(blocks), dim3((unsigned)sh.threads), sh.lds, st, a, tab, pix, gain,
+                       list, out);
     return hipGetLastError();
 }
 
@@ -418,11 +441,13 @@ hipError_t launch_lct_samples(const LctArgs& a, void* ws, float* out, hipStream_
     const LctShape sh = lct_shape(a);
     if (a.M > kLctMaxRow || a.N > 65535 || sh.lds > kLctLds || sh.np * a.M > sh.threads * kLctPer)
         return hipErrorInvalidValue;
+    LctSample* smp = reinterpret_cast<LctSample*>(w + l.smp);
+    double* part = reinterpret_cast<double*>(w + l.part);
     const unsigned nb = (unsigned)(((int64_t)a.N * a.N + 255) / 256);
-    hipLaunchKernelGGL(k_lct_cone, dim3(nb), dim3(256), 0, st, a, tab, gain, list);
+    hipLaunchKernelGGL(k_lct_samples, dim3(nb), dim3(256), 0, st, a, smp, part, list);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_lct_pixels, dim3(nb), dim3(256), 0, st, a, tab, pix, list);
+    hipLaunchKernelGGL(k_lct_list, dim3(nb), dim3(256), 0, st, a, smp, part, tab, gain, pix, list);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     switch (sh.np) {
     case 8: return launch_lct_sum<8>(a, sh, tab, pix, gain, list, out, st);
