@@ -2,10 +2,13 @@
 
 For each class of problems (confocal or not, window length, number of
 histograms) it forces every supported unit shape in turn through the tuning
-table, times the forward operator on a seeded synthetic scene of that class
-(HIP events, median of repeated launches), and keeps the fastest if it beats
-the library's own plan by more than 2%.  The result is written as a JSON table that the package installs at import
-(``load_tuning``); ``python -m paper_2506_03747_amd.autotune [out.json]``.
+table, two units to a workgroup, and times the forward operator on a seeded
+synthetic scene of that class, alone and as a list of three (HIP events, median
+of repeated launches): an entry governs both.  A unit becomes an entry if it
+beats the library's own plans by more than 2% in one and is not more than 2%
+slower in the other.  The result is written as a JSON table that the package
+installs at import (``load_tuning``);
+``python -m paper_2506_03747_amd.autotune [out.json]``.
 
 Timing only chooses among shapes the library already supports; every shape
 computes the same result (the GPU tests force each one and compare them
@@ -18,7 +21,7 @@ import sys
 
 import numpy as np
 
-from . import forward, get_plan, make_params, out_shape, patches_from_depth, reset_tuning, set_tuning
+from . import Batcher, forward, forward_batched, get_plan, make_params, out_shape, patches_from_depth, reset_tuning, set_tuning
 
 CONFOCAL_UNITS = [(1, 4, 4), (1, 4, 2), (1, 2, 2), (1, 2, 1)]
 NONCONFOCAL_UNITS = [(2, 2, 2), (2, 1, 2), (1, 1, 2)]
@@ -66,34 +69,56 @@ def _time(fn, reps=7):
     return float(np.median(ts))
 
 
+def choose(own, timings):
+    """The unit to enter, or None: ``own`` is the library's plans' (alone, list)
+    times, ``timings`` {unit: (alone, list)}."""
+    best = None
+    for unit, got in timings.items():
+        r = [g / o for g, o in zip(got, own)]
+        if min(r) < 0.98 and max(r) <= 1.02 and (best is None or r[0] * r[1] < best[0]):
+            best = (r[0] * r[1], unit)
+    return best[1] if best else None
+
+
 def tune(n_patch=192, classes=CLASSES, verbose=True):
     """Time every unit per class; returns (table entries, all timings)."""
     import torch
     entries, report = [], []
+    batcher = Batcher()
     try:
         for k, cls in enumerate(classes):
             prm, rec, n = _scene(cls, n_patch, seed=1000 + k)
-            out = torch.empty(out_shape(prm), dtype=torch.float32, device="cuda")
+            outs = [torch.empty(out_shape(prm), dtype=torch.float32, device="cuda") for _ in range(3)]
             key = {f: cls[f] for f in ("confocal", "t_min", "t_max", "h_min", "h_max")}
+
+            def both():
+                return (_time(lambda: forward(prm, rec, n, out=outs[0])),
+                        _time(lambda: forward_batched([(prm, rec, n, o) for o in outs], batcher)))
+
             set_tuning([])
-            own = _time(lambda: forward(prm, rec, n, out=out))
-            best = None
+            own, timings, rows = both(), {}, []
             for unit in (CONFOCAL_UNITS if cls["confocal"] else NONCONFOCAL_UNITS):
                 set_tuning([dict(key, tl=unit[0], tx=unit[1], ty=unit[2])])
                 plan = get_plan(prm, rec.shape[0])
-                if (plan["tl"], plan["tx"], plan["ty"]) != unit:
-                    continue            # histograms of this unit do not fit in LDS at this window
-                ms = _time(lambda: forward(prm, rec, n, out=out))
-                report.append(dict(key, T=cls["T"], scan=cls["scan"], lasers=cls["lasers"], unit=list(unit),
-                                   ms=ms, plan=plan))
+                # (its plan is the library's own where two of the units do not fit in LDS)
+                if (plan["tl"], plan["tx"], plan["ty"]) == unit:
+                    timings[unit] = both()
+                    rows.append((unit, plan, timings[unit]))
+            # (the library's own plans at both ends: the first timings of a class run
+            # 1 to 2% slow)
+            set_tuning([])
+            own = tuple(map(min, own, both()))
+            rows.insert(0, (None, get_plan(prm, rec.shape[0]), own))
+            for unit, plan, (ms, list_ms) in rows:
+                report.append(dict(key, T=cls["T"], scan=cls["scan"], lasers=cls["lasers"],
+                                   unit=None if unit is None else list(unit), ms=ms, list_ms=list_ms, plan=plan))
                 if verbose:
                     print(f"class {k} T={cls['T']} scan={cls['scan']}^2 lasers={cls['lasers']}^2 "
-                          f"unit={unit}: {ms:.4f} ms  {plan}", flush=True)
-                if best is None or ms < best[0]:
-                    best = (ms, unit)
-            if best and best[0] < 0.98 * own:
-                entries.append(dict(key, tl=best[1][0], tx=best[1][1], ty=best[1][2]))
-            del out
+                          f"unit={unit or 'own'}: {ms:.4f} ms, list of 3 {list_ms:.4f} ms  {plan}", flush=True)
+            unit = choose(own, timings)
+            if unit:
+                entries.append(dict(key, tl=unit[0], tx=unit[1], ty=unit[2]))
+            del outs
     finally:
         reset_tuning()
     return entries, report
