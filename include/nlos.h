@@ -504,10 +504,11 @@ int nlos_lct_forward(const nlos_params* p, const float* depth, const float* albe
  * plan with the least estimated time (one or two units per workgroup, one or
  * two workgroups per CU); in a list of requests (batched calls, ticks) the
  * largest unit of which two fit and that still gives each request its share
- * of workgroups, or the least estimate where none does or the request is the
- * list's only one; a list splits a request's patches over workgroups (whose
- * parts meet in float atomics) only where the call alone does.  The table is the library's only shared state: it is
- * copied, read under a lock, and replaced as a whole.
+ * of workgroups, or the least estimate on that share where that is clearly
+ * lower, none does, or the request is the list's only one; a list splits a
+ * request's patches over workgroups (whose parts meet in float atomics) only
+ * where the call alone does.  The table is the library's only shared state: it
+ * is copied, read under a lock, and replaced as a whole.
  */
 typedef struct nlos_tuning_entry {
     int32_t confocal;        /* 1: confocal, 0: non-confocal */
@@ -518,7 +519,8 @@ typedef struct nlos_tuning_entry {
 
 typedef struct nlos_plan_info {
     int32_t tl, tx, ty;      /* unit */
-    int32_t pair;            /* 1: one or two units per workgroup over the whole window */
+    int32_t pair;            /* 1: one or two units per workgroup over the whole window
+                                (workgroups / n_split tells which: as many as units, or half) */
     int32_t n_split;         /* patch ranges per workgroup's units */
     int32_t n_windows;       /* time windows (1 unless a histogram exceeds LDS) */
     int64_t workgroups;

@@ -161,9 +161,8 @@ int64_t stats_count(int32_t n_patches) { return ((int64_t)n_patches + nlos::kSta
 // whole window takes the plan with the least estimated time (plan_solo).  In a
 // list of requests, or with a unit named by the tuning table, a workgroup owns
 // two units: of the named shape, patches split over workgroups when they are
-// fewer than the target; else of the largest shape that gives the target of
-// workgroups, or what plan_share estimates where none does.  Longer histograms:
-// one per workgroup over a window of bins.
+// fewer than the target; else what plan_share estimates.  Longer histograms: one
+// per workgroup over a window of bins.
 // Tuning table (nlos_set_tuning): the unit shape to use per (geometry,
 // window length, histogram count) class, found by measurement.  Read under a
 // lock by every plan; replaced as a whole.
@@ -277,16 +276,22 @@ int plan_solo(const nlos_params* p, int32_t n_patches, int stride, nlos::Plan* p
     return any && plan->n_blocks <= 0x7fffffff ? NLOS_OK : NLOS_EINVAL;
 }
 
-// Unit shape and split of a list's only request, or of one whose share of
-// workgroups no shape that fits gives: the least estimate on `target` CUs.  The patches are
-// split only where the call alone splits them too (its estimate has all CUs),
-// so that both give the same bits wherever the call alone has no float atomics.
+// Unit shape and split of a list's request whose share of the CUs is `target`;
+// *chosen: the largest shape that gives as many workgroups, -1: none does.  The
+// least estimate on that many CUs; but where a shape gives the share, it stays
+// unless the estimate is a fifth lower, as the last round of one request's
+// workgroups is filled by the next one's (the only request has no next).  The
+// patches are split only where the call alone splits them too (its estimate has
+// all CUs), so that both give the same bits wherever the call alone has no float
+// atomics.
 // A tick of one request of 16 x 16 points, 128 x 128 pixels, 512 bins takes 97 us
 // with the largest unit split 16 ways, 37 so; of 8 x 8 points, 256 x 256 pixels,
 // 1024 bins 237 and 54; of 25 x 22 points, 84 x 19 pixels, 895 bins 39 with the
-// largest shape that gives 256 workgroups, 33 so.  Lists whose requests all have
-// a shape that gives their share are left to that rule (8 requests of 32^2 to
-// 128^2 points 469 us both ways).
+// largest shape that gives 256 workgroups, 33 so.  60 random lists of 1 to 6
+// requests of 2^2 to 48^2 points: 1.57 times faster than by the largest shape that
+// gives the share or splits; 39 of 2 to 10 requests of 32^2 to 128^2 points the
+// same within 3%.
+constexpr double kShareMargin = 0.8;
 void plan_share(const nlos_params* p, int32_t n_patches, int stride, int64_t target, int* chosen, int64_t* split)
 {
     const bool conf = is_confocal(p);
@@ -294,7 +299,8 @@ void plan_share(const nlos_params* p, int32_t n_patches, int stride, int64_t tar
     const int64_t L = conf ? 1 : (int64_t)p->laser.nx * p->laser.ny;
     nlos::Plan alone;
     const bool may_split = plan_solo(p, n_patches, stride, &alone) == NLOS_OK && alone.n_split > 1;
-    double best = 0.0;
+    const int rule = *chosen;
+    double best = 0.0, kept = 0.0;
     bool any = false;
     for (int i = 0; i < (conf ? 5 : 4); ++i) {
         const Cand& c = cands[i];
@@ -306,12 +312,17 @@ void plan_share(const nlos_params* p, int32_t n_patches, int stride, int64_t tar
             may_split ? std::max<int64_t>(1, std::min<int64_t>(target / groups, n_patches / nlos::kBlock)) : 1;
         for (int64_t sp = 1; sp <= most; sp += std::max<int64_t>(1, most - 1)) {
             const double t = plan_cost(p, 0.6 * (double)n_patches, c, 2, false, units, sp, target);
+            if (i == rule && sp == 1) kept = t;
             if (any && t >= best) continue;
             any = true;
             best = t;
             *chosen = i;
             *split = sp;
         }
+    }
+    if (rule >= 0 && target < kTargetBlocks && best > kShareMargin * kept) {
+        *chosen = rule;
+        *split = 1;
     }
 }
 
@@ -351,20 +362,18 @@ int make_plan(const nlos_params* p, int32_t n_patches, int R, int64_t target, bo
         return ((L + c.tl - 1) / c.tl) * (int64_t)((p->relay.nx + c.tx - 1) / c.tx) *
                (int64_t)((p->relay.ny + c.ty - 1) / c.ty);
     };
-    // (a list of one request has all CUs, where the last round of workgroups counts)
-    const bool estimate = !solo && !forced && target >= kTargetBlocks;
     int chosen = -1, largest = -1;
     for (int i = 0; i < nc; ++i) {
         const int slots = 2 * cands[i].tl * cands[i].tx * cands[i].ty;
         if (nlos::lds_bytes_for(slots, stride_of(T), q_cap) > kLdsMax) continue;
         if (largest < 0) largest = i;
-        if ((forced && i == 0) || (!estimate && (units_of(cands[i]) + 1) / 2 >= target)) {
+        if ((forced && i == 0) || (units_of(cands[i]) + 1) / 2 >= target) {
             chosen = i;
             break;
         }
     }
     int64_t share_split = 0;   // from plan_share
-    if (chosen < 0 && largest >= 0 && !solo && !forced)
+    if (largest >= 0 && !solo && !forced)
         plan_share(p, n_patches, stride_of(T), target, &chosen, &share_split);
     if (chosen < 0) chosen = largest;
     int tw = T, n_tw = 1, pair = 1;
