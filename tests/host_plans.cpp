@@ -66,3 +66,18 @@ extern "C" int64_t host_noise_launches(int64_t n, int64_t* threads)
     }
     return count;
 }
+
+// The smooth kernels' polynomials at width sigma (bins), with one term more for
+// the adjoint: their terms (0: by taps), nodes and coefficients.
+extern "C" int host_moment_fit(double sigma, int32_t adjoint, double* node, double* coef)
+{
+    int n = nlos::smooth_moments(sigma);
+    if (n == 0) return 0;
+    if (adjoint) n = nlos::adj_moments(n);
+    const nlos::MomentFit f = moment_fit(sigma, (int)std::ceil(6.0 * sigma), n);
+    for (int m = 0; m < n; ++m) {
+        node[m] = f.node[m];
+        for (int j = 0; j < n; ++j) coef[m * n + j] = f.coef[m * nlos::kMaxMoments + j];
+    }
+    return n;
+}

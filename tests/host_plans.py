@@ -58,3 +58,10 @@ def adjoint_plan(prm, n_patches):
     rc = lib().host_adjoint_plan(C.byref(prm), n_patches, out)
     assert rc == 0, rc
     return dict(zip(ADJOINT, out))
+
+
+def moment_fit(sigma, adjoint):
+    """(nodes, coefficients [m][j]) of the smooth kernels' polynomials, or None: by taps."""
+    node, coef = (C.c_double * 16)(), (C.c_double * 256)()
+    n = lib().host_moment_fit(C.c_double(sigma), int(adjoint), node, coef)
+    return (list(node)[:n], [list(coef)[m * n:(m + 1) * n] for m in range(n)]) if n else None
