@@ -224,9 +224,10 @@ __device__ __attribute__((noinline)) void guard_overflow(u64* hist_row, const fl
 // Guard pairs: every pair whose fp32 bin lies in 0 .. Tl is added there; the
 // pairs whose fp32 arrival lies within the guard band of a bin edge (lane
 // mask `m`, uniform, every lane of the wavefront present) are also queued and
-// moved to their fp64 bin after the pair loop.  Each wavefront appends to its
-// own queue segment (qw entries) and keeps the fill `qn`, uniform, in a
-// register, so a push waits for nothing.  A full segment corrects in place.
+// moved to their fp64 bin by a drain: between chunks once half the segment is
+// full, and after the pair loop.  Each wavefront appends to its own queue
+// segment (qw entries) and keeps the fill `qn`, uniform, in a register, so a
+// push waits for nothing.  A segment that fills within a chunk corrects in place.
 __device__ __forceinline__ void guard_push(const Lds& L, const FwdArgs& a, uint64_t m, int p, int j, int kf,
                                            uint32_t inc, int hb, int Tl, int wave, int qw, int& qn)
 {
@@ -266,8 +267,9 @@ __device__ __forceinline__ float fast_arrival(const FwdArgs& a, const Lds& L, fl
     return ll.rr + ld.rr;
 }
 
-// After the wavefront's pair loop: its own segment (qn entries), one entry
-// per lane; other wavefronts may still be adding (all adds commute).  The
+// Between two chunks, or after the wavefront's pair loop: its own segment (qn
+// entries), one entry per lane; other wavefronts may still be adding (all adds
+// commute).  The
 // coordinates come from the stream the pair loop read (records, or their
 // pair-loop constants, which keep them as recorded).
 template <bool CONF>
@@ -283,9 +285,6 @@ __device__ __forceinline__ void guard_drain(const Lds& L, const FwdArgs& a, int 
         guard_fix(L.hist + (size_t)j * a.stride, kf, ke, Tl, q.y);
     }
 }
-
-// Load patch p of [pb, pe) or, past the range, a stand-in patch whose arrival
-// lies at least 64 bins past the window (never binned, never queued, culled).
 
 __global__ void __launch_bounds__(kStatBlock) k_chunk_stats(const FwdArgs a, ChunkStat* st)
 {
