@@ -190,16 +190,20 @@ constexpr Cand nc_c[] = {{2, 2, 2}, {2, 1, 2}, {1, 1, 2}, {1, 1, 1}};
 // (two, or one), `half` workgroups of kHalfBlock threads two to a CU, the
 // patches split over `split` workgroups.  A workgroup evaluates every 64-record
 // chunk against its units, 16 (8) wavefronts on four SIMDs, then writes its rows
-// out; `cus` (twice as many) run at a time, and the last round is rarely full.  Constants: instructions per chunk, unit
-// and pair and the fixed part of a workgroup, fitted to the times of every
-// feasible plan of 144 random problems (6 x 6 to 128 x 128 points, 256 to 1.6e5
-// pixels, 256 to 2048 bins, confocal and not): the plan with the least estimate
-// took 1.025 times the best plan's time in the geometric mean, the rule before
-// (the largest paired unit that gives a workgroup per CU, else split patches)
-// 1.79 times.  Float atomics of split patches: 55 G/s measured.
-double plan_cost(const nlos_params* p, double n, const Cand& c, int nu, bool half, int64_t units, int64_t split,
-                 int64_t cus)
+// out; `cus` (twice as many) run at a time, and the last round is rarely full.
+// Constants: instructions per chunk, unit and pair and the fixed part of a
+// workgroup, fitted to the times of every feasible plan of 144 random problems (6
+// x 6 to 128 x 128 points, 256 to 1.6e5 pixels, 256 to 2048 bins, confocal and
+// not): on those same problems the plan with the least estimate took 1.025 times
+// the best plan's time in the geometric mean, the rule before (the largest paired
+// unit that gives a workgroup per CU, else split patches) 1.79 times; on 80 others
+// (1 x 1 to 130 x 130 points, 100 to 4000 bins) it was 1.9 times faster than that
+// rule, and slower on two, by 6 and 9%.  Float atomics of split patches: 55 G/s
+// measured.
+inline __attribute__((always_inline)) double plan_cost(const nlos_params* p, double n, const Cand& c, int nu, bool half,
+                                                       int64_t units, int64_t split, int64_t cus)
 {
+    const double per_cu = 1.0 / (double)cus;   // (a constant where the call has all CUs)
     const bool conf = is_confocal(p);
     const double nh = (double)c.tl * c.tx * c.ty, T = p->n_bins;
     const double body = conf ? nh * (16.1 + 3.0 / c.ty + 3.0 / c.tx) : nh * 9.0 + 89.0 * c.tl + 74.0 * c.tx * c.ty;
@@ -214,7 +218,7 @@ double plan_cost(const nlos_params* p, double n, const Cand& c, int nu, bool hal
     double t;
     if (!half) {
         const double w = std::max(chunks * per, std::ceil(chunks / 16.0) * per * 5.1) + flush + 11700.0;
-        const double x = (double)wg / (double)cus;
+        const double x = (double)wg * per_cu;
         // (a unit near the border has fewer pairs in the window: two by a torus
         // shift even that out)
         t = w * (nu == 2 ? 1.0 : 1.1) * (x <= 1.0 ? 1.0 : rounds(x));
@@ -223,7 +227,7 @@ double plan_cost(const nlos_params* p, double n, const Cand& c, int nu, bool hal
         t = (w * 1.38 + flush + 10700.0) * 1.1;
     } else {
         const double w = std::max(2.0 * chunks * per, std::ceil(chunks / 8.0) * per * 5.1) + 1.36 * flush + 10700.0;
-        const double x = (double)wg / (double)(2 * cus);
+        const double x = (double)wg * (0.5 * per_cu);
         t = w * (x <= 1.0 ? 1.1 : rounds(x));
     }
     if (split > 1) t += 10000.0 + (double)n_hist(p) * T * (double)split * 0.044;
@@ -326,9 +330,13 @@ void plan_share(const nlos_params* p, int32_t n_patches, int stride, int64_t tar
     }
 }
 
-// `solo`: the call runs alone (one launch with the kernel variant that suits
-// it); else the plan is for a list that shares the GPU, `target` workgroups.
-int make_plan(const nlos_params* p, int32_t n_patches, int R, int64_t target, bool solo, nlos::Plan* plan)
+// What a plan is for: a call that runs alone (one launch with the kernel variant
+// that suits it), a list's request (paired units for `target` workgroups, its
+// share of the GPU), or only to see that there is one (no estimates: a call asks
+// for its workspace's size too).
+enum class PlanFor { alone, list, size };
+
+int make_plan(const nlos_params* p, int32_t n_patches, int R, int64_t target, PlanFor what, nlos::Plan* plan)
 {
     const bool conf = is_confocal(p);
     const Cand* cands = conf ? conf_c : nc_c;
@@ -373,7 +381,7 @@ int make_plan(const nlos_params* p, int32_t n_patches, int R, int64_t target, bo
         }
     }
     int64_t share_split = 0;   // from plan_share
-    if (largest >= 0 && !solo && !forced)
+    if (largest >= 0 && what == PlanFor::list && !forced)
         plan_share(p, n_patches, stride_of(T), target, &chosen, &share_split);
     if (chosen < 0) chosen = largest;
     int tw = T, n_tw = 1, pair = 1;
@@ -422,7 +430,7 @@ int make_plan(const nlos_params* p, int32_t n_patches, int R, int64_t target, bo
     plan->n_split = (int)split;
     plan->n_blocks = tiles * split;
     if (plan->n_blocks > 0x7fffffff || units > 0x7fffffff) return NLOS_EINVAL;
-    if (solo && pair && !forced) return plan_solo(p, n_patches, stride_of(T), plan);
+    if (what == PlanFor::alone && pair && !forced) return plan_solo(p, n_patches, stride_of(T), plan);
     return NLOS_OK;
 }
 
@@ -433,15 +441,14 @@ size_t stats_bytes(int32_t n_patches)
 }
 
 int forward_workspace(const nlos_params* p, int32_t n_patches, size_t* bytes, nlos::Plan* plan_out,
-                      int64_t target = kTargetBlocks, bool solo = true)
+                      int64_t target = kTargetBlocks, PlanFor what = PlanFor::size)
 {
     float taps[nlos::kMaxTaps];
     int32_t R = 0;
     int rc = jitter_taps(p->fwhm_ps, p->bin_ps, taps, &R);
     if (rc != NLOS_OK) return rc;
     nlos::Plan plan;
-    // (where only the size is asked for, any plan shows that there is one)
-    rc = make_plan(p, n_patches, R, target, solo && plan_out, &plan);
+    rc = make_plan(p, n_patches, R, target, what, &plan);
     if (rc != NLOS_OK) return rc;
     *bytes = stats_bytes(n_patches);
     if (plan_out) *plan_out = plan;
@@ -451,7 +458,7 @@ int forward_workspace(const nlos_params* p, int32_t n_patches, size_t* bytes, nl
 // Checks of one forward request, its plan (for `target` workgroups) and its
 // kernel arguments (all but the summaries pointer); *ws_need = workspace.
 int setup_forward(const nlos_params* p, const float* patches, int32_t n_patches, const int32_t* n_active,
-                  float* out, int64_t target, bool solo, nlos::FwdArgs* a, nlos::Plan* plan,
+                  float* out, int64_t target, PlanFor what, nlos::FwdArgs* a, nlos::Plan* plan,
                   size_t* ws_need)
 {
     int rc = params_ok(p);
@@ -460,7 +467,7 @@ int setup_forward(const nlos_params* p, const float* patches, int32_t n_patches,
     if (n_patches > 0 && !patches) return NLOS_EINVAL;
     if ((patches && !aligned(patches, 16)) || !aligned(out, 16) || (n_active && !aligned(n_active, 4)))
         return NLOS_EINVAL;
-    rc = forward_workspace(p, n_patches, ws_need, plan, target, solo);
+    rc = forward_workspace(p, n_patches, ws_need, plan, target, what);
     if (rc != NLOS_OK) return rc;
     rc = fill_args(p, patches, n_patches, n_active, out, a);
     if (rc != NLOS_OK) return rc;
@@ -529,7 +536,7 @@ int plan_batch(const nlos_request* reqs, int32_t n, FwdBatch* b)
         const double pairs = (double)n_hist(&r.params) * (double)std::max(r.n_patches, 1);
         const int64_t target = std::max<int64_t>(1, (int64_t)std::ceil(kTargetBlocks * pairs / total));
         size_t need = 0;
-        const int rc = setup_forward(&r.params, r.patches, r.n_patches, r.n_active, r.out, target, false, &b->args[i],
+        const int rc = setup_forward(&r.params, r.patches, r.n_patches, r.n_active, r.out, target, PlanFor::list, &b->args[i],
                                      &b->plans[i], &need);
         if (rc != NLOS_OK) return rc;
         work[i] = pairs / (double)std::max<int64_t>(1, b->plans[i].n_blocks);
@@ -1295,7 +1302,7 @@ int nlos_forward(const nlos_params* p, const float* patches, int32_t n_patches, 
     nlos::FwdArgs a;
     nlos::Plan plan;
     size_t need = 0;
-    int rc = setup_forward(p, patches, n_patches, n_active, out, kTargetBlocks, true, &a, &plan, &need);
+    int rc = setup_forward(p, patches, n_patches, n_active, out, kTargetBlocks, PlanFor::alone, &a, &plan, &need);
     if (rc != NLOS_OK) return rc;
     if (ws_bytes < need) return NLOS_ENOSPC;
     if (need > 0 && !ws) return NLOS_EINVAL;
@@ -1366,7 +1373,7 @@ int nlos_tick_plan(const nlos_tick_caps* caps, const nlos_sim_request* reqs, int
         const double pairs = (double)n_hist(&r.params) * (double)npx;
         const int64_t target = std::max<int64_t>(1, (int64_t)std::ceil(kTargetBlocks * pairs / std::max(total, 1.0)));
         size_t need = 0;
-        rc = setup_forward(&r.params, r.patches, npx, r.n_active, r.out, target, false, &fa[i], &pl[i], &need);
+        rc = setup_forward(&r.params, r.patches, npx, r.n_active, r.out, target, PlanFor::list, &fa[i], &pl[i], &need);
         if (rc != NLOS_OK) return rc;
         const nlos::Plan& plan = pl[i];
         const int v = nlos::tick_variant(plan.tx, plan.ty, fa[i].cosines != 0);
@@ -1525,7 +1532,7 @@ int nlos_forward_noalloc(const nlos_params* p, const float* patches, int32_t n_p
     nlos::FwdArgs a;
     nlos::Plan plan;
     size_t need = 0;
-    int rc = setup_forward(p, patches, n_patches, n_active, out, kTargetBlocks, true, &a, &plan, &need);
+    int rc = setup_forward(p, patches, n_patches, n_active, out, kTargetBlocks, PlanFor::alone, &a, &plan, &need);
     if (rc != NLOS_OK) return rc;
     if (n_patches > NLOS_NOALLOC_MAX_PATCHES || need > kNoAllocScratchBytes) return NLOS_ENOSPC;
     const int dev = device_check();
@@ -1546,6 +1553,14 @@ int nlos_forward_noalloc(const nlos_params* p, const float* patches, int32_t n_p
     return e == hipSuccess ? NLOS_OK : hip_fail(e);
 }
 
+// Workspace of nlos_simulate from its parts: the geometry's block counts, the
+// record summaries (those of nlos_forward), then the records' pair-loop
+// constants, 32 bytes per record.
+static size_t simulate_bytes(size_t geo, size_t fwd, int64_t pixels)
+{
+    return align_up(geo, 256) + align_up(fwd, 256) + (size_t)pixels * 32;
+}
+
 int nlos_simulate_workspace_bytes(const nlos_params* p, const nlos_grid* g, size_t* bytes)
 {
     if (!bytes || !grid_ok(g) || (int64_t)g->nx * g->ny > NLOS_MAX_PATCHES) return NLOS_EINVAL;
@@ -1554,9 +1569,7 @@ int nlos_simulate_workspace_bytes(const nlos_params* p, const nlos_grid* g, size
     if (rc != NLOS_OK) return rc;
     rc = nlos_forward_workspace_bytes(p, g->nx * g->ny, &fwd);
     if (rc != NLOS_OK) return rc;
-    // the geometry's block counts, the record summaries (those of
-    // nlos_forward), then the records' pair-loop constants, 32 bytes per record
-    *bytes = align_up(geo, 256) + align_up(fwd, 256) + (size_t)g->nx * g->ny * 32;
+    *bytes = simulate_bytes(geo, fwd, (int64_t)g->nx * g->ny);
     return NLOS_OK;
 }
 
@@ -1572,17 +1585,16 @@ int nlos_simulate(const nlos_params* p, const nlos_grid* g, const float* depth, 
     nlos::FwdArgs a;
     nlos::Plan plan;
     size_t need_fwd = 0;
-    rc = setup_forward(p, patches, n_patches, n_active, out, kTargetBlocks, true, &a, &plan, &need_fwd);
+    rc = setup_forward(p, patches, n_patches, n_active, out, kTargetBlocks, PlanFor::alone, &a, &plan, &need_fwd);
     if (rc != NLOS_OK) return rc;
-    size_t need = 0;
-    rc = nlos_simulate_workspace_bytes(p, g, &need);
+    size_t geo = 0;
+    rc = nlos_patches_workspace_bytes(g, &geo);
     if (rc != NLOS_OK) return rc;
-    if (ws_bytes < need) return NLOS_ENOSPC;
+    // (the size from the plan just made, not from another one: 0.6 us of a call of 17)
+    if (ws_bytes < simulate_bytes(geo, need_fwd, n_patches)) return NLOS_ENOSPC;
     if (!ws || !aligned(ws, 256)) return NLOS_EINVAL;
     const int dev = device_check();
     if (dev != NLOS_OK) return dev;
-    size_t geo = 0;
-    nlos_patches_workspace_bytes(g, &geo);
     unsigned char* w = static_cast<unsigned char*>(ws);
     ga.counts = reinterpret_cast<int32_t*>(w);
     ga.offsets = ga.n_blocks <= nlos::kScanFreeBlocks ? nullptr : ga.counts + ga.n_blocks;
@@ -1947,7 +1959,7 @@ int nlos_get_plan(const nlos_params* p, int32_t n_patches, nlos_plan_info* info)
     int rc = jitter_taps(p->fwhm_ps, p->bin_ps, taps, &R);
     if (rc != NLOS_OK) return rc;
     nlos::Plan plan;
-    rc = make_plan(p, n_patches, R, kTargetBlocks, true, &plan);
+    rc = make_plan(p, n_patches, R, kTargetBlocks, PlanFor::alone, &plan);
     if (rc != NLOS_OK) return rc;
     info->tl = plan.tl;
     info->tx = plan.tx;

@@ -13,7 +13,7 @@ extern "C" int host_forward_plan(const nlos_params* p, int32_t n_patches, int64_
     int rc = jitter_taps(p->fwhm_ps, p->bin_ps, taps, &R);
     if (rc != NLOS_OK) return rc;
     nlos::Plan plan;
-    rc = make_plan(p, n_patches, R, target, solo != 0, &plan);
+    rc = make_plan(p, n_patches, R, target, solo ? PlanFor::alone : PlanFor::list, &plan);
     if (rc != NLOS_OK) return rc;
     const int64_t v[10] = {plan.tl, plan.tx, plan.ty, plan.pair, plan.one, plan.groups, plan.n_split, plan.n_tw,
                            plan.n_blocks, (int64_t)plan.lds_bytes};
