@@ -39,7 +39,7 @@ FP32_FMA_CEILING_TFLOPS = 78.6
 TRAFFIC_BYTES = (4304.6 * 2.0 + 16393.8 * 1.0) * 1024
 TRAFFIC_SOURCES = ("paper_2506_03747_amd/csrc/nlos_forward.hip", "paper_2506_03747_amd/csrc/nlos_device.h",
                    "paper_2506_03747_amd/csrc/nlos_internal.h")
-TRAFFIC_HASH = "cf1f3d2f3c22d260"
+TRAFFIC_HASH = "3648e27a57890396"
 
 
 def traffic_for_sources():

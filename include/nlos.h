@@ -386,7 +386,9 @@ int nlos_tick_graph_destroy(nlos_tick_graph* graph);
  * sub-bin offset t = u - floor(u) - 1/2 of 8 terms (sigma < 1.6), 7 (< 2.5),
  * 6 (< 4.9) or 5: each pair adds w (-t)^m, and the rows are convolved with the
  * polynomials' coefficients; they are within 2.5e-8 (relative L2 over the
- * support, root mean square over t) of the samples.
+ * support, root mean square over t) of the samples.  There floor(u) is taken
+ * from an arrival that may be 1e-4 bins short of u, so the support's ends can
+ * lie one bin further on (below the Gaussian's tail at 6 sigma).
  */
 int nlos_forward_smooth_workspace_bytes(const nlos_params* p, int32_t n_patches, size_t* bytes);
 

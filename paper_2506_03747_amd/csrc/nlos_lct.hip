@@ -257,10 +257,11 @@ __global__ void __launch_bounds__(256) k_lct_list(const LctArgs a, const LctSamp
 // wrap, a sample is within 2^-63 of that sum, and one bright pixel among dim
 // ones costs them no bits (2^62 / (N^2 max w) did: beside one 10^10 times
 // brighter a pixel kept 16 at N = 64).  Root mean square error of the rows
-// against that of fp64 transforms (smooth surface, albedo 0.05 to 1): before the
-// resampling 0.41 of it at N = 64, 0.57 at 128, 0.92 at 384, 1.65 at 512 (0.8,
-// 1.6, 2.6 and 4.7 with the former scale); after it, relative to the output,
-// 1 to 3 10^-16 against 3 10^-10 to 8 10^-12, as it amplifies the transforms'
+// against that of fp64 transforms (models of both on a smooth surface, albedo
+// 0.05 to 1): before the resampling 0.30 of it at N = 64, 0.57 at 128, 0.92 at
+// 384, 1.65 at 512 (0.8, 1.6, 2.6 and 4.7 with the former scale), 0.12 to 0.73
+// with three pixels 10^4 times brighter (31 to 10^4); after it, relative to the
+// output, 1 to 3 10^-16 against 10^-9 to 8 10^-12, as it amplifies the transforms'
 // noise in the first bins.
 // Bound: the LDS adds (bank conflicts included) and VALU, about 15 cycles per
 // wavefront and pair; then the write-out's fp64 resampling and jitter.  128^2
