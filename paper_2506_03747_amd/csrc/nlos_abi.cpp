@@ -301,8 +301,7 @@ void plan_share(const nlos_params* p, int32_t n_patches, int stride, int64_t tar
     const bool conf = is_confocal(p);
     const Cand* cands = conf ? conf_c : nc_c;
     const int64_t L = conf ? 1 : (int64_t)p->laser.nx * p->laser.ny;
-    nlos::Plan alone;
-    const bool may_split = plan_solo(p, n_patches, stride, &alone) == NLOS_OK && alone.n_split > 1;
+    int may_split = -1;   // (asked only where there are CUs to split for)
     const int rule = *chosen;
     double best = 0.0, kept = 0.0;
     bool any = false;
@@ -312,8 +311,12 @@ void plan_share(const nlos_params* p, int32_t n_patches, int stride, int64_t tar
         const int64_t units = (L + c.tl - 1) / c.tl * ((p->relay.nx + c.tx - 1) / c.tx) *
                               (int64_t)((p->relay.ny + c.ty - 1) / c.ty);
         const int64_t groups = (units + 1) / 2;
-        const int64_t most =
-            may_split ? std::max<int64_t>(1, std::min<int64_t>(target / groups, n_patches / nlos::kBlock)) : 1;
+        int64_t most = std::max<int64_t>(1, std::min<int64_t>(target / groups, n_patches / nlos::kBlock));
+        if (most > 1 && may_split < 0) {
+            nlos::Plan alone;
+            may_split = plan_solo(p, n_patches, stride, &alone) == NLOS_OK && alone.n_split > 1 ? 1 : 0;
+        }
+        if (may_split <= 0) most = 1;
         for (int64_t sp = 1; sp <= most; sp += std::max<int64_t>(1, most - 1)) {
             const double t = plan_cost(p, 0.6 * (double)n_patches, c, 2, false, units, sp, target);
             if (i == rule && sp == 1) kept = t;
